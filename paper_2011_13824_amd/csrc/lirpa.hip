@@ -5086,6 +5086,8 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+#include "win_pass.hpp"
+
 // Projected Adam ascent step (bias-corrected), alpha clipped to [0, 1].
 __global__ void __launch_bounds__(kBlock) k_adam(long n, float* __restrict__ alpha,
                                                  float* __restrict__ m, float* __restrict__ v,
@@ -5467,6 +5469,9 @@ struct Plan {
   size_t off_kidx1 = 0, off_list1 = 0, off_cnt1 = 0;  // its unstable layer-1 neurons' ranks
   size_t off_kidx2 = 0, off_list2 = 0, off_cnt2 = 0;  // and layer-2 neurons'
   size_t off_psel = 0;  // its position pairs of layer-2 tiles per sub-domain
+  // split weight fragments of the receptive-field passes (k_win_pass), by layer: T^T, T
+  size_t off_fb[kMaxLayers + 1] = {}, off_ff[kMaxLayers + 1] = {};
+  size_t off_wpart = 0, off_wflag = 0;  // their reverse sweep's partial sums and block flags
   long fwd_floats = 0;
   // lower and upper bounds in one call: the spec rows [C; -C] (or -C alone) and, for the bound,
   // the [Bc][2S] bounds of those rows before they are split into lb and ub
@@ -5531,7 +5536,93 @@ long pass2_blocks(const lirpa_net* net, long nb) {
 
 // Whether bound mode (no gradient tape) runs pass k, 2 <= k < L, in one kernel that keeps the
 // pass's coefficients on chip: such a pass needs no bound-matrix slab.
-bool pass_on_chip(const lirpa_net* net, int k, long Bc);
+// (dense: as if no pass ran k_win_pass)
+bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool dense = false);
+
+// k_win_pass for pass k: its windows and LDS layout.  False when a layer up to k is no
+// convolution, or the windows do not fit in LDS.
+struct WinLaunch {
+  WinDesc d;
+  size_t lds = 0;
+  int threads = 0;
+};
+bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out) {
+  if (k < 2 || k >= net->L || k - 1 >= kWinMax) return false;
+  for (int m = 1; m <= k; ++m)
+    if (net->T[m - 1].kind != LIRPA_CONV2D) return false;
+  WinLaunch q{};
+  WinDesc& d = q.d;
+  const lirpa_layer& tk = net->T[k - 1];
+  d.k = k;
+  d.H = tk.out_h;
+  d.W = tk.out_w;
+  d.C = tk.out_c;
+  d.G = (tk.out_c + 7) / 8;
+  d.K = tk.k;
+  d.Wk = tk.W;
+  d.bk = tk.b;
+  int w = 1, S = 1, P = 0;
+  double o = 0;  // LDS bytes so far (a double: windows of unusual nets can be huge)
+  double slot[2] = {0, 0};
+  for (int m = k - 1; m >= 0; --m) {
+    const lirpa_layer& t = net->T[m];  // T_(m+1): from g^(m+1) down to g^(m)
+    WinLayer& l = d.L[m];
+    w = (w - 1) * t.stride + t.k;
+    P = P * t.stride + t.pad;
+    S *= t.stride;
+    if (w > 512) return false;
+    l.w = w;
+    l.S = S;
+    l.P = P;
+    l.H = t.in_h;
+    l.W = t.in_w;
+    l.C = t.in_c;
+    l.Cq = m >= 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
+    if (m >= 1) {
+      const lirpa_layer& tm = net->T[m - 1];
+      l.K = tm.k;
+      l.s = tm.stride;
+      l.t = (tm.k + tm.stride - 1) / tm.stride;
+      const int cqi = m - 1 >= 1 ? 2 * ((tm.in_c + 7) / 8) : (tm.in_c + 3) / 4;
+      l.nmt = (l.s * l.s * 4 * cqi + 15) / 16;
+      l.nks = (l.t * l.t * 4 * l.Cq + 31) / 32;
+      l.nmtf = (4 * l.Cq + 15) / 16;
+      l.nksf = (l.K * l.K * 4 * cqi + 31) / 32;
+      l.poff = net->poff[m];
+      l.noff = net->off[m];
+      const double ent = (double)w * w * 4 * l.Cq;
+      slot[m & 1] = std::max(slot[m & 1], 3 * (ent * 32 + 16));
+      if (o + slot[0] + slot[1] + ent * 16 > kWinLds) return false;
+      l.o_prm = (int)o;
+      o += ent * 16;
+      if (grad) {
+        l.o_at = (int)o;
+        o += ent * 64;
+        l.part = d.npart;
+        d.npart += (int)ent * (m > 1 ? 3 : 1);
+      }
+      l.plane = (int)ent * 32 + 16;
+    } else if (grad) {
+      slot[0] = std::max(slot[0], (double)w * w * 16 * 4 * l.Cq);
+    }
+  }
+  if (o + slot[0] + slot[1] + 4096 > kWinLds) return false;
+  for (int m = 1; m < k; ++m) d.L[m].o_pl = (int)(o + (m & 1 ? slot[0] : 0));
+  d.o_x = (int)o;
+  o += slot[0] + slot[1];
+  d.o_red = (int)o;
+  // four waves a block where several blocks share a CU, else eight
+  q.threads = o <= 53 * 1024 ? 256 : 512;
+  q.lds = (size_t)o + (q.threads / 64) * 32 * 4 + 128;
+  *out = q;
+  return true;
+}
+
+// Whether pass k runs k_win_pass: its reverse sweep in a gradient plan (every chain of
+// convolutions but the pass 2 that k_pass2_window_grad takes), its bound (what no specialised
+// window kernel takes).
+bool win_grad_pass(const lirpa_net* net, int k);
+bool win_bound_pass(const lirpa_net* net, int k);
 
 // The fused two-layer witness forward of pass 3 (k_fwd_conv12) for a net whose T_1 is
 // Conv(3 -> C1, k4 s2 p1, 32x32), T_2 Conv(C1 -> C2, k4 s2 p1, 16x16) and T_3 Linear, with
@@ -5564,10 +5655,14 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
   int nw_unused = 0;
   const bool win2 = (mode == 0 && pass2_kernel_for(net, &nw_unused) != nullptr) ||
                     (mode == 1 && pass2_grad_kernel_for(net) != nullptr);
+  // passes that keep everything on chip in both directions
+  auto onchip = [&](int k) {
+    return (k == 2 && win2) || (mode == 1 ? win_grad_pass(net, k) : win_bound_pass(net, k));
+  };
   for (int k = 2; k <= L; ++k) {
     long R = (k < L) ? 2 * net->n[k] : S;
     long qp = round_up(Bc * R, 64);
-    if (k == 2 && win2 && k < L) continue;
+    if (k < L && onchip(k)) continue;
     qpmax = std::max(qpmax, qp);
     if (mode == 0 && k < L && pass_on_chip(net, k, Bc)) continue;
     int mtop = (k < L) ? k - 1 : L;  // slabs hold A over h^(m), m = mtop..1
@@ -5619,6 +5714,7 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
         o = align256(o + (size_t)pass2_blocks(net, Bc));
         continue;
       }
+      if (k < L && onchip(k)) continue;
       for (int m = 0; m <= k - 1; ++m) {
         p.off_tape[k][m] = o;  // over x: signs, one byte per entry
         o = align256(o + (size_t)net->n[m] * qp * (m == 0 ? 1 : 4));
@@ -5637,7 +5733,7 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
     p.off_lbt = o; o = align256(o + (size_t)Bc * S * 4);
     long gpart = 0, gflag = 0;
     for (int k = 2; k <= L - 1; ++k) {
-      if ((k == 2 && win2) || (2 * net->n[k]) % 8) continue;
+      if (onchip(k) || (2 * net->n[k]) % 8) continue;
       const long qp8 = round_up(Bc * 2 * net->n[k], 64) / 8;
       gflag = std::max(gflag, qp8);
       for (int m = 1; m <= k - 1; ++m) gpart = std::max(gpart, qp8 * 3 * net->n[m]);
@@ -5669,14 +5765,45 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
       o = align256(o + (size_t)Bc * 4 * 8 * 2 * 4);
     }
   }
-  p.total = o;
-  // kernels address a slab with 32-bit element offsets
-  long big = std::max(slab, p.fwd_floats);
-  if (mode == 1)
-    for (int k = 2; k <= L; ++k) {
-      if (k == 2 && win2 && k < L) continue;
-      big = std::max(big, net->n[0] * round_up(Bc * ((k < L) ? 2 * net->n[k] : S), 64));
+  long wblocks = 0, wpart = 0;
+  for (int k = 2; k < L; ++k) {
+    WinLaunch q;
+    const bool gw = mode == 1 && win_grad_pass(net, k);
+    if (!(gw || win_bound_pass(net, k)) || !win_desc(net, k, gw, &q)) continue;
+    for (int m = 1; m < k; ++m) {
+      const WinLayer& l = q.d.L[m];
+      if (!p.off_fb[m]) {
+        p.off_fb[m] = o;
+        o = align256(o + (size_t)l.nmt * l.nks * 3072);
+      }
+      if (gw && !p.off_ff[m]) {
+        p.off_ff[m] = o;
+        o = align256(o + (size_t)l.nmtf * l.nksf * 3072);
+      }
     }
+    if (gw) {
+      const long nblk = Bc * q.d.G * q.d.H * q.d.W;
+      wblocks = std::max(wblocks, nblk);
+      wpart = std::max(wpart, nblk * q.d.npart);
+    }
+  }
+  if (wblocks) {
+    p.off_wpart = o;
+    o = align256(o + (size_t)wpart * 4);
+    p.off_wflag = o;
+    o = align256(o + (size_t)wblocks);
+  }
+  p.total = o;
+  // Kernels address a slab with 32-bit element offsets.  The limit counts the slabs of a dense
+  // pass also where k_win_pass needs none, so that the largest chunk of a net does not depend on
+  // which of its passes run it.
+  long big = std::max(slab, p.fwd_floats);
+  for (int k = 2; k <= L; ++k) {
+    if (k < L && ((k == 2 && win2) || (mode == 0 && pass_on_chip(net, k, Bc, true)))) continue;
+    const long qp = round_up(Bc * ((k < L) ? 2 * net->n[k] : S), 64);
+    for (int m = mode == 1 ? 0 : 1; m <= (k < L ? k - 1 : L); ++m)
+      big = std::max(big, net->n[m] * qp);
+  }
   if (big >= (1L << 31)) p.total = (size_t)-1;
   return p;
 }
@@ -6278,12 +6405,119 @@ Pass4Kernel pass4_kernel_for(const lirpa_net* net) {
   return nullptr;
 }
 
-bool pass_on_chip(const lirpa_net* net, int k, long Bc) {
+bool win_grad_pass(const lirpa_net* net, int k) {
+  WinLaunch q;
+  return !(k == 2 && pass2_grad_kernel_for(net)) && win_desc(net, k, true, &q);
+}
+
+bool win_bound_pass(const lirpa_net* net, int k) {
+  int nw = 0;
+  if (k == 2 && pass2_kernel_for(net, &nw)) return false;
+  if (k == 3 && pass3_kernel_for(net)) return false;
+  if (k == 4 && pass4_kernel_for(net)) return false;
+  WinLaunch q;
+  return win_desc(net, k, false, &q);
+}
+
+// Launches k_win_pass for pass k of the chunk; 1 when the pass does not run it.
+int win_pass(const Chunk& c, int k, bool grad) {
+  const lirpa_net* net = c.net;
+  WinLaunch q;
+  if (!(grad ? win_grad_pass(net, k) : win_bound_pass(net, k)) || !win_desc(net, k, grad, &q))
+    return 1;
+  for (int m = 1; m < k; ++m) {
+    q.d.L[m].fb = at<uint4v>(c.ws, c.p->off_fb[m]);
+    if (grad) q.d.L[m].ff = at<uint4v>(c.ws, c.p->off_ff[m]);
+  }
+  WinArgs a{};
+  a.a_lo = at<float>(c.ws, c.p->off_alo);
+  a.a_up = at<float>(c.ws, c.p->off_aup);
+  a.b_up = at<float>(c.ws, c.p->off_bup);
+  a.bias = at<float>(c.ws, c.p->off_bz);
+  a.pstride = net->pstride;
+  a.n_relu = net->n_relu;
+  a.noff_k = net->off[k];
+  a.eps = c.eps;
+  a.lo = c.L;
+  a.hi = c.U;
+  if (grad) {
+    a.gl = at<float>(c.ws, c.p->off_gl);
+    a.gu = at<float>(c.ws, c.p->off_gu);
+    a.part = at<float>(c.ws, c.p->off_wpart);
+    a.pflag = at<unsigned char>(c.ws, c.p->off_wflag);
+  }
+  const void* kern = grad ? reinterpret_cast<const void*>(k_win_pass<true>)
+                          : reinterpret_cast<const void*>(k_win_pass<false>);
+  if (q.lds > 65536 && hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)q.lds) != hipSuccess)
+    return fail(LIRPA_EDEVICE, "cannot reserve %zu bytes of LDS", q.lds);
+  const unsigned blocks = (unsigned)(c.nb * q.d.G * q.d.H * q.d.W);
+  if (int e = launch_k(tag(grad ? "win_grad" : "win_bound", 1, k), c.st, [&] {
+        if (grad)
+          hipLaunchKernelGGL(k_win_pass<true>, dim3(blocks), dim3(q.threads), q.lds, c.st, q.d, a);
+        else
+          hipLaunchKernelGGL(k_win_pass<false>, dim3(blocks), dim3(q.threads), q.lds, c.st, q.d,
+                             a);
+      }))
+    return e;
+  if (!grad) return LIRPA_OK;
+  for (int m = k - 1; m >= 1; --m) {
+    const long off = net->off[m];
+    (void)off;
+    if (int e = launch_k(tag("win_gather", m, k), c.st, [&] {
+          hipLaunchKernelGGL(k_win_gather, grid_for(c.nb * net->n[m]), dim3(kBlock), 0, c.st,
+                             c.nb, q.d.L[m], m, q.d.H, q.d.W, q.d.G, q.d.npart, a.part, a.pflag,
+                             at<int8_t>(c.ws, c.p->off_code), c.L, c.U, net->n_relu,
+                             at<float>(c.ws, c.p->off_ga), at<float>(c.ws, c.p->off_gl),
+                             at<float>(c.ws, c.p->off_gu));
+        }))
+      return e;
+  }
+  return LIRPA_OK;
+}
+
+// The split weight fragments of every layer that k_win_pass reads in this call.
+int win_frags(const lirpa_net* net, const Plan& p, void* ws, hipStream_t st) {
+  FragJobs jobs{};
+  int most = 0;
+  auto flush = [&]() -> int {
+    if (!jobs.n) return LIRPA_OK;
+    const int n = jobs.n, big = most;
+    const int e = launch_k("win_frags", st, [&] {
+      hipLaunchKernelGGL(k_win_frags, dim3((unsigned)((big * 64 + 255) / 256), (unsigned)n),
+                         dim3(256), 0, st, jobs);
+    });
+    jobs.n = 0;
+    most = 0;
+    return e;
+  };
+  for (int m = 1; m < net->L && m < kWinMax; ++m)
+    for (int kind = 0; kind < 2; ++kind) {
+      const size_t off = kind ? p.off_ff[m] : p.off_fb[m];
+      if (!off) continue;
+      const lirpa_layer& t = net->T[m - 1];
+      const int tt = (t.k + t.stride - 1) / t.stride;
+      const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
+      const int cqo = 2 * ((t.out_c + 7) / 8);
+      FragJob f{t.W, t.in_c, t.out_c, t.k, t.stride, tt, cqi, cqo, kind, 0, 0,
+                at<uint4v>(ws, off)};
+      f.nmt = kind ? (4 * cqo + 15) / 16 : (t.stride * t.stride * 4 * cqi + 15) / 16;
+      f.nks = kind ? (t.k * t.k * 4 * cqi + 31) / 32 : (tt * tt * 4 * cqo + 31) / 32;
+      most = std::max(most, f.nmt * f.nks);
+      jobs.j[jobs.n++] = f;
+      if (jobs.n == kFragJobs)
+        if (int e = flush()) return e;
+    }
+  return flush();
+}
+
+bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool dense) {
   // the same choices, in the same order, as bound_chunk makes for a chunk without a tape
   int nw = 0;
   if (k == 2) return pass2_kernel_for(net, &nw) != nullptr;
   if (k == 4 && pass4_kernel_for(net)) return true;
   if (k == 3 && pass3_kernel_for(net)) return true;
+  if (!dense && win_bound_pass(net, k)) return true;
   if (!fc_bound_for(net, k, &nw)) return false;
   // fc_open_ok holds for every chunk of at most Bc sub-domains when it holds for Bc
   Chunk c{};
@@ -6327,7 +6561,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    if (k == 4 && !c.tape) {
+    if (k == 4 && (!c.tape || win_grad_pass(net, k))) {
       int e = pass4_window(c);
       if (e != 1) {
         if (e) return e;
@@ -6335,8 +6569,16 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    if (k == 3 && !c.tape) {
+    if (k == 3 && (!c.tape || win_grad_pass(net, k))) {
       int e = pass3_window(c);
+      if (e != 1) {
+        if (e) return e;
+        if (int e2 = relax_layer(c, k)) return e2;
+        continue;
+      }
+    }
+    if (!c.tape || win_grad_pass(net, k)) {
+      int e = win_pass(c, k, false);
       if (e != 1) {
         if (e) return e;
         if (int e2 = relax_layer(c, k)) return e2;
@@ -6503,6 +6745,7 @@ int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0
     job.S = S;
     total += (long)S * (net->n[net->L - 1] + 1);
   }
+  if (int e = win_frags(net, p, ws, st)) return e;
   return launch_k(tag("setup", 1, 1), st, [&] {
     hipLaunchKernelGGL(k_setup, grid_for(total), dim3(kBlock), 0, st, job);
   });
@@ -6560,6 +6803,13 @@ int grad_chunk(const Chunk& c, int full) {
                                c.nb, dlayer(t1), dlayer(t2), t2.k * t2.k, part, pflag, code,
                                net->n_relu, ga);
         });
+        if (e) return e;
+        continue;
+      }
+    }
+    if (P < L) {
+      const int e = win_pass(c, P, true);
+      if (e != 1) {
         if (e) return e;
         continue;
       }

@@ -1,0 +1,72 @@
+"""Receptive-field passes of convolution chains of any geometry, against the fp64 oracle: bounds,
+intermediate bounds and gradients of nets whose windows have every edge the kernel handles
+(strides 1 to 4, kernels 1 to 7 larger than the map, taps that do not divide by the stride,
+channel counts off the 4, 8 and 16 of its tiles, up to four convolutions), and of one whose
+windows do not fit on chip (the dense stages).
+
+Tolerance: a bound is at most four chained fp32 sums of up to 2,000 terms, each within 8e-7 of its
+2-norm (the fp32 matrix instruction's measured error at that length); with a factor 3 for
+cancellation 1e-5 (1 + |ref|).  Gradients: the same, normwise, with the kink rule of the gradient
+tests."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+from paper_2011_13824_amd import lirpa
+from paper_2011_13824_amd import workloads as wl
+from tests.test_gpu_grad import check_grad, dev, one_sided
+
+pytestmark = pytest.mark.gpu
+
+NETS = {
+    "stride2-k3": [wl.conv(2, 9, 5, 3, 2, 1), wl.conv(5, 5, 9, 3, 1, 1), wl.fc(225, 6),
+                   wl.fc(6, 3)],
+    "k7-stride4": [wl.conv(1, 11, 17, 7, 4, 3), wl.conv(17, 3, 6, 2, 1, 0), wl.fc(24, 5),
+                   wl.fc(5, 3)],
+    "four-convs": [wl.conv(5, 7, 3, 3, 1, 1), wl.conv(3, 7, 10, 3, 2, 0), wl.conv(10, 3, 8, 2, 1, 1),
+                   wl.conv(8, 4, 20, 4, 2, 1), wl.fc(80, 3)],
+    "k-over-map": [wl.conv(3, 6, 8, 5, 3, 2), wl.conv(8, 2, 33, 1, 1, 0), wl.fc(132, 3)],
+    "wide-channels": [wl.conv(3, 6, 40, 3, 1, 1), wl.conv(40, 6, 12, 3, 2, 1), wl.fc(108, 3)],
+    "conv-last": [wl.conv(1, 6, 4, 4, 2, 1), wl.conv(4, 3, 16, 3, 1, 1), wl.conv(16, 3, 1, 3, 1, 0)],
+    "off-chip": [wl.conv(1, 4, 64, 7, 1, 3), wl.conv(64, 4, 2, 7, 1, 3), wl.fc(32, 3)],
+}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lirpa.load()
+
+
+def close(name, got, want):
+    excess = np.abs(got - want) - 1e-5 * (1 + np.abs(want))
+    print(f"{name}: max |gpu - oracle| = {np.abs(got - want).max():.3g}", flush=True)
+    assert np.all(excess <= 0), f"{name}: off by {excess.max():.3g} beyond tolerance"
+
+
+@pytest.mark.parametrize("name", sorted(NETS))
+@pytest.mark.parametrize("B", [1, 7])
+def test_windows(name, B):
+    arch = NETS[name]
+    layers = wl.random_net(arch, 5 + len(name))
+    rng = np.random.default_rng(len(name))
+    x0 = rng.uniform(0, 1, wl.n_in(arch[0])).astype(np.float32)
+    eps = 0.1
+    C = wl.margin_spec(3, 1) if wl.n_out(arch[-1]) == 3 else np.ones((1, 1), np.float32)
+    rnet = ref.RefNet(layers)
+    split = wl.make_splits(B, rnet.n_relu, 6, B, ref.root_unstable(rnet, x0, eps, C))
+    alpha = rng.uniform(0.05, 0.95, (B, rnet.n_relu)).astype(np.float32)
+    net = lirpa.Network(layers)
+    for a in (None, alpha):
+        lb, l, u = net.bound(dev(x0), eps, dev(C), dev(split), dev(a), want_lu=True)
+        lr, llr, ulr, _ = ref.bound(rnet, x0, eps, C, split, a)
+        close(f"{name} lb", lb.cpu().double().numpy(), lr)
+        close(f"{name} l", l.cpu().double().numpy(), llr)
+        close(f"{name} u", u.cpu().double().numpy(), ulr)
+    lb, g = net.bound_grad(dev(x0), eps, dev(C), dev(split), dev(alpha))
+    lr, gr = ref.bound_grad(rnet, x0, eps, C, split, alpha)
+    close(f"{name} grad lb", lb.cpu().double().numpy(), lr)
+    check_grad(f"{name} grad", g.cpu().double().numpy(), gr, split,
+               lambda b, j: one_sided(rnet, x0, eps, C, split, alpha, b, j))
