@@ -5087,6 +5087,7 @@ __global__ void __launch_bounds__(256)
 }
 
 #include "win_pass.hpp"
+#include "conv_split.hpp"
 
 // Projected Adam ascent step (bias-corrected), alpha clipped to [0, 1].
 __global__ void __launch_bounds__(kBlock) k_adam(long n, float* __restrict__ alpha,
@@ -5448,6 +5449,9 @@ __global__ void __launch_bounds__(kBlock)
 struct Plan {
   long Bc = 0;
   int mode = 0;
+  // the split kernels (k_win_pass, k_convT_split, k_conv_split) may run; false only for a
+  // workspace too small for their weight fragments
+  bool split = true;
   size_t off_l = 0, off_u = 0, off_alo = 0, off_aup = 0, off_bup = 0, off_code = 0;
   size_t off_l1u1 = 0, off_slab0 = 0, off_slab1 = 0, off_beta = 0, total = 0;
   size_t off_wsp = 0;  // C W_L [S][n_{L-1}], then C b_L [S] (L >= 2, T_L fully connected)
@@ -5536,8 +5540,8 @@ long pass2_blocks(const lirpa_net* net, long nb) {
 
 // Whether bound mode (no gradient tape) runs pass k, 2 <= k < L, in one kernel that keeps the
 // pass's coefficients on chip: such a pass needs no bound-matrix slab.
-// (dense: as if no pass ran k_win_pass)
-bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool dense = false);
+// (split: k_win_pass may run)
+bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool split);
 
 // k_win_pass for pass k: its windows and LDS layout.  False when a layer up to k is no
 // convolution, or the windows do not fit in LDS.
@@ -5621,8 +5625,37 @@ bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out) {
 // Whether pass k runs k_win_pass: its reverse sweep in a gradient plan (every chain of
 // convolutions but the pass 2 that k_pass2_window_grad takes), its bound (what no specialised
 // window kernel takes).
-bool win_grad_pass(const lirpa_net* net, int k);
-bool win_bound_pass(const lirpa_net* net, int k);
+// (split: Plan::split, here and below)
+bool win_grad_pass(const lirpa_net* net, int k, bool split);
+bool win_bound_pass(const lirpa_net* net, int k, bool split);
+
+// Split fragments of layer m (kind 0: T^T, 1: T), shared by k_win_pass and the split stages.
+// The channels below T_m come in eights, those of x and the rows that only feed an epilogue in
+// quads.
+FragJob frag_job(const lirpa_net* net, int m, int kind) {
+  const lirpa_layer& t = net->T[m - 1];
+  const int tt = (t.k + t.stride - 1) / t.stride;
+  const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
+  const int cqo = 2 * ((t.out_c + 7) / 8);
+  FragJob f{t.W, t.in_c, t.out_c, t.k, t.stride, tt, cqi, cqo, kind, 0, 0, nullptr};
+  f.nmt = kind ? (4 * cqo + 15) / 16 : (t.stride * t.stride * 4 * cqi + 15) / 16;
+  f.nks = kind ? (t.k * t.k * 4 * cqi + 31) / 32 : (tt * tt * 4 * cqo + 31) / 32;
+  return f;
+}
+size_t frag_bytes(const lirpa_net* net, int m, int kind) {
+  const FragJob f = frag_job(net, m, kind);
+  return (size_t)f.nmt * f.nks * 3072;
+}
+bool split_back(const lirpa_net* net, int m, bool split);
+bool split_fwd(const lirpa_net* net, int m, bool split);
+// Geometry and LDS of k_convT_split (dir 0) or k_conv_split (dir 1: over a z slab, 2: over the
+// sign tape) for layer t, the net's m-th; false for other layers, and when the ring does not fit.
+struct SplitLaunch {
+  ConvSplit c;
+  size_t lds = 0;
+  int threads = 0;
+};
+bool conv_split_desc(const lirpa_layer& t, int m, int dir, SplitLaunch* out);
 
 // The fused two-layer witness forward of pass 3 (k_fwd_conv12) for a net whose T_1 is
 // Conv(3 -> C1, k4 s2 p1, 32x32), T_2 Conv(C1 -> C2, k4 s2 p1, 16x16) and T_3 Linear, with
@@ -5646,8 +5679,9 @@ Fwd12Kernel fwd12_for(const lirpa_net* net) {
   return nullptr;
 }
 
-Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
+Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0, bool split = true) {
   Plan p;
+  p.split = split;
   p.Bc = Bc;
   p.mode = mode;
   const int L = net->L;
@@ -5657,14 +5691,14 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
                     (mode == 1 && pass2_grad_kernel_for(net) != nullptr);
   // passes that keep everything on chip in both directions
   auto onchip = [&](int k) {
-    return (k == 2 && win2) || (mode == 1 ? win_grad_pass(net, k) : win_bound_pass(net, k));
+    return (k == 2 && win2) || (mode == 1 ? win_grad_pass(net, k, split) : win_bound_pass(net, k, split));
   };
   for (int k = 2; k <= L; ++k) {
     long R = (k < L) ? 2 * net->n[k] : S;
     long qp = round_up(Bc * R, 64);
     if (k < L && onchip(k)) continue;
     qpmax = std::max(qpmax, qp);
-    if (mode == 0 && k < L && pass_on_chip(net, k, Bc)) continue;
+    if (mode == 0 && k < L && pass_on_chip(net, k, Bc, split)) continue;
     int mtop = (k < L) ? k - 1 : L;  // slabs hold A over h^(m), m = mtop..1
     for (int m = 1; m <= mtop; ++m) slab = std::max(slab, net->n[m] * qp);
   }
@@ -5765,20 +5799,30 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
       o = align256(o + (size_t)Bc * 4 * 8 * 2 * 4);
     }
   }
+  for (int m = 1; m <= L; ++m) {
+    SplitLaunch q;
+    if (split_back(net, m, split) && conv_split_desc(net->T[m - 1], m, 0, &q)) {
+      p.off_fb[m] = o;
+      o = align256(o + frag_bytes(net, m, 0));
+    }
+    if (mode == 1 && m < L && split_fwd(net, m, split)) {
+      p.off_ff[m] = o;
+      o = align256(o + frag_bytes(net, m, 1));
+    }
+  }
   long wblocks = 0, wpart = 0;
   for (int k = 2; k < L; ++k) {
     WinLaunch q;
-    const bool gw = mode == 1 && win_grad_pass(net, k);
-    if (!(gw || win_bound_pass(net, k)) || !win_desc(net, k, gw, &q)) continue;
+    const bool gw = mode == 1 && win_grad_pass(net, k, split);
+    if (!(gw || win_bound_pass(net, k, split)) || !win_desc(net, k, gw, &q)) continue;
     for (int m = 1; m < k; ++m) {
-      const WinLayer& l = q.d.L[m];
       if (!p.off_fb[m]) {
         p.off_fb[m] = o;
-        o = align256(o + (size_t)l.nmt * l.nks * 3072);
+        o = align256(o + frag_bytes(net, m, 0));
       }
       if (gw && !p.off_ff[m]) {
         p.off_ff[m] = o;
-        o = align256(o + (size_t)l.nmtf * l.nksf * 3072);
+        o = align256(o + frag_bytes(net, m, 1));
       }
     }
     if (gw) {
@@ -5799,7 +5843,7 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0) {
   // which of its passes run it.
   long big = std::max(slab, p.fwd_floats);
   for (int k = 2; k <= L; ++k) {
-    if (k < L && ((k == 2 && win2) || (mode == 0 && pass_on_chip(net, k, Bc, true)))) continue;
+    if (k < L && ((k == 2 && win2) || (mode == 0 && pass_on_chip(net, k, Bc, false)))) continue;
     const long qp = round_up(Bc * ((k < L) ? 2 * net->n[k] : S), 64);
     for (int m = mode == 1 ? 0 : 1; m <= (k < L ? k - 1 : L); ++m)
       big = std::max(big, net->n[m] * qp);
@@ -5903,9 +5947,63 @@ WsKernel convT_ws_for(const DLayer& t, bool tape, bool fc, int* nwaves, size_t* 
   return nullptr;
 }
 
+bool conv_split_desc(const lirpa_layer& t, int m, int dir, SplitLaunch* out) {
+  if (t.kind != LIRPA_CONV2D) return false;
+  SplitLaunch q{};
+  ConvSplit& c = q.c;
+  c.K = t.k;
+  c.s = t.stride;
+  c.t = (t.k + t.stride - 1) / t.stride;
+  c.pad = t.pad;
+  // channels come in eights, those of x in quads (as in frag_job)
+  const int q8i = 2 * ((t.in_c + 7) / 8), q8o = 2 * ((t.out_c + 7) / 8);
+  if (dir == 0) {
+    c.C = t.out_c;
+    c.Cq = q8o;
+    c.H = t.out_h;
+    c.W = t.out_w;
+    c.Cd = t.in_c;
+    c.Cqd = m > 1 ? q8i : (t.in_c + 3) / 4;
+    c.Hd = t.in_h;
+    c.Wd = t.in_w;
+    c.NS = c.t + 1;
+    c.nmt = (c.s * c.s * 4 * c.Cqd + 15) / 16;
+    c.nks = (c.t * c.t * 4 * c.Cq + 31) / 32;
+  } else {
+    c.C = t.in_c;
+    c.Cq = dir == 2 ? (t.in_c + 3) / 4 : q8i;
+    c.H = t.in_h;
+    c.W = t.in_w;
+    c.Cd = t.out_c;
+    c.Cqd = (t.out_c + 3) / 4;
+    c.Hd = t.out_h;
+    c.Wd = t.out_w;
+    c.NS = c.K + c.s;
+    c.nmt = (4 * c.Cqd + 15) / 16;
+    c.nks = (c.K * c.K * 4 * c.Cq + 31) / 32;
+  }
+  const double row = (double)c.W * 16 * c.Cq * (dir == 2 ? 4 : 8) + (dir == 2 ? 0 : 16);
+  const double lds = row * (dir == 2 ? 1 : 3) * c.NS;
+  if (lds + 4096 > kWinLds) return false;
+  c.rowb = (int)row;
+  // four waves a block where several blocks share a CU, else eight
+  q.threads = lds <= 53 * 1024 ? 256 : 512;
+  q.lds = (size_t)lds + (q.threads / 64) * 3 * 16 * 4;
+  *out = q;
+  return true;
+}
+
+int reserve_lds(const void* kern, size_t lds) {
+  if (lds > 65536 && hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)lds) != hipSuccess)
+    return fail(LIRPA_EDEVICE, "cannot reserve %zu bytes of LDS", lds);
+  return LIRPA_OK;
+}
+
+// (fb: the layer's T^T fragments where split_back holds)
 template <int MODE>
 int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ldq, long Q,
-                 const Sink& s, hipStream_t st) {
+                 const Sink& s, const uint4v* fb, hipStream_t st) {
   DLayer t = dlayer(net->T[m - 1]);
   const char* sfx = MODE == MODE_SLAB ? "_relax" : "_bound";
   const unsigned nblk32 = (unsigned)((Q + 31) / 32);
@@ -5953,6 +6051,24 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
                  sizeof(float);
     return launch_k(tag((std::string("convT") + sfx).c_str(), m, pass), st, [&] {
       hipLaunchKernelGGL(kern, dim3(nblk16), dim3(64 * nw), lds, st, t, in, (unsigned)ldq,
+                         (unsigned)Q, s);
+    });
+  }
+  SplitLaunch q;
+  if (fb && conv_split_desc(net->T[m - 1], m, 0, &q)) {
+    q.c.frag = fb;
+    auto kern = k_convT_split<MODE, 0>;
+    switch (q.c.nks) {
+      case 1: kern = k_convT_split<MODE, 1>; break;
+      case 2: kern = k_convT_split<MODE, 2>; break;
+      case 3: kern = k_convT_split<MODE, 3>; break;
+      case 4: kern = k_convT_split<MODE, 4>; break;
+      default: break;
+    }
+    if (int e = reserve_lds(reinterpret_cast<const void*>(kern), q.lds)) return e;
+    const unsigned nblk16 = (unsigned)round_up((Q + 15) / 16, 16);
+    return launch_k(tag((std::string("convT_split") + sfx).c_str(), m, pass), st, [&] {
+      hipLaunchKernelGGL(kern, dim3(nblk16), dim3(q.threads), q.lds, st, q.c, in, (unsigned)ldq,
                          (unsigned)Q, s);
     });
   }
@@ -6134,6 +6250,7 @@ int run_stages(const Chunk& c, int pass, int mtop, long R, long Q, long ldq, flo
   int cur = 0;
   for (int m = mtop; m >= 1; --m) {
     int e;
+    const uint4v* fb = split_back(c.net, m, c.p->split) ? at<uint4v>(c.ws, c.p->off_fb[m]) : nullptr;
     if (m == 2 && !c.tape && R >= 8) {
       // T_2^T, the layer-1 relaxation, T_1^T and the concretisation in one kernel
       int nw = 0;
@@ -6183,13 +6300,13 @@ int run_stages(const Chunk& c, int pass, int mtop, long R, long Q, long ldq, flo
     if (m > 1) {
       Sink s = slab_sink(c, m - 1, slab[1 - cur], ldq, R);
       s.tape = tape_of(c, pass, m - 1);
-      e = launch_stage<MODE_SLAB>(c.net, m, pass, slab[cur], ldq, Q, s, c.st);
+      e = launch_stage<MODE_SLAB>(c.net, m, pass, slab[cur], ldq, Q, s, fb, c.st);
       cur ^= 1;
     } else {
       Sink s = bound_sink(c, R, lo, hi, bstride, n_half);
       s.ldq = ldq;
       s.tsign = tsign_of(c, pass);
-      e = launch_stage<MODE_BOUND>(c.net, m, pass, slab[cur], ldq, Q, s, c.st);
+      e = launch_stage<MODE_BOUND>(c.net, m, pass, slab[cur], ldq, Q, s, fb, c.st);
     }
     if (e) return e;
   }
@@ -6405,13 +6522,31 @@ Pass4Kernel pass4_kernel_for(const lirpa_net* net) {
   return nullptr;
 }
 
-bool win_grad_pass(const lirpa_net* net, int k) {
-  WinLaunch q;
-  return !(k == 2 && pass2_grad_kernel_for(net)) && win_desc(net, k, true, &q);
+// Whether layer m's stages run the split kernels: convolutions without a kernel of their own
+// whose ring fits in LDS.
+bool split_back(const lirpa_net* net, int m, bool split) {
+  const lirpa_layer& t = net->T[m - 1];
+  int nw = 0;
+  SplitLaunch q;
+  return split && t.kind == LIRPA_CONV2D && !convT_mfma_for<MODE_SLAB>(dlayer(t), false, &nw) &&
+         conv_split_desc(t, m, 0, &q);
 }
 
-bool win_bound_pass(const lirpa_net* net, int k) {
+bool split_fwd(const lirpa_net* net, int m, bool split) {
+  const lirpa_layer& t = net->T[m - 1];
+  SplitLaunch q;
+  return split && t.kind == LIRPA_CONV2D && !fwd_conv_for(t, true, false) &&
+         conv_split_desc(t, m, m == 1 ? 2 : 1, &q);
+}
+
+bool win_grad_pass(const lirpa_net* net, int k, bool split) {
+  WinLaunch q;
+  return split && !(k == 2 && pass2_grad_kernel_for(net)) && win_desc(net, k, true, &q);
+}
+
+bool win_bound_pass(const lirpa_net* net, int k, bool split) {
   int nw = 0;
+  if (!split) return false;
   if (k == 2 && pass2_kernel_for(net, &nw)) return false;
   if (k == 3 && pass3_kernel_for(net)) return false;
   if (k == 4 && pass4_kernel_for(net)) return false;
@@ -6423,7 +6558,9 @@ bool win_bound_pass(const lirpa_net* net, int k) {
 int win_pass(const Chunk& c, int k, bool grad) {
   const lirpa_net* net = c.net;
   WinLaunch q;
-  if (!(grad ? win_grad_pass(net, k) : win_bound_pass(net, k)) || !win_desc(net, k, grad, &q))
+  const bool sp = c.p->split;
+  if (!(grad ? win_grad_pass(net, k, sp) : win_bound_pass(net, k, sp)) ||
+      !win_desc(net, k, grad, &q))
     return 1;
   for (int m = 1; m < k; ++m) {
     q.d.L[m].fb = at<uint4v>(c.ws, c.p->off_fb[m]);
@@ -6448,9 +6585,7 @@ int win_pass(const Chunk& c, int k, bool grad) {
   }
   const void* kern = grad ? reinterpret_cast<const void*>(k_win_pass<true>)
                           : reinterpret_cast<const void*>(k_win_pass<false>);
-  if (q.lds > 65536 && hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)q.lds) != hipSuccess)
-    return fail(LIRPA_EDEVICE, "cannot reserve %zu bytes of LDS", q.lds);
+  if (int e = reserve_lds(kern, q.lds)) return e;
   const unsigned blocks = (unsigned)(c.nb * q.d.G * q.d.H * q.d.W);
   if (int e = launch_k(tag(grad ? "win_grad" : "win_bound", 1, k), c.st, [&] {
         if (grad)
@@ -6476,7 +6611,7 @@ int win_pass(const Chunk& c, int k, bool grad) {
   return LIRPA_OK;
 }
 
-// The split weight fragments of every layer that k_win_pass reads in this call.
+// The split weight fragments that this call's kernels read.
 int win_frags(const lirpa_net* net, const Plan& p, void* ws, hipStream_t st) {
   FragJobs jobs{};
   int most = 0;
@@ -6491,18 +6626,12 @@ int win_frags(const lirpa_net* net, const Plan& p, void* ws, hipStream_t st) {
     most = 0;
     return e;
   };
-  for (int m = 1; m < net->L && m < kWinMax; ++m)
+  for (int m = 1; m <= net->L; ++m)
     for (int kind = 0; kind < 2; ++kind) {
       const size_t off = kind ? p.off_ff[m] : p.off_fb[m];
       if (!off) continue;
-      const lirpa_layer& t = net->T[m - 1];
-      const int tt = (t.k + t.stride - 1) / t.stride;
-      const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
-      const int cqo = 2 * ((t.out_c + 7) / 8);
-      FragJob f{t.W, t.in_c, t.out_c, t.k, t.stride, tt, cqi, cqo, kind, 0, 0,
-                at<uint4v>(ws, off)};
-      f.nmt = kind ? (4 * cqo + 15) / 16 : (t.stride * t.stride * 4 * cqi + 15) / 16;
-      f.nks = kind ? (t.k * t.k * 4 * cqi + 31) / 32 : (tt * tt * 4 * cqo + 31) / 32;
+      FragJob f = frag_job(net, m, kind);
+      f.dst = at<uint4v>(ws, off);
       most = std::max(most, f.nmt * f.nks);
       jobs.j[jobs.n++] = f;
       if (jobs.n == kFragJobs)
@@ -6511,13 +6640,13 @@ int win_frags(const lirpa_net* net, const Plan& p, void* ws, hipStream_t st) {
   return flush();
 }
 
-bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool dense) {
+bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool split) {
   // the same choices, in the same order, as bound_chunk makes for a chunk without a tape
   int nw = 0;
   if (k == 2) return pass2_kernel_for(net, &nw) != nullptr;
   if (k == 4 && pass4_kernel_for(net)) return true;
   if (k == 3 && pass3_kernel_for(net)) return true;
-  if (!dense && win_bound_pass(net, k)) return true;
+  if (win_bound_pass(net, k, split)) return true;
   if (!fc_bound_for(net, k, &nw)) return false;
   // fc_open_ok holds for every chunk of at most Bc sub-domains when it holds for Bc
   Chunk c{};
@@ -6561,7 +6690,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    if (k == 4 && (!c.tape || win_grad_pass(net, k))) {
+    if (k == 4 && (!c.tape || win_grad_pass(net, k, c.p->split))) {
       int e = pass4_window(c);
       if (e != 1) {
         if (e) return e;
@@ -6569,7 +6698,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    if (k == 3 && (!c.tape || win_grad_pass(net, k))) {
+    if (k == 3 && (!c.tape || win_grad_pass(net, k, c.p->split))) {
       int e = pass3_window(c);
       if (e != 1) {
         if (e) return e;
@@ -6577,7 +6706,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    if (!c.tape || win_grad_pass(net, k)) {
+    if (!c.tape || win_grad_pass(net, k, c.p->split)) {
       int e = win_pass(c, k, false);
       if (e != 1) {
         if (e) return e;
@@ -6921,7 +7050,11 @@ int grad_chunk(const Chunk& c, int full) {
       const unsigned nblk16 = (unsigned)round_up((Q + 15) / 16, 16);
       FwdKernel fk = fwd_conv_for(net->T[m - 1], m == 1, zout != nullptr);
       // fused adjoint sums (groups of 8 rows aligned to the sub-domains) where R allows it
-      const bool fused = fk && P < L && R % 8 == 0 && p.off_gpart != 0;
+      SplitLaunch sq;
+      const bool fsplit = !fk && split_fwd(net, m, p.split) &&
+                          conv_split_desc(net->T[m - 1], m, m == 1 ? 2 : 1, &sq);
+      const bool fused = (fk || (fsplit && t.out_c % 4 == 0)) && P < L && R % 8 == 0 &&
+                         p.off_gpart != 0;
       // an FC-opened pass recorded no tape over its first stage's input: rebuild it from W_P
       const bool wtape = m == P - 1 && fc_open_ok(c, P, R);
       const float* tapeW = wtape ? net->T[P - 1].W : nullptr;
@@ -6932,8 +7065,27 @@ int grad_chunk(const Chunk& c, int full) {
       const lirpa_layer& tl = net->T[m - 1];
       const bool fc_gemm = !fk && m > 1 && tl.kind == LIRPA_LINEAR && tl.in_c % 4 == 0 &&
                            tl.out_c <= 128;
+      decltype(&k_conv_split<true, 0>) ks = nullptr;
+      if (fsplit) {
+        sq.c.frag = at<uint4v>(c.ws, p.off_ff[m]);
+        switch (sq.c.nks) {
+          case 1: ks = m == 1 ? k_conv_split<true, 1> : k_conv_split<false, 1>; break;
+          case 2: ks = m == 1 ? k_conv_split<true, 2> : k_conv_split<false, 2>; break;
+          case 3: ks = m == 1 ? k_conv_split<true, 3> : k_conv_split<false, 3>; break;
+          case 4: ks = m == 1 ? k_conv_split<true, 4> : k_conv_split<false, 4>; break;
+          default: ks = m == 1 ? k_conv_split<true, 0> : k_conv_split<false, 0>; break;
+        }
+        if (int e = reserve_lds(reinterpret_cast<const void*>(ks), sq.lds)) return e;
+      }
       int e = launch_k(tag("fwd", m, P), c.st, [&] {
-        if (fc_gemm) {
+        if (fsplit) {
+          hipLaunchKernelGGL(ks, dim3(nblk16), dim3(sq.threads), sq.lds, c.st, sq.c, zin,
+                             (unsigned)ldq, (unsigned)Q, R, w, c.eps, tp,
+                             at<float>(c.ws, p.off_alo) + poff, at<float>(c.ws, p.off_aup) + poff,
+                             at<float>(c.ws, p.off_bup) + poff,
+                             at<float>(c.ws, p.off_bz) + poff, net->pstride, G, zout, gpart,
+                             gflag);
+        } else if (fc_gemm) {
           auto kf = k_fwd_fc<8>;
           switch ((tl.out_c + 15) / 16) {
             case 1: kf = k_fwd_fc<1>; break;
@@ -7026,9 +7178,9 @@ int check_common(const lirpa_net* net, const float* x0, float eps, const float* 
 // Workspace plan of a call kind: 0 lirpa_bound, 1 lirpa_bound_grad / lirpa_optimize,
 // 2 lirpa_bound_ul (the final pass bounds the 2S rows [C; -C]), 3 lirpa_optimize_ul (the
 // optimiser's plan and the rows -C).
-Plan plan_for(const lirpa_net* net, long S, long Bc, int mode) {
-  if (mode <= 1) return make_plan(net, S, Bc, mode);
-  Plan p = make_plan(net, mode == 2 ? 2 * S : S, Bc, mode == 2 ? 0 : 1);
+Plan plan_for(const lirpa_net* net, long S, long Bc, int mode, bool split = true) {
+  if (mode <= 1) return make_plan(net, S, Bc, mode, split);
+  Plan p = make_plan(net, mode == 2 ? 2 * S : S, Bc, mode == 2 ? 0 : 1, split);
   if (p.total == (size_t)-1) return p;
   const long nL = net->n[net->L];
   size_t o = p.total;
@@ -7042,15 +7194,21 @@ Plan plan_for(const lirpa_net* net, long S, long Bc, int mode) {
   return p;
 }
 
-// Largest chunk whose workspace fits.
+// Largest chunk whose workspace fits (without the split kernels where even one sub-domain does
+// not fit beside their weight fragments).
 long fit_chunk(const lirpa_net* net, long S, long B, size_t ws_bytes, Plan* out, int mode = 0) {
-  long lo = 0, hi = B;
-  while (lo < hi) {
-    long mid = (lo + hi + 1) / 2;
-    if (plan_for(net, S, mid, mode).total <= ws_bytes) lo = mid; else hi = mid - 1;
+  for (const bool split : {true, false}) {
+    long lo = 0, hi = B;
+    while (lo < hi) {
+      long mid = (lo + hi + 1) / 2;
+      if (plan_for(net, S, mid, mode, split).total <= ws_bytes) lo = mid; else hi = mid - 1;
+    }
+    if (lo > 0) {
+      *out = plan_for(net, S, lo, mode, split);
+      return lo;
+    }
   }
-  if (lo > 0) *out = plan_for(net, S, lo, mode);
-  return lo;
+  return 0;
 }
 
 Chunk make_chunk(lirpa_net* net, const Plan& p, void* ws, const float* x0, float eps, long S,
@@ -7270,7 +7428,8 @@ struct BabPlan {
   size_t inner_bytes = 0, total = 0;
 };
 
-BabPlan bab_plan(const lirpa_net* net, const lirpa_bab_params& bp) {
+// (split: room for the split kernels' weight fragments)
+BabPlan bab_plan(const lirpa_net* net, const lirpa_bab_params& bp, bool split = true) {
   BabPlan q;
   const long n = net->n_relu;
   q.cap = (long)bp.max_domains + bp.batch;
@@ -7305,8 +7464,8 @@ BabPlan bab_plan(const lirpa_net* net, const lirpa_bab_params& bp) {
   q.cbr = take((size_t)q.nc * 4);
   q.cdst = take((size_t)q.nc * 4);
   q.sum = take(sizeof(BabSummary));
-  const size_t ul = plan_for(net, 1, q.nc, 2).total;
-  const size_t op = q.alpha ? plan_for(net, 1, q.nc, 1).total : 0;
+  const size_t ul = plan_for(net, 1, q.nc, 2, split).total;
+  const size_t op = q.alpha ? plan_for(net, 1, q.nc, 1, split).total : 0;
   q.inner_bytes = std::max(ul, op);
   q.inner = o;
   q.total = (ul == (size_t)-1 || op == (size_t)-1) ? (size_t)-1 : o + q.inner_bytes;
@@ -7716,7 +7875,8 @@ int lirpa_bab(lirpa_net* net, const float* x0, float eps, const float* c,
   if (int e = check_common(net, x0, eps, c, 1, 1, ws)) return e;
   if (!params || !result) return fail(LIRPA_EINVAL, "params and result must be given");
   if (int e = check_bab_params(*params)) return e;
-  const BabPlan q = bab_plan(net, *params);
+  BabPlan q = bab_plan(net, *params);
+  if (q.total > ws_bytes) q = bab_plan(net, *params, false);
   if (q.total > ws_bytes)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes, branch and bound needs %zu", ws_bytes,
                 q.total);

@@ -70,3 +70,33 @@ def test_windows(name, B):
     close(f"{name} grad lb", lb.cpu().double().numpy(), lr)
     check_grad(f"{name} grad", g.cpu().double().numpy(), gr, split,
                lambda b, j: one_sided(rnet, x0, eps, C, split, alpha, b, j))
+
+
+@pytest.mark.parametrize("mode", ["bound", "grad"])
+def test_workspace_without_room_for_fragments(mode):
+    # a workspace that holds one sub-domain but not the split weight fragments beside it: the
+    # dense stages run, with the same results
+    layers = wl.random_net(NETS["off-chip"], 3)
+    rng = np.random.default_rng(3)
+    x0 = rng.uniform(0, 1, wl.n_in(layers[0])).astype(np.float32)
+    C = wl.margin_spec(3, 0)
+    rnet = ref.RefNet(layers)
+    alpha = rng.uniform(0.05, 0.95, (2, rnet.n_relu)).astype(np.float32)
+    net = lirpa.Network(layers)
+    S = C.shape[0]
+    full = lirpa.lirpa_workspace_bytes(net.handle, S, 1, 1 if mode == "grad" else 0)
+    for room in (full, full - 256):  # the fragments, 147 KB of it at least, are the last to fit
+        ws = torch.empty(room, dtype=torch.uint8, device="cuda")
+        lb = torch.empty((2, S), device="cuda")
+        if mode == "grad":
+            g = torch.empty((2, rnet.n_relu), device="cuda")
+            lirpa.lirpa_bound_grad(net.handle, dev(x0), 0.1, dev(C), S, 2, None, dev(alpha), 1, lb,
+                                   g, ws, room)
+            lr, gr = ref.bound_grad(rnet, x0, 0.1, C, None, alpha)
+            check_grad("grad", g.cpu().double().numpy(), gr, None,
+                       lambda b, j: one_sided(rnet, x0, 0.1, C, None, alpha, b, j))
+        else:
+            lirpa.lirpa_bound(net.handle, dev(x0), 0.1, dev(C), S, 2, None, dev(alpha), lb, None,
+                              None, None, ws, room)
+            lr = ref.bound(rnet, x0, 0.1, C, None, alpha)[0]
+        close(f"{mode} lb", lb.cpu().double().numpy(), lr)
