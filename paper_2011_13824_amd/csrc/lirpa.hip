@@ -5088,6 +5088,7 @@ __global__ void __launch_bounds__(256)
 
 #include "win_pass.hpp"
 #include "conv_split.hpp"
+#include "fc_split.hpp"
 
 // Projected Adam ascent step (bias-corrected), alpha clipped to [0, 1].
 __global__ void __launch_bounds__(kBlock) k_adam(long n, float* __restrict__ alpha,
@@ -5629,17 +5630,27 @@ bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out) {
 bool win_grad_pass(const lirpa_net* net, int k, bool split);
 bool win_bound_pass(const lirpa_net* net, int k, bool split);
 
+// Whether the final pass of a plain bound takes its last two layers in k_final_fc.
+bool final_fc_covers(const lirpa_net* net) {
+  if (net->L < 3 || net->T[net->L - 1].kind != LIRPA_LINEAR ||
+      net->T[net->L - 2].kind != LIRPA_LINEAR)
+    return false;
+  const long ks = (net->n[net->L - 1] + 3) / 4;
+  return ks == 8 || ks == 16 || ks == 25 || ks == 32;
+}
+
 // Split fragments of layer m (kind 0: T^T, 1: T), shared by k_win_pass and the split stages.
 // The channels below T_m come in eights, those of x and the rows that only feed an epilogue in
 // quads.
 FragJob frag_job(const lirpa_net* net, int m, int kind) {
   const lirpa_layer& t = net->T[m - 1];
-  const int tt = (t.k + t.stride - 1) / t.stride;
+  const bool fc = t.kind == LIRPA_LINEAR;  // (a 1x1 convolution of a 1x1 map)
+  const int k = fc ? 1 : t.k, st = fc ? 1 : t.stride, tt = (k + st - 1) / st;
   const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
   const int cqo = 2 * ((t.out_c + 7) / 8);
-  FragJob f{t.W, t.in_c, t.out_c, t.k, t.stride, tt, cqi, cqo, kind, 0, 0, nullptr};
-  f.nmt = kind ? (4 * cqo + 15) / 16 : (t.stride * t.stride * 4 * cqi + 15) / 16;
-  f.nks = kind ? (t.k * t.k * 4 * cqi + 31) / 32 : (tt * tt * 4 * cqo + 31) / 32;
+  FragJob f{t.W, t.in_c, t.out_c, k, st, tt, cqi, cqo, kind, 0, 0, nullptr};
+  f.nmt = kind ? (4 * cqo + 15) / 16 : (st * st * 4 * cqi + 15) / 16;
+  f.nks = kind ? (k * k * 4 * cqi + 31) / 32 : (tt * tt * 4 * cqo + 31) / 32;
   return f;
 }
 size_t frag_bytes(const lirpa_net* net, int m, int kind) {
@@ -5648,6 +5659,44 @@ size_t frag_bytes(const lirpa_net* net, int m, int kind) {
 }
 bool split_back(const lirpa_net* net, int m, bool split);
 bool split_fwd(const lirpa_net* net, int m, bool split);
+
+// Whether the fully connected layer m runs k_fcT_split, or (m = 1) its witness forward
+// k_fc_sign: from 16,384 weights on (measured below that, a 32 x 32 layer's stages are launch
+// latency either way and the fragments are one launch more), where 16 rows' panel fits in LDS.
+// FcSplit and the row tiles: the most of 4, 2, 1 that fit and leave two blocks a CU (Q rows).
+struct FcLaunch {
+  FcSplit c;
+  int nt = 0;
+  size_t lds = 0;
+};
+bool fc_split_desc(const lirpa_net* net, int m, int kind, bool split, FcLaunch* out,
+                   long Q = 1L << 40) {
+  const lirpa_layer& t = net->T[m - 1];
+  if (!split || t.kind != LIRPA_LINEAR || (long)t.in_c * t.out_c < 16384 || (kind && m > 1))
+    return false;
+  const FragJob f = frag_job(net, m, kind);
+  for (int nt = 4; nt >= 1; nt /= 2) {
+    const double plane = (double)f.nks * 4 * nt * 256;
+    const double lds = kind ? plane / 2 : 3 * plane + (kFcThreads / 64) * 3 * 16 * nt * 4;
+    if (lds > kWinLds || (nt > 1 && Q < 16L * nt * 512)) continue;
+    *out = FcLaunch{{kind ? t.in_c : t.out_c, kind ? t.out_c : t.in_c, f.nks, f.nmt, (int)plane,
+                     nullptr},
+                    nt, (size_t)lds};
+    return true;
+  }
+  return false;
+}
+// ... and whether a plan's calls run that stage at all (the final pass of a plain bound takes
+// its last two layers in k_final_fc or k_convT_fc_bound where they are covered).
+bool fc_split_used(const lirpa_net* net, int m, int kind, int mode, bool split) {
+  FcLaunch q;
+  if (!fc_split_desc(net, m, kind, split, &q)) return false;
+  if (mode == 1) return kind == 0 || m < net->L;
+  if (kind) return false;
+  for (int k = m + 1; k < net->L; ++k)
+    if (net->T[k - 1].kind == LIRPA_LINEAR) return true;
+  return m != net->L - 1 || !final_fc_covers(net);
+}
 // Geometry and LDS of k_convT_split (dir 0) or k_conv_split (dir 1: over a z slab, 2: over the
 // sign tape) for layer t, the net's m-th; false for other layers, and when the ring does not fit.
 struct SplitLaunch {
@@ -5805,7 +5854,12 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0, bool split =
       p.off_fb[m] = o;
       o = align256(o + frag_bytes(net, m, 0));
     }
-    if (mode == 1 && m < L && split_fwd(net, m, split)) {
+    if (fc_split_used(net, m, 0, mode, split)) {
+      p.off_fb[m] = o;
+      o = align256(o + frag_bytes(net, m, 0));
+    }
+    if (mode == 1 && m < L &&
+        (split_fwd(net, m, split) || fc_split_used(net, m, 1, mode, split))) {
       p.off_ff[m] = o;
       o = align256(o + frag_bytes(net, m, 1));
     }
@@ -6008,6 +6062,18 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
   const char* sfx = MODE == MODE_SLAB ? "_relax" : "_bound";
   const unsigned nblk32 = (unsigned)((Q + 31) / 32);
   if (t.kind == LIRPA_LINEAR) {
+    FcLaunch f;
+    if (fb && fc_split_desc(net, m, 0, true, &f, Q)) {
+      f.c.frag = fb;
+      auto kern = f.nt == 4 ? k_fcT_split<MODE, 4>
+                            : (f.nt == 2 ? k_fcT_split<MODE, 2> : k_fcT_split<MODE, 1>);
+      if (int e = reserve_lds(reinterpret_cast<const void*>(kern), f.lds)) return e;
+      const unsigned nb = (unsigned)round_up((Q + 16 * f.nt - 1) / (16 * f.nt), 8);
+      return launch_k(tag((std::string("fcT_split") + sfx).c_str(), m, pass), st, [&] {
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(kFcThreads), f.lds, st, f.c, in, (unsigned)ldq,
+                           (unsigned)Q, s);
+      });
+    }
     if (t.out_c <= 448) {
       // few row tiles (a final pass): 16 waves per block, so that each wave carries fewer
       // output tiles in sequence
@@ -6250,7 +6316,11 @@ int run_stages(const Chunk& c, int pass, int mtop, long R, long Q, long ldq, flo
   int cur = 0;
   for (int m = mtop; m >= 1; --m) {
     int e;
-    const uint4v* fb = split_back(c.net, m, c.p->split) ? at<uint4v>(c.ws, c.p->off_fb[m]) : nullptr;
+    // (split fragments: of the layers whose stages read them)
+    const uint4v* fb = c.p->off_fb[m] && (split_back(c.net, m, c.p->split) ||
+                                          c.net->T[m - 1].kind == LIRPA_LINEAR)
+                           ? at<uint4v>(c.ws, c.p->off_fb[m])
+                           : nullptr;
     if (m == 2 && !c.tape && R >= 8) {
       // T_2^T, the layer-1 relaxation, T_1^T and the concretisation in one kernel
       int nw = 0;
@@ -6793,7 +6863,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
     Sink s = slab_sink(c, L - 2, at<float>(c.ws, c.p->off_slab0), ldq, R);
     const long nj = net->n[L - 1];
     const size_t lds = (size_t)(((nj + 3) & ~3L) * 16 + NW * 64 + NW * 16) * sizeof(float);
-    // k-steps of the kernel: ceil(n_{L-1} / 4) for the instantiated sizes
+    // k-steps of the kernel: ceil(n_{L-1} / 4) for the instantiated sizes (final_fc_covers)
     auto fkern = [&]() -> void (*)(DLayer, const float*, int, long, long, const float*,
                                    const float*, const float*, const float*, Sink) {
       switch ((nj + 3) / 4) {
@@ -7053,7 +7123,9 @@ int grad_chunk(const Chunk& c, int full) {
       SplitLaunch sq;
       const bool fsplit = !fk && split_fwd(net, m, p.split) &&
                           conv_split_desc(net->T[m - 1], m, m == 1 ? 2 : 1, &sq);
-      const bool fused = (fk || (fsplit && t.out_c % 4 == 0)) && P < L && R % 8 == 0 &&
+      FcLaunch fs;
+      const bool fsign = m == 1 && fc_split_desc(net, 1, 1, p.split, &fs, Q);
+      const bool fused = (fk || ((fsplit || fsign) && t.out_c % 4 == 0)) && P < L && R % 8 == 0 &&
                          p.off_gpart != 0;
       // an FC-opened pass recorded no tape over its first stage's input: rebuild it from W_P
       const bool wtape = m == P - 1 && fc_open_ok(c, P, R);
@@ -7077,8 +7149,21 @@ int grad_chunk(const Chunk& c, int full) {
         }
         if (int e = reserve_lds(reinterpret_cast<const void*>(ks), sq.lds)) return e;
       }
+      auto kfs = fs.nt == 4 ? k_fc_sign<4> : (fs.nt == 2 ? k_fc_sign<2> : k_fc_sign<1>);
+      if (fsign) {
+        fs.c.frag = at<uint4v>(c.ws, p.off_ff[1]);
+        if (int e = reserve_lds(reinterpret_cast<const void*>(kfs), fs.lds)) return e;
+      }
       int e = launch_k(tag("fwd", m, P), c.st, [&] {
-        if (fsplit) {
+        if (fsign) {
+          const unsigned nb = (unsigned)round_up((Q + 16 * fs.nt - 1) / (16 * fs.nt), 8);
+          hipLaunchKernelGGL(kfs, dim3(nb), dim3(kFcThreads), fs.lds, c.st, fs.c,
+                             reinterpret_cast<const int8_t*>(zin), (unsigned)ldq, (unsigned)Q, R,
+                             w, c.eps, tp, at<float>(c.ws, p.off_alo) + poff,
+                             at<float>(c.ws, p.off_aup) + poff, at<float>(c.ws, p.off_bup) + poff,
+                             at<float>(c.ws, p.off_bz) + poff, net->pstride, G, zout, gpart,
+                             gflag);
+        } else if (fsplit) {
           hipLaunchKernelGGL(ks, dim3(nblk16), dim3(sq.threads), sq.lds, c.st, sq.c, zin,
                              (unsigned)ldq, (unsigned)Q, R, w, c.eps, tp,
                              at<float>(c.ws, p.off_alo) + poff, at<float>(c.ws, p.off_aup) + poff,

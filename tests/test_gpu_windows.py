@@ -2,7 +2,9 @@
 intermediate bounds and gradients of nets whose windows have every edge the kernel handles
 (strides 1 to 4, kernels 1 to 7 larger than the map, taps that do not divide by the stride,
 channel counts off the 4, 8 and 16 of its tiles, up to four convolutions), and of one whose
-windows do not fit on chip (the dense stages).
+windows do not fit on chip (the dense stages).  The fc nets do the same for the fully connected
+stages: four, two and one tiles of rows a block, widths off every tile, and a layer too narrow
+for the split kernels.
 
 Tolerance: a bound is at most four chained fp32 sums of up to 2,000 terms, each within 8e-7 of its
 2-norm (the fp32 matrix instruction's measured error at that length); with a factor 3 for
@@ -29,6 +31,9 @@ NETS = {
     "k-over-map": [wl.conv(3, 6, 8, 5, 3, 2), wl.conv(8, 2, 33, 1, 1, 0), wl.fc(132, 3)],
     "wide-channels": [wl.conv(3, 6, 40, 3, 1, 1), wl.conv(40, 6, 12, 3, 2, 1), wl.fc(108, 3)],
     "conv-last": [wl.conv(1, 6, 4, 4, 2, 1), wl.conv(4, 3, 16, 3, 1, 1), wl.conv(16, 3, 1, 3, 1, 0)],
+    "fc-four-tiles": [wl.fc(70, 250), wl.fc(250, 67), wl.fc(67, 3)],
+    "fc-two-tiles": [wl.fc(50, 330), wl.fc(330, 54), wl.fc(54, 3)],
+    "fc-one-tile": [wl.fc(20, 850), wl.fc(850, 20), wl.fc(20, 31), wl.fc(31, 3)],
     "off-chip": [wl.conv(1, 4, 64, 7, 1, 3), wl.conv(64, 4, 2, 7, 1, 3), wl.fc(32, 3)],
 }
 
