@@ -5089,6 +5089,7 @@ __global__ void __launch_bounds__(256)
 #include "win_pass.hpp"
 #include "conv_split.hpp"
 #include "fc_split.hpp"
+#include "fc_net.hpp"
 
 // Projected Adam ascent step (bias-corrected), alpha clipped to [0, 1].
 __global__ void __launch_bounds__(kBlock) k_adam(long n, float* __restrict__ alpha,
@@ -7361,6 +7362,53 @@ int validate_enqueue(const lirpa_net* net, const float* x0, const float* C, int 
 }
 
 
+// The whole bound of a small fully connected net in one launch (k_fc_net): every width up to 64
+// and the weights within 32 KB, where the stages' launches cost more than their work.  Measured
+// against the stages, one spec row: 4-32-32-2 33.1 -> 12.5 us at 64 sub-domains, 152 -> 80 at
+// 4,096; eight layers of 30 261 -> 94 and 3,559 -> 938; 60-60-60-10 52.7 -> 41.3 at 64, 139 -> 116
+// at 1,024 but 396 -> 422 at 4,096, so widths over 48 stop at 1,024; two layers, where no pass
+// needs the weights more than once, 22.7 -> 14.6 at 256 but 23.3 -> 32.2 at 1,024, so they stop
+// at 256.  Returns 1 for other calls.
+int fc_net_run(const lirpa_net* net, const float* x0, float eps, const float* C, int S, int B,
+               const int8_t* split, const float* alpha, float* lb, float* l_out, float* u_out,
+               int8_t* code_out, const float* l_par, const float* u_par, hipStream_t stream) {
+  if (net->L < 2 || net->L > kNetLayers || (net->L == 2 && B > 256)) return 1;
+  FcNet d{};
+  int o = 0;
+  for (int m = 0; m <= net->L; ++m) {
+    if (net->n[m] > kNetWidth || (net->n[m] > 48 && B > 1024)) return 1;
+    d.n[m] = (int)net->n[m];
+    if (m == 0) continue;
+    const lirpa_layer& t = net->T[m - 1];
+    if (t.kind != LIRPA_LINEAR) return 1;
+    d.w[m] = o;
+    o += t.in_c * t.out_c;
+    d.bo[m] = o;
+    o += t.out_c;
+    if (o > kNetWeights) return 1;
+    d.W[m] = t.W;
+    d.b[m] = t.b;
+    if (m < net->L) d.off[m] = (int)net->off[m];
+  }
+  d.L = net->L;
+  d.S = S;
+  d.x0 = x0;
+  d.C = C;
+  d.eps = eps;
+  d.n_relu = net->n_relu;
+  d.split = split;
+  d.alpha = alpha;
+  d.lpar = l_par;
+  d.upar = u_par;
+  d.lb = lb;
+  d.l = l_out;
+  d.u = u_out;
+  d.code = code_out;
+  return launch_k("fc_net", stream, [&] {
+    hipLaunchKernelGGL(k_fc_net, dim3((unsigned)B), dim3(kNetThreads), 0, stream, d);
+  });
+}
+
 // lirpa_bound on a workspace that holds chunks of Bc sub-domains (plan p).
 int bound_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float eps, const float* C,
               int S, int B, const int8_t* split, const float* alpha, float* lb, float* l_out,
@@ -7368,6 +7416,10 @@ int bound_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float eps
               const float* l_par = nullptr, const float* u_par = nullptr) {
   if (int e = validate_report(stream)) return e;
   if (int e = validate_enqueue(net, x0, C, S, B, split, alpha, stream)) return e;
+  if (const int e = fc_net_run(net, x0, eps, C, S, B, split, alpha, lb, l_out, u_out, code_out,
+                               l_par, u_par, stream);
+      e != 1)
+    return e;
   if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, stream)) return e;
   for (long b0 = 0; b0 < B; b0 += Bc) {
     Chunk c = make_chunk(net, p, ws, x0, eps, S, B, b0, split, alpha, l_out, u_out, stream);

@@ -4,7 +4,7 @@ intermediate bounds and gradients of nets whose windows have every edge the kern
 channel counts off the 4, 8 and 16 of its tiles, up to four convolutions), and of one whose
 windows do not fit on chip (the dense stages).  The fc nets do the same for the fully connected
 stages: four, two and one tiles of rows a block, widths off every tile, and a layer too narrow
-for the split kernels.
+for the split kernels.  The net nets run the one-launch bound of small fully connected nets.
 
 Tolerance: a bound is at most four chained fp32 sums of up to 2,000 terms, each within 8e-7 of its
 2-norm (the fp32 matrix instruction's measured error at that length); with a factor 3 for
@@ -34,6 +34,10 @@ NETS = {
     "fc-four-tiles": [wl.fc(70, 250), wl.fc(250, 67), wl.fc(67, 3)],
     "fc-two-tiles": [wl.fc(50, 330), wl.fc(330, 54), wl.fc(54, 3)],
     "fc-one-tile": [wl.fc(20, 850), wl.fc(850, 20), wl.fc(20, 31), wl.fc(31, 3)],
+    "net-edges": [wl.fc(1, 64), wl.fc(64, 1), wl.fc(1, 33), wl.fc(33, 3)],
+    "net-eight-layers": [wl.fc(7, 5), wl.fc(5, 6), wl.fc(6, 7), wl.fc(7, 8), wl.fc(8, 9),
+                         wl.fc(9, 10), wl.fc(10, 11), wl.fc(11, 3)],
+    "net-two-layers": [wl.fc(20, 16), wl.fc(16, 3)],
     "off-chip": [wl.conv(1, 4, 64, 7, 1, 3), wl.conv(64, 4, 2, 7, 1, 3), wl.fc(32, 3)],
 }
 
