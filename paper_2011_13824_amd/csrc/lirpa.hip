@@ -1740,9 +1740,16 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
 // both blocked by groups of 8 rows, [q / 8][entry][q % 8], so that the reverse sweep, which
 // takes 8 rows at a time, reads contiguous memory (rows past Q included: they lie inside the
 // padded width ldq, and hold zeros).
+// SYM (FC source, bounds without given slopes): every neuron's lower slope is its upper slope, so
+// the row -e_j is the negative of the row +e_j all the way down.  A row q is then +e_j alone
+// (R = n_k rows per sub-domain, even) and gives both bounds: with gap = sum |a| b_up over the
+// entries it relaxes, l = beta - eps ||A_x||_1 and u = beta + gap + eps ||A_x||_1 (the negated
+// row's intercepts are those of the positive entries).  Half the rows of a bound: the
+// pass of 400 sub-domains of the 8-16-channel net 0.440 -> 0.231 ms, of 1,024 of the
+// 16-32-channel net 2.84 -> 1.53.
 template <int K, int S, int P, int H1, int W1, int H0, int W0, int CO, int CI, int CPW, int K1,
           int S1, int P1, int HX, int WX, int C0, int NXW, bool FC, int NBS, int SPEC = 0,
-          bool TAPE = false>
+          bool TAPE = false, bool SYM = false>
 __global__ void __launch_bounds__(64 * (CI / CPW + NXW))
 __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3), 8)))
     k_convT_fc_bound(DLayer t, DLayer t1, const float* __restrict__ in, unsigned ldq, unsigned Q,
@@ -1770,6 +1777,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   static_assert(NBS == 2 || NBS == 3, "sub-domains per block");
   static_assert(SPEC == 0 || !FC, "the spec source replaces the slab source");
   static_assert(!TAPE || FC, "tapes are written for the FC source only");
+  static_assert(!SYM || (FC && !TAPE), "one row per neuron: plain bounds of the FC source");
   constexpr int NMT_S = CO * W1 / 16;  // spec source: 16-entry tiles of an input row
   static_assert(SPEC == 0 || (NMT_S % (CI / CPW) == 0 && W1 % 4 == 0), "spec tiles per wave");
   static_assert(SPEC == 0 || NMT_S / (CI / CPW) <= 2, "spec operands: two tiles per wave");
@@ -1787,7 +1795,8 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   __shared__ float tiles[2][TILE];
   __shared__ float ring[2][SLOT];
   __shared__ float4v pars[2][PSLOT4];
-  __shared__ float red[NM * 16 + 2 * NXW * 16];
+  __shared__ float red[NM * 16 + 2 * NXW * 16 + (SYM ? (NM + NXW) * 16 : 0)];
+  float* gred = red + NM * 16 + 2 * NXW * 16;  // SYM: the gaps, matrix waves then x waves
   // spec source: the block's rows relaxed onto layer L-1, the MFMA B operand [4 SPEC][16 rows]
   __shared__ float vts[SPEC > 0 ? SPEC * 64 : 1];
   // border exchange of the x waves (see there): [step parity][wave - 1][channel, column][lane]
@@ -1882,7 +1891,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     int g_lds[TPL];
     bool g_on[TPL];
     float4v g_xa[TPL], g_xb[TPL], g_lo[TPL], g_up[TPL], g_bu[TPL];
-    float fbeta_a = 0.f, fbeta_b = 0.f;
+    float fbeta_a = 0.f, fbeta_b = 0.f, fgap_a = 0.f, fgap_b = 0.f;
     if constexpr (FC) {
       const unsigned nin = CO * H1 * W1, nk = (unsigned)fc.nk;
 #pragma unroll
@@ -1896,10 +1905,10 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
         // rows 2 qp, 2 qp + 1 are +e_j, -e_j of one neuron j (R is even): one row of W_k
         (void)nk;
         g_sa[k] = qa < Q ? 1.f : 0.f;
-        g_sb[k] = qb < Q ? -1.f : 0.f;
+        g_sb[k] = qb < Q ? (SYM ? 1.f : -1.f) : 0.f;
         const unsigned i0 = (unsigned)co * H1 * W1 + 4u * t4;
-        g_wa[k] = (ra >> 1) * nin + i0;
-        g_wb[k] = g_wa[k];
+        g_wa[k] = (SYM ? ra : ra >> 1) * nin + i0;
+        g_wb[k] = SYM ? g_wa[k] + nin : g_wa[k];  // (R is even: row ra + 1 is there too)
         // R is even, so rows 2 qp and 2 qp + 1 share their sub-domain
         g_pb[k] = (qa < Q ? qa / R : b0) * (unsigned)s.pstride + i0;
         g_bz[k] = t.b[co];
@@ -1912,7 +1921,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
         if (g_on[k]) {
           const unsigned o = (unsigned)yg * W1;
           g_xa[k] = *reinterpret_cast<const float4v*>(fc.W + (g_wa[k] + o));
-          g_xb[k] = g_xa[k];
+          g_xb[k] = SYM ? *reinterpret_cast<const float4v*>(fc.W + (g_wb[k] + o)) : g_xa[k];
           g_lo[k] = *reinterpret_cast<const float4v*>(fc.a_lo + (g_pb[k] + o));
           g_up[k] = *reinterpret_cast<const float4v*>(fc.a_up + (g_pb[k] + o));
           g_bu[k] = *reinterpret_cast<const float4v*>(fc.b_up + (g_pb[k] + o));
@@ -1931,6 +1940,10 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
             fbeta_a = fmaf(ha, g_bz[k], fbeta_a);
             fbeta_b = fmaf(fminf(b, 0.f), g_bu[k][e], fbeta_b);
             fbeta_b = fmaf(hb, g_bz[k], fbeta_b);
+            if constexpr (SYM) {
+              fgap_a = fmaf(fabsf(a), g_bu[k][e], fgap_a);
+              fgap_b = fmaf(fabsf(b), g_bu[k][e], fgap_b);
+            }
             *reinterpret_cast<float2v*>(buf + g_lds[k] + e * CO * 16) = float2v{ha, hb};
           }
         }
@@ -2118,10 +2131,18 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
       for (int o = 8; o < 64; o <<= 1) {
         fbeta_a += __shfl_xor(fbeta_a, o, 64);
         fbeta_b += __shfl_xor(fbeta_b, o, 64);
+        if constexpr (SYM) {
+          fgap_a += __shfl_xor(fgap_a, o, 64);
+          fgap_b += __shfl_xor(fgap_b, o, 64);
+        }
       }
       if (lane < 8) {
         red[wave * 16 + 2 * lane] = fbeta_a;
         red[wave * 16 + 2 * lane + 1] = fbeta_b;
+        if constexpr (SYM) {
+          gred[wave * 16 + 2 * lane] = fgap_a;
+          gred[wave * 16 + 2 * lane + 1] = fgap_b;
+        }
       }
     }
     if constexpr (SPEC > 0) {
@@ -2193,7 +2214,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     if (x >= S1 && (x - S1) / K1 < NF) v += od[c0][(x - S1) / K1][(x - S1) % K1];
     return v;
   };
-  float l1 = 0.f, beta = 0.f;
+  float l1 = 0.f, beta = 0.f, gap = 0.f;
   float pend[C0 * NSH];  // right shared columns of the pending row
   bool pend_ok = false;
   int pend_y = 0;
@@ -2293,6 +2314,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
         const float ah = a * (a >= 0.f ? p[0] : p[1]);
         beta = fmaf(fminf(a, 0.f), p[2], beta);
         beta = fmaf(ah, p[3], beta);
+        if constexpr (SYM) gap = fmaf(fabsf(a), p[2], gap);
         hn[ks] = ah;
       }
     };
@@ -2358,6 +2380,11 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     red[NM * 16 + XB * 16 + lane] = beta;
     red[NM * 16 + (NXW + XB) * 16 + lane] = l1;
   }
+  if constexpr (SYM) {
+    gap += __shfl_xor(gap, 16, 64);
+    gap += __shfl_xor(gap, 32, 64);
+    if (lane < 16) gred[(NM + XB) * 16 + lane] = gap;
+  }
   };
   if (xw == 0) xrun(std::integral_constant<int, 0>());
   if (NXW > 1 && xw == 1) xrun(std::integral_constant<int, (NXW > 1 ? 1 : 0)>());
@@ -2370,8 +2397,8 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   const unsigned r = q % R;
   float tb = 0.f;
   if constexpr (FC) {
-    const float bj = fc.b[(r >> 1) % (unsigned)fc.nk];
-    tb = (r & 1) ? -bj : bj;
+    const float bj = fc.b[SYM ? r : (r >> 1) % (unsigned)fc.nk];
+    tb = !SYM && (r & 1) ? -bj : bj;
     for (int w = 0; w < NM; ++w) tb += red[w * 16 + lane];
   }
   if constexpr (SPEC > 0) {
@@ -2383,11 +2410,19 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   if constexpr (FC) {
     // rows 2j, 2j + 1 (lanes 2i, 2i + 1) give l_j and -u_j; then the relaxation of layer k
     const float v = tb - s.eps * ta;
-    const float vn = __shfl_xor(v, 1, 64);
-    if (q >= Q || (r & 1)) return;  // (Q is even: row q + 1 exists)
-    const unsigned b = q / R, jj = r >> 1;
+    float uv;
+    if constexpr (SYM) {
+      float gs = 0.f;
+      for (int w = 0; w < NM + NXW; ++w) gs += gred[w * 16 + lane];
+      uv = (tb + gs) + s.eps * ta;
+      if (q >= Q) return;
+    } else {
+      uv = -__shfl_xor(v, 1, 64);
+      if (q >= Q || (r & 1)) return;  // (Q is even: row q + 1 exists)
+    }
+    const unsigned b = q / R, jj = SYM ? r : r >> 1;
     const long pi = (long)b * fc.n_relu + fc.off + jj;
-    float lv = v, uv = -vn;
+    float lv = v;
     parent_clip(lv, uv, fc.lpar, fc.upar, pi);
     s.lo[b * s.bstride + jj] = lv;
     s.hi[b * s.bstride + jj] = uv;
@@ -2435,11 +2470,14 @@ __host__ __device__ inline int p2_groups(int C2) { return C2 / 8; }
 //  (3) concretises the footprint (Eq. 8; positions outside the image are zero padding) and
 //      writes l_j (sign +) or u_j (sign -) of the sub-domain.
 // The result equals the dense pass exactly in arithmetic terms: the skipped products are zeros.
-template <int K1, int S1, int P1, int K2, int C1, int NW, int XW>
+// SYM (no given slopes, C2 a multiple of 16): the row -e_j is the negative of +e_j, so the 16
+// rows are 16 channels and each gives both bounds (see k_convT_fc_bound): 0.151 -> 0.095 ms for
+// 400 sub-domains of the 8-16-channel net, 1.24 -> 0.71 for 1,024 of the 16-32-channel net.
+template <int K1, int S1, int P1, int K2, int C1, int NW, int XW, bool SYM>
 // (with 8 windows per block the kernel fits 80 VGPRs with 8 channels on T_1, 128 with 16, one
 // more wave per SIMD than it would take unhinted; with 4 it would spill, so it is left alone)
 __global__ void __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) : 1, 8)))
+__attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) - (SYM ? 1 : 0) : 1, 8)))
     k_pass2_window(DLayer t1, DLayer t2, long nb, const float* __restrict__ a_lo,
                const float* __restrict__ a_up, const float* __restrict__ b_up, long pstride,
                const float* __restrict__ z1, float eps, float* __restrict__ L,
@@ -2460,16 +2498,17 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) : 1, 8)))
   constexpr int NEP = (NE + RPT - 1) / RPT;         // window entries per thread (phase 1)
   constexpr int NPP = (NE + NT - 1) / NT;           // staged parameters per thread
   __shared__ float tile[NEL];
-  __shared__ float red[NW * 16 + RPT * 16];
+  __shared__ float red[NW * 16 + (SYM ? 2 : 1) * RPT * 16];
   __shared__ float4v prm[NE];  // (a_lo, a_up, b_up, W1 x0 + b1) of the window (0 outside)
-  __shared__ float vb[XW][16];  // the rows' bounds, written out once per block
+  __shared__ float vb[XW][SYM ? 32 : 16];  // the rows' bounds, written out once per block
+  static_assert(16 * XW <= NT, "a thread per neuron writes the bounds");
   float* bred = red + NW * 16;
 
   const int lane = threadIdx.x & 63, wave = wave_id();
   const int n = lane & 15, G = lane >> 4;
   // block -> (sub-domain, row group, y2, XW consecutive windows along x2)
   const int H2 = t2.out_h, W2 = t2.out_w, C2 = t2.out_c;
-  const int NG = p2_groups(C2);
+  const int NG = SYM ? C2 / 16 : p2_groups(C2);
   const int nxc = W2 / XW;
   unsigned blk = xcd_range(blockIdx.x);  // 32-bit: the scalar divisions stay short
   const int x2c = (int)(blk % (unsigned)nxc); blk /= (unsigned)nxc;
@@ -2483,7 +2522,7 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) : 1, 8)))
   // this thread's entries of W_2 (phase 1: row = tid mod 16, entries part, part + RPT, ...),
   // the same for every window of the block
   const int row = threadIdx.x & 15, part = threadIdx.x >> 4;
-  const P2Row prw = p2_row(C2, g, row);
+  const P2Row prw = SYM ? P2Row{g * 16 + row, false} : p2_row(C2, g, row);
   const float sgn = prw.neg ? -1.f : 1.f;
   // split by sign (relaxed entry = wp a_lo + wn a_up), and the entry's place in the tile.
   // Entries k and k + TP lie TS channels apart at the same position, so only the first TP
@@ -2559,7 +2598,7 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) : 1, 8)))
     __syncthreads();
     if (xi + 1 < XW) pfetch(X1 + t2.stride);
     {
-      float bpart = 0.f;
+      float bpart = 0.f, gpart = 0.f;
 #pragma unroll
       for (int k = 0; k < NEP; ++k) {
         // (no early exit: the loop unrolls, so the arrays are indexed statically)
@@ -2568,12 +2607,14 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) : 1, 8)))
           const float4v pr = prm[e];
           const float v = fmaf(wp[k], pr[0], wn[k] * pr[1]);
           bpart = fmaf(wn[k], pr[2], bpart);
+          if constexpr (SYM) gpart = fmaf(wp[k] - wn[k], pr[2], gpart);
           // layer-1 bias and the linear term of the concretisation together: v (W1 x0 + b1)
           bpart = fmaf(v, pr[3], bpart);
           tile[toff[k % TP] + (k / TP) * TS * CS] = v;
         }
       }
       bred[part * 16 + row] = bpart;
+      if constexpr (SYM) bred[(RPT + part) * 16 + row] = gpart;
     }
     __syncthreads();
 
@@ -2639,21 +2680,27 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) : 1, 8)))
     __syncthreads();
     if (threadIdx.x < 16) {
       const int r = threadIdx.x;
-      const P2Row pr = p2_row(C2, g, r);
+      const P2Row pr = SYM ? P2Row{g * 16 + r, false} : p2_row(C2, g, r);
       float ta = 0.f, tb = (pr.neg ? -1.f : 1.f) * t2.b[pr.c2];
       for (int w = 0; w < NW; ++w) ta += red[w * 16 + r];
       for (int q = 0; q < RPT; ++q) tb += bred[q * 16 + r];
       vb[xi][r] = tb - eps * ta;
+      if constexpr (SYM) {
+        float gs = 0.f;
+        for (int q = 0; q < RPT; ++q) gs += bred[(RPT + q) * 16 + r];
+        vb[xi][16 + r] = (tb + gs) + eps * ta;
+      }
     }
   }
-  // l and u of the block's 8 neurons in each of its XW windows (rows r and r + 8 are +-e_j of
-  // one neuron), and their relaxation for the passes above: XW consecutive neurons per channel
+  // l and u of the block's 8 (SYM: 16) neurons in each of its XW windows (rows r and r + 8 are
+  // +-e_j of one neuron), and their relaxation for the passes above: XW consecutive neurons per channel
   __syncthreads();
-  if (threadIdx.x < 8 * XW) {
+  constexpr int NC = SYM ? 16 : 8;
+  if (threadIdx.x < NC * XW) {
     const int cc = threadIdx.x / XW, xi = threadIdx.x - cc * XW;
-    const long j = ((long)(g * 8 + cc) * H2 + y2) * W2 + x2c * XW + xi;
+    const long j = ((long)(g * NC + cc) * H2 + y2) * W2 + x2c * XW + xi;
     const long pi = b * n_relu + off2 + j;
-    float l = vb[xi][cc], u = -vb[xi][cc + 8];
+    float l = vb[xi][cc], u = SYM ? vb[xi][cc + 16] : -vb[xi][cc + 8];
     parent_clip(l, u, lpar, upar, pi);
     L[pi] = l;
     U[pi] = u;
@@ -5491,28 +5538,41 @@ using Pass2Kernel = void (*)(DLayer, DLayer, long, const float*, const float*, c
                              const float*, float, float*, float*, long, long, const int8_t*,
                              const float*, float*, float*, float*, int8_t*, const float*,
                              const float*);
+long pass2_blocks(const lirpa_net* net, long nb);
 // Windows per block of the receptive-field pass 2 (along x2): 8 when the map width allows it
 // (fewer blocks, each set-up shared by more windows), else 4.
 int p2_xw(const lirpa_net* net) { return net->T[1].out_w % 8 == 0 ? 8 : 4; }
+// ... and of its bound of nb sub-domains: one where blocks of 8 or 4 windows would leave CUs
+// idle while each block runs its windows in turn (8-16-channel net, by eights and by ones: one
+// sub-domain 20.7 and 8.0 us, four 21.5 and 9.9).  The sums are the same either way, so results
+// do not depend on the chunk.
+int p2_xw_bound(const lirpa_net* net, long nb) {
+  return pass2_blocks(net, nb) / p2_xw(net) < 256 ? 1 : p2_xw(net);
+}
 
-template <int XW>
+template <int XW, bool SYM>
 Pass2Kernel pass2_kernel_xw(const lirpa_layer& t1, const lirpa_layer& t2) {
   if (t1.k == 4 && t1.stride == 2 && t1.pad == 1 && t1.in_c == 3) {
-    if (t2.k == 4 && t1.out_c == 8) return k_pass2_window<4, 2, 1, 4, 8, 3, XW>;
-    if (t2.k == 4 && t1.out_c == 16) return k_pass2_window<4, 2, 1, 4, 16, 3, XW>;
-    if (t2.k == 3 && t1.out_c == 8) return k_pass2_window<4, 2, 1, 3, 8, 3, XW>;
+    if (t2.k == 4 && t1.out_c == 8) return k_pass2_window<4, 2, 1, 4, 8, 3, XW, SYM>;
+    if (t2.k == 4 && t1.out_c == 16) return k_pass2_window<4, 2, 1, 4, 16, 3, XW, SYM>;
+    if (t2.k == 3 && t1.out_c == 8) return k_pass2_window<4, 2, 1, 3, 8, 3, XW, SYM>;
   }
   return nullptr;
 }
 
-Pass2Kernel pass2_kernel_for(const lirpa_net* net, int* nw) {
+// (sym: no given slopes, one row per neuron; xw: p2_xw_bound)
+Pass2Kernel pass2_kernel_for(const lirpa_net* net, int* nw, bool sym = false, int xw = 0) {
   if (net->L < 3) return nullptr;
   if (net->T[1].out_w % 4) return nullptr;
   const lirpa_layer &t1 = net->T[0], &t2 = net->T[1];
   if (t1.kind != LIRPA_CONV2D || t2.kind != LIRPA_CONV2D) return nullptr;
   if ((t2.out_c % 16 && t2.out_c != 8) || t1.in_c > 8) return nullptr;
   *nw = t1.in_c;
-  return p2_xw(net) == 8 ? pass2_kernel_xw<8>(t1, t2) : pass2_kernel_xw<4>(t1, t2);
+  sym = sym && t2.out_c % 16 == 0;
+  if (xw == 1) return sym ? pass2_kernel_xw<1, true>(t1, t2) : pass2_kernel_xw<1, false>(t1, t2);
+  if (sym)
+    return p2_xw(net) == 8 ? pass2_kernel_xw<8, true>(t1, t2) : pass2_kernel_xw<4, true>(t1, t2);
+  return p2_xw(net) == 8 ? pass2_kernel_xw<8, false>(t1, t2) : pass2_kernel_xw<4, false>(t1, t2);
 }
 
 using Pass2GradKernel = void (*)(DLayer, DLayer, const float*, const float*, long, float,
@@ -6239,9 +6299,10 @@ int8_t* tsign_of(const Chunk& c, int pass) {
 using FcBoundKernel = void (*)(DLayer, DLayer, const float*, unsigned, unsigned, Sink, FcSrc);
 // (spec: the variant that takes the final pass's spec rows from C W_L through a closing
 // Linear layer of 97..100 features; conv 3 -> 8 -> 16 channels, three sub-domains per block;
-// tape: the FC variant that also writes the reverse sweep's tape over g^(1) and sign tape)
+// tape: the FC variant that also writes the reverse sweep's tape over g^(1) and sign tape;
+// sym: the FC variant with one row per neuron)
 FcBoundKernel conv12_bound_for(const lirpa_net* net, bool fc, int nbs, int* nwaves,
-                               bool spec = false, bool tape = false) {
+                               bool spec = false, bool tape = false, bool sym = false) {
   if (net->L < 3) return nullptr;
   const lirpa_layer &t2 = net->T[1], &t1 = net->T[0];
   if (t2.kind != LIRPA_CONV2D || t1.kind != LIRPA_CONV2D) return nullptr;
@@ -6264,6 +6325,9 @@ FcBoundKernel conv12_bound_for(const lirpa_net* net, bool fc, int nbs, int* nwav
     if (fc && tape)
       return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, true, 2, 0,
                               true>;
+    if (fc && sym)
+      return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, true, 2, 0,
+                              false, true>;
     if (fc) return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, true, 2>;
     if (nbs == 2)
       return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, false, 2>;
@@ -6276,6 +6340,9 @@ FcBoundKernel conv12_bound_for(const lirpa_net* net, bool fc, int nbs, int* nwav
     if (fc && tape)
       return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, true, 2, 0,
                               true>;
+    if (fc && sym)
+      return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, true, 2, 0,
+                              false, true>;
     if (fc) return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, true, 2>;
     return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, false, 2>;
   }
@@ -6388,10 +6455,12 @@ int run_stages(const Chunk& c, int pass, int mtop, long R, long Q, long ldq, flo
 int pass2_window(const Chunk& c) {
   const lirpa_net* net = c.net;
   int nw = 0;
-  Pass2Kernel kern = pass2_kernel_for(net, &nw);
+  const int xw = p2_xw_bound(net, c.nb);
+  Pass2Kernel kern = pass2_kernel_for(net, &nw, !c.alpha, xw);
   if (!kern) return 1;
   const lirpa_layer &t1 = net->T[0], &t2 = net->T[1];
-  long blocks = pass2_blocks(net, c.nb) / p2_xw(net);
+  long blocks = pass2_blocks(net, c.nb) / xw;
+  if (!c.alpha && t2.out_c % 16 == 0) blocks /= 2;
   const float* alo = at<float>(c.ws, c.p->off_alo) + net->poff[1];
   const float* aup = at<float>(c.ws, c.p->off_aup) + net->poff[1];
   const float* bup = at<float>(c.ws, c.p->off_bup) + net->poff[1];
@@ -6515,9 +6584,10 @@ int fc_open_stage(const Chunk& c, int k, long R, long Q, long ldq) {
 
 // Pass 3 of a net whose layers 1 and 2 are such convolutions and whose layer 3 is fully
 // connected, bounded without a gradient tape: one kernel from the rows of W_3 to the bounds.
-FcBoundKernel fc_bound_for(const lirpa_net* net, int k, int* nwaves, bool tape = false) {
+FcBoundKernel fc_bound_for(const lirpa_net* net, int k, int* nwaves, bool tape = false,
+                           bool sym = false) {
   if (k != 3 || net->L < 4 || net->T[2].kind != LIRPA_LINEAR) return nullptr;
-  return conv12_bound_for(net, true, 2, nwaves, false, tape);
+  return conv12_bound_for(net, true, 2, nwaves, false, tape, sym);
 }
 
 // Whether pass k of a gradient chunk runs as one tape-writing k_convT_fc_bound.  Its rows are
@@ -6534,8 +6604,15 @@ int fc_bound_stage(const Chunk& c, int k, long R, long Q) {
   const lirpa_net* net = c.net;
   int nw = 0;
   const bool tape = c.tape;
-  FcBoundKernel kern = fc_bound_for(net, k, &nw, tape);
+  // without given slopes (and a tape, which holds both signs' rows) one row per neuron does; a
+  // block's rows still span at most two sub-domains, and rows 2i, 2i + 1 one
+  const bool sym = !tape && !c.alpha && net->n[k] % 2 == 0 && net->n[k] >= 16;
+  FcBoundKernel kern = fc_bound_for(net, k, &nw, tape, sym);
   if (!kern || !fc_open_ok(c, k, R) || (tape && !fused_tape_pass(c, k, R))) return 1;
+  if (sym) {
+    R /= 2;
+    Q /= 2;
+  }
   const lirpa_layer& fl = net->T[k - 1];
   Sink s = slab_sink(c, 1, nullptr, 0, R);  // the relaxation of layer 1 (bias: z1)
   const Sink sb = bound_sink(c, R, c.L + net->off[k], c.U + net->off[k], net->n_relu, net->n[k]);
@@ -7284,7 +7361,10 @@ Plan plan_for(const lirpa_net* net, long S, long Bc, int mode, bool split = true
 // not fit beside their weight fragments).
 long fit_chunk(const lirpa_net* net, long S, long B, size_t ws_bytes, Plan* out, int mode = 0) {
   for (const bool split : {true, false}) {
-    long lo = 0, hi = B;
+    // (the whole batch usually fits: one plan)
+    *out = plan_for(net, S, B, mode, split);
+    if (out->total <= ws_bytes) return B;
+    long lo = 0, hi = B - 1;
     while (lo < hi) {
       long mid = (lo + hi + 1) / 2;
       if (plan_for(net, S, mid, mode, split).total <= ws_bytes) lo = mid; else hi = mid - 1;
