@@ -253,6 +253,8 @@ struct FcSrc {
   // spec source of k_convT_fc_bound (the final pass from the merged spec rows): b holds
   // C W_L [S][nk] followed by C b_L [S]; r_lo, r_up, r_bu the relaxation of layer L-1 (read);
   // a_lo, a_up, b_up that of layer L-2; the two layers' bias vectors
+  int nspec = 0;  // spec rows; a sub-domain's rows past them (R > nspec) repeat the last and are
+                  // not written
   const float* sbias_k = nullptr;   // layer L-2
   const float* sbias_k1 = nullptr;  // layer L-1
 };
@@ -446,6 +448,8 @@ __global__ void __launch_bounds__(256) k_init_fc_rows(DLayer t, const float* __r
   if (w == 0 && ok) s.beta[q] = sgn * t.b[j] + ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
+#include "split_frags.hpp"
+
 // Everything a call derives from the network, x0 and eps alone, in one launch: the exact
 // layer-1 bounds and z1 = W1 x0 + b1, the per-neuron bias vectors of ReLU layers 2..L-1 and the
 // transposed weights of the fully connected layers whose intermediate pass starts from them.
@@ -472,14 +476,18 @@ struct SetupJob {
   const float* C;
   DLayer tL;
   int S;
+  // split weight fragments: the blocks from frag_blk on, frag[k].blk of them per job
+  int frag_blk, nfrag;
+  FragJob frag[kFragJobs];
 };
 
 // Neuron j of h^(1): row +-e_j carried through T_1 is +-W_1[j] (no relaxation in front of
 // layer 1), so its bounds are z1_j -+ eps ||W_1[j]||_1 with z1_j = W_1[j] x0 + b_1[j] (Eq. 8; the
 // taps of a convolution that fall on the zero padding are no entries of the row).  The 16 lanes
 // of a group take every 16th entry and the sums meet in a fixed shuffle tree.
-__device__ __forceinline__ void layer1_neuron(const SetupJob& job, long j, int g) {
-  const DLayer& t = job.t1;
+template <class Job>
+__device__ __forceinline__ void layer1_neuron(const Job& job, long j, int g) {
+  const auto& t = job.t1;
   float lin = 0.f, l1 = 0.f;
   if (t.kind == LIRPA_LINEAR) {
     for (int i = g; i < t.in_c; i += 16) {
@@ -512,7 +520,16 @@ __device__ __forceinline__ void layer1_neuron(const SetupJob& job, long j, int g
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_setup(SetupJob job) {
+__global__ void __launch_bounds__(kBlock) k_setup(SetupJob job_) {
+  const __attribute__((address_space(4))) SetupJob& job =
+      *(const __attribute__((address_space(4))) SetupJob*)__builtin_amdgcn_kernarg_segment_ptr();
+  if ((int)blockIdx.x >= job.frag_blk) {
+    int fb = (int)blockIdx.x - job.frag_blk, k = 0;
+    while (k + 1 < job.nfrag && fb >= job.frag[k].blk) fb -= job.frag[k++].blk;
+    const int idx = fb * (int)blockDim.x + (int)threadIdx.x;
+    if (idx < job.frag[k].nmt * job.frag[k].nks * 64) frag_entry(job.frag[k], idx);
+    return;
+  }
   long e = blockIdx.x * (long)blockDim.x + threadIdx.x;
   if (e < 16 * job.n1) {  // a group of 16 lanes never straddles the segment's end
     layer1_neuron(job, e >> 4, (int)(e & 15));
@@ -1984,7 +2001,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
       // the matrix waves share the rows: wave w relaxes k-steps w, w + NM, ... (each feature
       // j once, its terms in the wave's sbeta); a barrier of both roles follows
       const int nj = fc.nk;
-      const unsigned sn = qs - bs * R;
+      const unsigned sn = min(qs - bs * R, (unsigned)fc.nspec - 1u);
       const long pb3 = (long)bs * s.pstride;
 #pragma unroll
       for (int t = 0; t < (SPEC + NM - 1) / NM; ++t) {
@@ -2002,7 +2019,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
         }
         vts[j * 16 + n] = ah;
       }
-      if (wave == 0 && G == 0) sbeta += fc.b[(long)R * nj + sn];
+      if (wave == 0 && G == 0) sbeta += fc.b[(long)fc.nspec * nj + sn];
       lds_barrier();  // the rows (matched by the x waves' first barrier of the spec source)
     }
     // A operands of entry tile mt of input row y1 (4 k + G < 4 (SPEC - 1) < nj for
@@ -2434,7 +2451,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     fc.r_bu[pp] = rx.bu;
     fc.code[pi] = (int8_t)rx.code;
   } else {
-    if (q >= Q) return;
+    if (q >= Q || (SPEC > 0 && (int)r >= fc.nspec)) return;
     Acc a{tb, 0.f, ta};
     // (spec source: no running bias from an earlier stage)
     sink_finish<MODE_BOUND>(s, a, q, q / R, r, SPEC > 0);
@@ -5709,7 +5726,7 @@ FragJob frag_job(const lirpa_net* net, int m, int kind) {
   const int k = fc ? 1 : t.k, st = fc ? 1 : t.stride, tt = (k + st - 1) / st;
   const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
   const int cqo = 2 * ((t.out_c + 7) / 8);
-  FragJob f{t.W, t.in_c, t.out_c, k, st, tt, cqi, cqo, kind, 0, 0, nullptr};
+  FragJob f{t.W, t.in_c, t.out_c, k, st, tt, cqi, cqo, kind, 0, 0, 0, nullptr};
   f.nmt = kind ? (4 * cqo + 15) / 16 : (st * st * 4 * cqi + 15) / 16;
   f.nks = kind ? (k * k * 4 * cqi + 31) / 32 : (tt * tt * 4 * cqo + 31) / 32;
   return f;
@@ -6211,6 +6228,7 @@ struct Chunk {
   const float* x0;
   float eps;
   long S;
+  long B;              // sub-domains of the call (the same for every chunk of it)
   long nb;             // sub-domains in this chunk
   float* L;            // l rows of the chunk, stride n_relu
   float* U;
@@ -6759,35 +6777,6 @@ int win_pass(const Chunk& c, int k, bool grad) {
   return LIRPA_OK;
 }
 
-// The split weight fragments that this call's kernels read.
-int win_frags(const lirpa_net* net, const Plan& p, void* ws, hipStream_t st) {
-  FragJobs jobs{};
-  int most = 0;
-  auto flush = [&]() -> int {
-    if (!jobs.n) return LIRPA_OK;
-    const int n = jobs.n, big = most;
-    const int e = launch_k("win_frags", st, [&] {
-      hipLaunchKernelGGL(k_win_frags, dim3((unsigned)((big * 64 + 255) / 256), (unsigned)n),
-                         dim3(256), 0, st, jobs);
-    });
-    jobs.n = 0;
-    most = 0;
-    return e;
-  };
-  for (int m = 1; m <= net->L; ++m)
-    for (int kind = 0; kind < 2; ++kind) {
-      const size_t off = kind ? p.off_ff[m] : p.off_fb[m];
-      if (!off) continue;
-      FragJob f = frag_job(net, m, kind);
-      f.dst = at<uint4v>(ws, off);
-      most = std::max(most, f.nmt * f.nks);
-      jobs.j[jobs.n++] = f;
-      if (jobs.n == kFragJobs)
-        if (int e = flush()) return e;
-    }
-  return flush();
-}
-
 bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool split) {
   // the same choices, in the same order, as bound_chunk makes for a chunk without a tape
   int nw = 0;
@@ -6900,7 +6889,12 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
   // final pass
   long R = c.S, Q = c.nb * R, ldq = round_up(Q, 64);
   const lirpa_layer& tL = net->T[L - 1];
-  if (!c.tape && L == 4 && c.p->off_wsp && net->T[2].kind == LIRPA_LINEAR && R >= 8 &&
+  // With fewer than 8 spec rows (a search's one property, bounded on both sides: 2) the kernel
+  // below takes a sub-domain's rows padded to the 8 its blocks need: at 129 sub-domains one launch
+  // of 41 us instead of three of 82; from 512 on the padding costs a second round of blocks (84
+  // against 85 us with one row at 1,000, 83 against 132 with four), from 1,025 a third.
+  const long Rp = c.S < 8 && c.B * 8 <= 8192 ? 8 : c.S;
+  if (!c.tape && L == 4 && c.p->off_wsp && net->T[2].kind == LIRPA_LINEAR && Rp >= 8 &&
       (net->n[3] + 3) / 4 == 25) {
     // the whole final pass in one kernel: the spec rows through T_4 (k_setup's C W_4), their
     // relaxation onto layer 3, T_3^T on MFMA and the relaxation onto layer 2 built into the
@@ -6908,8 +6902,9 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
     // concretisation (conv 3 -> 8 -> 16 channels on 32x32, then a Linear layer of 97..100)
     int nw = 0;
     if (FcBoundKernel kern = conv12_bound_for(net, false, 3, &nw, /*spec=*/true)) {
-      Sink s = slab_sink(c, 1, nullptr, ldq, R);
-      const Sink sb = bound_sink(c, R, lb, lb, c.S, c.S);
+      const long Qp = c.nb * Rp;
+      Sink s = slab_sink(c, 1, nullptr, ldq, Rp);
+      const Sink sb = bound_sink(c, Rp, lb, lb, c.S, c.S);
       s.eps = sb.eps;
       s.x0 = sb.x0;
       s.lo = sb.lo;
@@ -6928,10 +6923,11 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
       f.r_bu = at<float>(c.ws, c.p->off_bup) + net->poff[3];
       f.sbias_k = at<float>(c.ws, c.p->off_bz) + net->poff[2];
       f.sbias_k1 = at<float>(c.ws, c.p->off_bz) + net->poff[3];
-      const unsigned nblk16 = (unsigned)round_up((Q + 15) / 16, 16);
+      f.nspec = (int)c.S;
+      const unsigned nblk16 = (unsigned)round_up((Qp + 15) / 16, 16);
       return launch_k(tag("spec_bound", 2, L), c.st, [&] {
         hipLaunchKernelGGL(kern, dim3(nblk16), dim3(64 * nw), 0, c.st, dlayer(net->T[1]),
-                           dlayer(net->T[0]), nullptr, (unsigned)ldq, (unsigned)Q, s, f);
+                           dlayer(net->T[0]), nullptr, (unsigned)ldq, (unsigned)Qp, s, f);
       });
     }
   }
@@ -7022,10 +7018,28 @@ int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0
     job.S = S;
     total += (long)S * (net->n[net->L - 1] + 1);
   }
-  if (int e = win_frags(net, p, ws, st)) return e;
-  return launch_k(tag("setup", 1, 1), st, [&] {
-    hipLaunchKernelGGL(k_setup, grid_for(total), dim3(kBlock), 0, st, job);
-  });
+  // the split weight fragments that this call's kernels read; a net with more of them than a
+  // launch carries takes more launches
+  int m = 1, kind = 0, blocks = (int)grid_for(total).x;
+  job.frag_blk = blocks;
+  do {
+    job.nfrag = 0;
+    for (; m <= net->L && job.nfrag < kFragJobs; kind ? (++m, kind = 0) : kind = 1) {
+      const size_t off = kind ? p.off_ff[m] : p.off_fb[m];
+      if (!off) continue;
+      FragJob f = frag_job(net, m, kind);
+      f.dst = at<uint4v>(ws, off);
+      f.blk = (f.nmt * f.nks * 64 + kBlock - 1) / kBlock;
+      blocks += f.blk;
+      job.frag[job.nfrag++] = f;
+    }
+    if (int e = launch_k(tag("setup", 1, 1), st, [&] {
+          hipLaunchKernelGGL(k_setup, dim3((unsigned)blocks), dim3(kBlock), 0, st, job);
+        }))
+      return e;
+    job.frag_blk = blocks = 0;  // further launches: fragments alone
+  } while (m <= net->L);
+  return LIRPA_OK;
 }
 
 // Gradient of J_b = sum_s lb[b][s] with respect to alpha for every sub-domain of the chunk,
@@ -7387,6 +7401,7 @@ Chunk make_chunk(lirpa_net* net, const Plan& p, void* ws, const float* x0, float
   c.x0 = x0;
   c.eps = eps;
   c.S = S;
+  c.B = B;
   c.nb = std::min(p.Bc, B - b0);
   c.L = l_out ? l_out + b0 * net->n_relu : at<float>(ws, p.off_l);
   c.U = u_out ? u_out + b0 * net->n_relu : at<float>(ws, p.off_u);

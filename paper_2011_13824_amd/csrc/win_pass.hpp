@@ -23,88 +23,9 @@
 constexpr int kWinMax = 6;   // most layers below the pass's own
 constexpr int kWinLds = 160 * 1024;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-
-// Two floats as a pair of bf16 (round to nearest even), the first in the low half.
-__device__ __forceinline__ unsigned pk_bf16(float a, float b) {
-  return __builtin_bit_cast(unsigned, __builtin_convertvector(float2v{a, b}, bf16x2));
-}
-
-// The three bf16 parts of a pair of floats.
-__device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsigned& m,
-                                           unsigned& l) {
-  h = pk_bf16(a, b);
-  a -= __builtin_bit_cast(float, h << 16);
-  b -= __builtin_bit_cast(float, h & 0xffff0000u);
-  m = pk_bf16(a, b);
-  a -= __builtin_bit_cast(float, m << 16);
-  b -= __builtin_bit_cast(float, m & 0xffff0000u);
-  l = pk_bf16(a, b);
-}
-
 __device__ __forceinline__ float4v mfma_b(uint4v a, uint4v b, float4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
-// Split weights of one layer in the order of the matrix operand: dst[(mt ks + k) 3 + part][lane],
-// 8 bf16 each, for M tile mt and K step k.  Lane l holds row mt 16 + l % 16, entries
-// 8 (l / 16) .. + 7 of the step's 32.
-//   kind 0, T^T:  row (phase py s + px, input channel ci of 4 Cqi), entry (j = jy t + jx, output
-//                 channel of 4 Cqo);
-//   kind 1, T:    row output channel, entry (tap, input channel of 4 Cqi).
-struct FragJob {
-  const float* W;  // [out_c][in_c][k][k]
-  int in_c, out_c, k, s, t, Cqi, Cqo, kind, nmt, nks;
-  uint4v* dst;
-};
-constexpr int kFragJobs = 16;
-struct FragJobs {
-  int n;
-  FragJob j[kFragJobs];
-};
-
-__global__ void __launch_bounds__(256) k_win_frags(FragJobs jobs) {
-  const FragJob& f = jobs.j[blockIdx.y];
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= f.nmt * f.nks * 64) return;
-  const int lane = idx & 63, step = idx >> 6;
-  const int mt = step / f.nks, ks = step - mt * f.nks;
-  const int M = mt * 16 + (lane & 15);
-  float v[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int kk = ks * 32 + (lane >> 4) * 8 + e;
-    v[e] = 0.f;
-    if (f.kind == 0) {
-      const int ci = M % (4 * f.Cqi), ph = M / (4 * f.Cqi);
-      const int co = kk % (4 * f.Cqo), j = kk / (4 * f.Cqo);
-      const int ky = ph / f.s + f.s * (j / f.t), kx = ph % f.s + f.s * (j % f.t);
-      if (ph < f.s * f.s && j < f.t * f.t && ci < f.in_c && co < f.out_c && ky < f.k && kx < f.k)
-        v[e] = f.W[(((long)co * f.in_c + ci) * f.k + ky) * f.k + kx];
-    } else {
-      const int ci = kk % (4 * f.Cqi), tap = kk / (4 * f.Cqi);
-      if (M < f.out_c && tap < f.k * f.k && ci < f.in_c)
-        v[e] = f.W[((long)M * f.in_c + ci) * f.k * f.k + tap];
-    }
-  }
-  uint4v h, m, l;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    unsigned a, b, c;
-    split_pair(v[2 * e], v[2 * e + 1], a, b, c);
-    h[e] = a;
-    m[e] = b;
-    l[e] = c;
-  }
-  uint4v* d = f.dst + (size_t)step * 192 + lane;
-  d[0] = h;
-  d[64] = m;
-  d[128] = l;
 }
 
 // One map of the chain.  Index m = 0 is x; T_m leads from g^(m) down to g^(m-1).

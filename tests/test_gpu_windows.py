@@ -109,3 +109,20 @@ def test_workspace_without_room_for_fragments(mode):
                               None, None, ws, room)
             lr = ref.bound(rnet, x0, 0.1, C, None, alpha)[0]
         close(f"{mode} lb", lb.cpu().double().numpy(), lr)
+
+
+@pytest.mark.parametrize("B,S", [(1, 1), (5, 7), (129, 2), (1024, 1), (1025, 3)])
+def test_few_spec_rows(B, S):
+    # fewer than 8 spec rows, padded to 8 up to 1,024 sub-domains and in stages beyond: the rows
+    # of the call with all 9, whose blocks need no padding (the same sums up to their order: 1e-5)
+    w = wl.base()
+    rng = np.random.default_rng(B)
+    net = lirpa.Network(w.layers)
+    alpha = dev(rng.uniform(0, 1, (B, net.n_relu)).astype(np.float32))
+    want = net.bound(dev(w.x0), w.eps, dev(w.C), None, alpha).cpu().double().numpy()
+    lb = net.bound(dev(w.x0), w.eps, dev(w.C[:S]), None, alpha)
+    close("lb", lb.cpu().double().numpy(), want[:, :S])
+    lo, up = net.bound_ul(dev(w.x0), w.eps, dev(w.C[:S]), None, alpha)
+    close("ul lb", lo.cpu().double().numpy(), want[:, :S])
+    neg = net.bound(dev(w.x0), w.eps, dev(-w.C), None, alpha).cpu().double().numpy()
+    close("ul ub", up.cpu().double().numpy(), -neg[:, :S])
