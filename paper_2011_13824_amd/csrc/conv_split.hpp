@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
   const unsigned b = qok ? q / (unsigned)s.R : 0u;
   const long pb = (long)b * s.pstride;
   const int slotb = 3 * c.rowb, NS = c.NS, c2 = c.Cq / 2;
-  float* red = reinterpret_cast<float*>(csm + NS * slotb);  // [nw][3][16]
+  float* red = reinterpret_cast<float*>(csm + NS * slotb);  // [nw][4][16]
   for (int e = tid; e < NS * 3; e += nt)  // the zero chunk that ends each part of a row
     *reinterpret_cast<uint4v*>(csm + (e + 1) * c.rowb - 16) = uint4v{0, 0, 0, 0};
   const int ntask = c.W * c.Cq * 4, HW = c.H * c.W;
@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
   // M tiles dealt to the waves; with fewer tiles than waves, nw / nmt waves share a tile's columns
   const int share = nw / c.nmt > 1 ? nw / c.nmt : 1;
   const int mt0 = wave / share, xs0 = wave - mt0 * share, mstep = (nw + share - 1) / share;
-  float beta = 0.f, lin = 0.f, l1 = 0.f;
+  float beta = 0.f, lin = 0.f, l1 = 0.f, gap = 0.f;
   uint4v A[KS ? KS : 1][3];
   int cur = -1;
   for (int ay = 0; ay < nay; ++ay) {
@@ -170,6 +170,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
             const float ah = a * (a >= 0.f ? lo[r] : up[r]);
             beta = fmaf(fminf(a, 0.f), bu[r], beta);
             beta = fmaf(ah, bz[r], beta);
+            gap = fmaf(fabsf(a), bu[r], gap);
             s.out[idx] = ah;
           } else {
             if (s.tsign) s.tsign[idx] = sign8(a);
@@ -182,6 +183,8 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     park(ay + 1);
     __syncthreads();
   }
+  gap += __shfl_xor(gap, 16, 64);
+  gap += __shfl_xor(gap, 32, 64);
   beta += __shfl_xor(beta, 16, 64);
   lin += __shfl_xor(lin, 16, 64);
   l1 += __shfl_xor(l1, 16, 64);
@@ -189,17 +192,19 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
   lin += __shfl_xor(lin, 32, 64);
   l1 += __shfl_xor(l1, 32, 64);
   if (lane < 16) {
-    red[(wave * 3 + 0) * 16 + lane] = beta;
-    red[(wave * 3 + 1) * 16 + lane] = lin;
-    red[(wave * 3 + 2) * 16 + lane] = l1;
+    red[(wave * 4 + 0) * 16 + lane] = beta;
+    red[(wave * 4 + 1) * 16 + lane] = lin;
+    red[(wave * 4 + 2) * 16 + lane] = l1;
+    red[(wave * 4 + 3) * 16 + lane] = gap;
   }
   __syncthreads();
   if (tid >= 16 || !qok) return;
   Acc tot{0.f, 0.f, 0.f};
   for (int w = 0; w < nw; ++w) {
-    tot.beta += red[(w * 3 + 0) * 16 + tid];
-    tot.lin += red[(w * 3 + 1) * 16 + tid];
-    tot.l1 += red[(w * 3 + 2) * 16 + tid];
+    tot.beta += red[(w * 4 + 0) * 16 + tid];
+    tot.lin += red[(w * 4 + 1) * 16 + tid];
+    tot.l1 += red[(w * 4 + 2) * 16 + tid];
+    tot.gap += red[(w * 4 + 3) * 16 + tid];
   }
   sink_finish<MODE>(s, tot, q, b, q % (unsigned)s.R, false);
 }

@@ -25,7 +25,7 @@ __global__ void __launch_bounds__(kFcThreads)
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), n = lane & 15, G = lane >> 4;
   const unsigned q0 = xcd_range(blockIdx.x) * (unsigned)NQ;
   if (q0 >= Q) return;  // grid padding, uniform per block
-  float* red = reinterpret_cast<float*>(fsm + 3 * c.plane);  // [NW][3][NQ]
+  float* red = reinterpret_cast<float*>(fsm + 3 * c.plane);  // [NW][4][NQ]
   for (int e = tid; e < c.nks * 8 * (NQ / 4); e += kFcThreads) {
     const int q4 = e % (NQ / 4), k4 = e / (NQ / 4);  // four inputs of four rows
     float4v v[4];
@@ -44,13 +44,13 @@ __global__ void __launch_bounds__(kFcThreads)
   unsigned qn[NT];
   bool qok[NT];
   long pb[NT];
-  float beta[NT], lin[NT], l1[NT];
+  float beta[NT], lin[NT], l1[NT], gap[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     qn[t] = q0 + 16 * t + n;
     qok[t] = qn[t] < Q;
     pb[t] = (long)(qok[t] ? qn[t] / (unsigned)s.R : 0u) * s.pstride;
-    beta[t] = lin[t] = l1[t] = 0.f;
+    beta[t] = lin[t] = l1[t] = gap[t] = 0.f;
   }
   const char* bp = fsm + n * 16;
   for (int mp = wave; 2 * mp < c.nmt; mp += NW) {
@@ -125,6 +125,7 @@ __global__ void __launch_bounds__(kFcThreads)
             const float ah = a * (a >= 0.f ? pl[r] : pu[r]);
             beta[t] = fmaf(fminf(a, 0.f), pc[r], beta[t]);
             beta[t] = fmaf(ah, pz[r], beta[t]);
+            gap[t] = fmaf(fabsf(a), pc[r], gap[t]);
             s.out[idx] = ah;
           } else {
             if (s.tsign) s.tsign[idx] = sign8(a);
@@ -137,12 +138,12 @@ __global__ void __launch_bounds__(kFcThreads)
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    float v[3] = {beta[t], lin[t], l1[t]};
+    float v[4] = {beta[t], lin[t], l1[t], gap[t]};
 #pragma unroll
-    for (int e = 0; e < 3; ++e) {
+    for (int e = 0; e < 4; ++e) {
       v[e] += __shfl_xor(v[e], 16, 64);
       v[e] += __shfl_xor(v[e], 32, 64);
-      if (lane < 16) red[(wave * 3 + e) * NQ + 16 * t + lane] = v[e];
+      if (lane < 16) red[(wave * 4 + e) * NQ + 16 * t + lane] = v[e];
     }
   }
   __syncthreads();
@@ -150,9 +151,10 @@ __global__ void __launch_bounds__(kFcThreads)
   if (tid >= NQ || q >= Q) return;
   Acc tot{0.f, 0.f, 0.f};
   for (int w = 0; w < NW; ++w) {
-    tot.beta += red[(w * 3 + 0) * NQ + tid];
-    tot.lin += red[(w * 3 + 1) * NQ + tid];
-    tot.l1 += red[(w * 3 + 2) * NQ + tid];
+    tot.beta += red[(w * 4 + 0) * NQ + tid];
+    tot.lin += red[(w * 4 + 1) * NQ + tid];
+    tot.l1 += red[(w * 4 + 2) * NQ + tid];
+    tot.gap += red[(w * 4 + 3) * NQ + tid];
   }
   sink_finish<MODE>(s, tot, q, q / (unsigned)s.R, q % (unsigned)s.R, false);
 }

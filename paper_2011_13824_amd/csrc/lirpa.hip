@@ -216,6 +216,9 @@ struct Sink {
   const float* x0;
   float eps;
   float* beta;  // running bias of each row, [Qp]
+  // one row per neuron (a pass without given slopes, whose row -e_j is the negative of +e_j):
+  // the running gap sum |a| b_up of each row; the row then gives lo and hi.  Else null.
+  float* gap;
   long R;       // rows per sub-domain
   float* lo;
   float* hi;
@@ -260,7 +263,7 @@ struct FcSrc {
 };
 
 struct Acc {
-  float beta, lin, l1;
+  float beta, lin, l1, gap = 0.f;
 };
 
 template <int MODE>
@@ -280,6 +283,7 @@ __device__ __forceinline__ void sink_put(const Sink& s, Acc& acc, long i, float 
       acc.beta = fmaf(a, s.b_up[pi], acc.beta);
       ah = a * s.a_up[pi];
     }
+    if (s.gap) acc.gap = fmaf(fabsf(a), s.b_up[pi], acc.gap);
     acc.beta = fmaf(ah, s.bias[(unsigned)i / (unsigned)s.bias_hw], acc.beta);
     s.out[i * s.ldq + q] = ah;
   } else {
@@ -294,9 +298,16 @@ __device__ __forceinline__ void sink_finish(const Sink& s, const Acc& acc, long 
                                             bool first) {
   if constexpr (MODE == MODE_SLAB) {
     s.beta[q] = first ? acc.beta : s.beta[q] + acc.beta;
+    if (s.gap) s.gap[q] = first ? acc.gap : s.gap[q] + acc.gap;
   } else {
     float beta = first ? acc.beta : s.beta[q] + acc.beta;
     float v = acc.lin - s.eps * acc.l1 + beta;
+    if (s.gap) {
+      const float g = first ? acc.gap : s.gap[q] + acc.gap;
+      s.lo[b * s.bstride + r] = v;
+      s.hi[b * s.bstride + r] = acc.lin + s.eps * acc.l1 + (beta + g);
+      return;
+    }
     if (r < s.n_half)
       s.lo[b * s.bstride + r] = v;
     else
@@ -398,11 +409,14 @@ __global__ void __launch_bounds__(kBlock) k_init_rows(DLayer t, const float* __r
 }
 
 // Pass initialisation for the rows +-e_j of a fully connected layer k, relaxed onto ReLU layer
-// k-1 (slab sink).  Block: 64 rows x 4 waves; each wave covers a quarter of the coefficients
+// k-1 (slab sink).  Block: 64 rows x NW waves; each wave covers its share of the coefficients
 // (float4 parameter loads), and the rows' bias terms are summed through LDS in a fixed order.
-__global__ void __launch_bounds__(256) k_init_fc_rows(DLayer t, const float* __restrict__ WT,
-                                                      long Q, Sink s) {
-  __shared__ float red[4][64];
+// 16 waves from 512 coefficients on: a wave's loop over them is a chain of cache latencies (1,568
+// coefficients, 25,500 rows: 0.306 ms with 4 waves, 0.119 with 16).
+template <int NW>
+__global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float* __restrict__ WT,
+                                                          long Q, Sink s) {
+  __shared__ float red[2][NW][64];
   const int lane = threadIdx.x & 63, w = wave_id();
   const long q = blockIdx.x * 64L + lane;
   const bool ok = q < Q;
@@ -411,11 +425,11 @@ __global__ void __launch_bounds__(256) k_init_fc_rows(DLayer t, const float* __r
   const int nk = t.out_c, nin = t.in_c;
   const int j = (int)(r % nk);
   const float sgn = r < nk ? 1.f : -1.f;
-  const int chunk = ((nin + 15) / 16) * 4;
+  const int chunk = ((nin + 4 * NW - 1) / (4 * NW)) * 4;
   const int i0 = w * chunk, i1 = min(nin, i0 + chunk);
   const long pb = b * s.pstride;
   const unsigned hw = (unsigned)s.bias_hw;
-  float beta = 0.f;
+  float beta = 0.f, gap = 0.f;
   if (ok) {
     int i = i0;
     for (; i + 4 <= i1; i += 4) {
@@ -429,6 +443,7 @@ __global__ void __launch_bounds__(256) k_init_fc_rows(DLayer t, const float* __r
         if (s.tape) s.tape[idx] = a;
         const float ah = a >= 0.f ? a * lo[u] : a * up[u];
         beta = fmaf(fminf(a, 0.f), bu[u], beta);
+        gap = fmaf(fabsf(a), bu[u], gap);
         beta = fmaf(ah, s.bias[(unsigned)(i + u) / hw], beta);
         s.out[idx] = ah;
       }
@@ -439,13 +454,23 @@ __global__ void __launch_bounds__(256) k_init_fc_rows(DLayer t, const float* __r
       if (s.tape) s.tape[idx] = a;
       const float ah = a >= 0.f ? a * s.a_lo[pb + i] : a * s.a_up[pb + i];
       beta = fmaf(fminf(a, 0.f), s.b_up[pb + i], beta);
+      gap = fmaf(fabsf(a), s.b_up[pb + i], gap);
       beta = fmaf(ah, s.bias[(unsigned)i / hw], beta);
       s.out[idx] = ah;
     }
   }
-  red[w][lane] = beta;
+  red[0][w][lane] = beta;
+  red[1][w][lane] = gap;
   __syncthreads();
-  if (w == 0 && ok) s.beta[q] = sgn * t.b[j] + ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+  if (w == 0 && ok) {
+    float tb = red[0][0][lane], tg = red[1][0][lane];
+    for (int e = 1; e < NW; ++e) {
+      tb += red[0][e][lane];
+      tg += red[1][e][lane];
+    }
+    s.beta[q] = sgn * t.b[j] + tb;
+    if (s.gap) s.gap[q] = tg;
+  }
 }
 
 #include "split_frags.hpp"
@@ -649,7 +674,7 @@ __global__ void __launch_bounds__(kBlock) k_convT(DLayer t, const float* __restr
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // Reduce (beta, lin, l1) of the two lane halves and of the waves of the block, then finish the
-// rows q0..q0+31.  red: LDS scratch of nw*3*32 floats.
+// rows q0..q0+31.  red: LDS scratch of nw*4*32 floats.
 template <int MODE>
 __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red, long q0, long Q,
                                              bool add_beta_from_acc) {
@@ -657,10 +682,12 @@ __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red,
   acc.beta += __shfl_xor(acc.beta, 32, 64);
   acc.lin += __shfl_xor(acc.lin, 32, 64);
   acc.l1 += __shfl_xor(acc.l1, 32, 64);
+  acc.gap += __shfl_xor(acc.gap, 32, 64);
   if (lane < 32) {
-    red[(wave * 3 + 0) * 32 + lane] = acc.beta;
-    red[(wave * 3 + 1) * 32 + lane] = acc.lin;
-    red[(wave * 3 + 2) * 32 + lane] = acc.l1;
+    red[(wave * 4 + 0) * 32 + lane] = acc.beta;
+    red[(wave * 4 + 1) * 32 + lane] = acc.lin;
+    red[(wave * 4 + 2) * 32 + lane] = acc.l1;
+    red[(wave * 4 + 3) * 32 + lane] = acc.gap;
   }
   __syncthreads();
   if (wave != 0 || lane >= 32) return;
@@ -668,9 +695,10 @@ __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red,
   if (q >= Q) return;
   Acc t{0.f, 0.f, 0.f};
   for (int w = 0; w < nw; ++w) {
-    t.beta += red[(w * 3 + 0) * 32 + lane];
-    t.lin += red[(w * 3 + 1) * 32 + lane];
-    t.l1 += red[(w * 3 + 2) * 32 + lane];
+    t.beta += red[(w * 4 + 0) * 32 + lane];
+    t.lin += red[(w * 4 + 1) * 32 + lane];
+    t.l1 += red[(w * 4 + 2) * 32 + lane];
+    t.gap += red[(w * 4 + 3) * 32 + lane];
   }
   (void)add_beta_from_acc;
   sink_finish<MODE>(s, t, q, q / s.R, q % s.R, false);
@@ -713,7 +741,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
   const unsigned q = q0 + n;
   const bool qok = q < Q;
   const unsigned b = qok ? q / (unsigned)s.R : 0u;
-  float* red = xs + (MODE == MODE_BOUND && s.x0 ? t.in_c * H0 * W0 : 0);  // [NW][3][16]
+  float* red = xs + (MODE == MODE_BOUND && s.x0 ? t.in_c * H0 * W0 : 0);  // [NW][4][16]
 
   const bool with_x0 = MODE == MODE_BOUND && s.x0 != nullptr;
   if (with_x0) {
@@ -747,7 +775,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
     }
   }
 
-  float beta = 0.f, lin = 0.f, l1 = 0.f;
+  float beta = 0.f, lin = 0.f, l1 = 0.f, gap = 0.f;
   // Relaxation parameters of one output row (MODE_SLAB): loaded before the MFMAs of the step
   // that completes the row, so their latency hides behind the matrix work.
   constexpr int NQ = W0 / 4;
@@ -812,6 +840,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
           const float ah = a >= 0.f ? a * lo[j] : a * up[j];
           beta = fmaf(fminf(a, 0.f), bu[j], beta);
           beta = fmaf(ah, bz[j], beta);
+          gap = fmaf(fabsf(a), bu[j], gap);
           s.out[idx] = ah;
         }
       }
@@ -995,6 +1024,8 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
   }
 
   // sum over lane groups and waves, then finish rows q0..q0+15
+  gap += __shfl_xor(gap, 16, 64);
+  gap += __shfl_xor(gap, 32, 64);
   beta += __shfl_xor(beta, 16, 64);
   lin += __shfl_xor(lin, 16, 64);
   l1 += __shfl_xor(l1, 16, 64);
@@ -1003,17 +1034,19 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
   l1 += __shfl_xor(l1, 32, 64);
   __syncthreads();
   if (lane < 16) {
-    red[(wave * 3 + 0) * 16 + lane] = beta;
-    red[(wave * 3 + 1) * 16 + lane] = lin;
-    red[(wave * 3 + 2) * 16 + lane] = l1;
+    red[(wave * 4 + 0) * 16 + lane] = beta;
+    red[(wave * 4 + 1) * 16 + lane] = lin;
+    red[(wave * 4 + 2) * 16 + lane] = l1;
+    red[(wave * 4 + 3) * 16 + lane] = gap;
   }
   __syncthreads();
   if (wave != 0 || lane >= 16 || !qok) return;
   Acc tot{0.f, 0.f, 0.f};
   for (int w = 0; w < NW; ++w) {
-    tot.beta += red[(w * 3 + 0) * 16 + lane];
-    tot.lin += red[(w * 3 + 1) * 16 + lane];
-    tot.l1 += red[(w * 3 + 2) * 16 + lane];
+    tot.beta += red[(w * 4 + 0) * 16 + lane];
+    tot.lin += red[(w * 4 + 1) * 16 + lane];
+    tot.l1 += red[(w * 4 + 2) * 16 + lane];
+    tot.gap += red[(w * 4 + 3) * 16 + lane];
   }
   sink_finish<MODE>(s, tot, q, b, q % (unsigned)s.R, false);
 }
@@ -1071,8 +1104,8 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   __shared__ float tiles[3][TILE];
   __shared__ float rows[2][RB];
   __shared__ float pars[3][PB];
-  __shared__ float red[NS * 16];
-  __shared__ float red_fc[FC ? NM * 16 : 1];
+  __shared__ float red[NS * 16], gred[NS * 16];
+  __shared__ float red_fc[FC ? NM * 16 : 1], gred_fc[FC ? NM * 16 : 1];
 
   const int lane = threadIdx.x & 63, wave = wave_id();
   const unsigned q0 = xcd_tile(blockIdx.x) * 16u;
@@ -1188,7 +1221,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
     int g_lds[TPL];
     bool g_on[TPL];
     float4v g_xa[TPL], g_xb[TPL], g_lo[TPL], g_up[TPL], g_bu[TPL];
-    float fbeta_a = 0.f, fbeta_b = 0.f;
+    float fbeta_a = 0.f, fbeta_b = 0.f, fgap_a = 0.f, fgap_b = 0.f;
     if constexpr (FC) {
       const unsigned nin = CO * H1 * W1, nk = (unsigned)fc.nk;
 #pragma unroll
@@ -1237,6 +1270,10 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
             fbeta_a = fmaf(ha, g_bz[k], fbeta_a);
             fbeta_b = fmaf(fminf(b, 0.f), g_bu[k][e], fbeta_b);
             fbeta_b = fmaf(hb, g_bz[k], fbeta_b);
+            if constexpr (!TAPE) {
+              fgap_a = fmaf(fabsf(a), g_bu[k][e], fgap_a);
+              fgap_b = fmaf(fabsf(b), g_bu[k][e], fgap_b);
+            }
             *reinterpret_cast<float2v*>(buf + g_lds[k] + e * CO * 16) = float2v{ha, hb};
           }
         }
@@ -1336,10 +1373,14 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
       for (int o = 8; o < 64; o <<= 1) {
         fbeta_a += __shfl_xor(fbeta_a, o, 64);
         fbeta_b += __shfl_xor(fbeta_b, o, 64);
+        fgap_a += __shfl_xor(fgap_a, o, 64);
+        fgap_b += __shfl_xor(fgap_b, o, 64);
       }
       if (lane < 8) {
         red_fc[wave * 16 + 2 * lane] = fbeta_a;
         red_fc[wave * 16 + 2 * lane + 1] = fbeta_b;
+        gred_fc[wave * 16 + 2 * lane] = fgap_a;
+        gred_fc[wave * 16 + 2 * lane + 1] = fgap_b;
       }
     }
     lds_barrier();  // the storers' final reduction
@@ -1356,7 +1397,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   // past Q are stored too (never read as results) and the stores need no lane mask.  A store
   // address is a block-uniform row base plus this lane's 32-bit byte offset.
   const unsigned lane_boff = (4u * xg * ldq + qn) * 4u;
-  float beta = 0.f;
+  float beta = 0.f, gap = 0.f;
   auto stage = [&](int e) {
     const int slot = e & 1;
     const float* pst = pars[e % 3];
@@ -1381,6 +1422,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
         const float ah = a[j] * (pos ? lo[j] : up[j]);
         beta = fmaf(pos ? 0.f : a[j], bu[j], beta);
         beta = fmaf(ah, bz[j], beta);
+        if constexpr (!TAPE) gap = fmaf(fabsf(a[j]), bu[j], gap);
         store_row(s.out + base, lane_boff, ah);
       }
     }
@@ -1395,19 +1437,24 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   stage(H1);
   beta += __shfl_xor(beta, 16, 64);
   beta += __shfl_xor(beta, 32, 64);
+  gap += __shfl_xor(gap, 16, 64);
+  gap += __shfl_xor(gap, 32, 64);
   if (lane < 16) red[ws * 16 + lane] = beta;
+  if (lane < 16) gred[ws * 16 + lane] = gap;
   lds_barrier();
   if (ws != 0 || lane >= 16 || !qok) return;
-  float tot = 0.f;
+  float tot = 0.f, tg = 0.f;
   for (int w = 0; w < NS; ++w) tot += red[w * 16 + lane];
+  for (int w = 0; w < NS; ++w) tg += gred[w * 16 + lane];
   if constexpr (FC) {
     // the rows' own bias +-b_k[j] and the terms of the relaxation that built them
     const unsigned r = q % R, nk = (unsigned)fc.nk;
     float fb = r < nk ? fc.b[r] : -fc.b[r - nk];
     for (int w = 0; w < NM; ++w) fb += red_fc[w * 16 + lane];
     tot += fb;
+    for (int w = 0; w < NM; ++w) tg += gred_fc[w * 16 + lane];
   }
-  Acc a{tot, 0.f, 0.f};
+  Acc a{tot, 0.f, 0.f, tg};
   sink_finish<MODE_SLAB>(s, a, q, q / R, q % R, FC);
 }
 
@@ -1452,7 +1499,7 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
   float* tiles = lds;                // 2 x TILE
   float* ring = tiles + 2 * TILE;    // 3 x SLOT
   float* pars = ring + 3 * SLOT;     // 2 x PB
-  float* red = pars + 2 * PB;        // (NS + C0) x 16
+  float* red = pars + 2 * PB;        // (2 NS + C0) x 16
 
   const int lane = threadIdx.x & 63, wave = wave_id();
   const unsigned q0 = xcd_tile(blockIdx.x) * 16u;
@@ -1598,7 +1645,7 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
     const unsigned q = q0 + qn;
     const bool qok = q < Q;
     const int bsel = qok ? (int)(q / R - b0) : 0;
-    float beta = 0.f;
+    float beta = 0.f, gap = 0.f;
     auto stage = [&](int e) {
       float* slot = ring + (e % 3) * SLOT;
       const float* pslot = pars + (e & 1) * PB;
@@ -1623,6 +1670,7 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
           if (qok) {
             beta = fmaf(pos ? 0.f : a, bu[j], beta);
             beta = fmaf(ah, bz[j], beta);
+            gap = fmaf(fabsf(a), bu[j], gap);
           }
           row[x * 16] = ah;
         }
@@ -1635,7 +1683,10 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
     }
     beta += __shfl_xor(beta, 16, 64);
     beta += __shfl_xor(beta, 32, 64);
+    gap += __shfl_xor(gap, 16, 64);
+    gap += __shfl_xor(gap, 32, 64);
     if (lane < 16) red[ws * 16 + lane] = beta;
+    if (lane < 16) red[(NS + C0 + ws) * 16 + lane] = gap;
     lds_barrier();
     return;
   }
@@ -1725,7 +1776,9 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
   float tb = 0.f, ta = 0.f;
   for (int w = 0; w < NS; ++w) tb += red[w * 16 + lane];
   for (int w = 0; w < C0; ++w) ta += red[(NS + w) * 16 + lane];
-  Acc a{tb, 0.f, ta};
+  float tg = 0.f;
+  for (int w = 0; w < NS; ++w) tg += red[(NS + C0 + w) * 16 + lane];
+  Acc a{tb, 0.f, ta, tg};
   sink_finish<MODE_BOUND>(s, a, q, q / R, q % R, false);
 }
 
@@ -1812,7 +1865,8 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   __shared__ float tiles[2][TILE];
   __shared__ float ring[2][SLOT];
   __shared__ float4v pars[2][PSLOT4];
-  __shared__ float red[NM * 16 + 2 * NXW * 16 + (SYM ? (NM + NXW) * 16 : 0)];
+  constexpr bool GAP = SYM || (!FC && SPEC == 0);  // (the slab source: where Sink::gap asks for it)
+  __shared__ float red[NM * 16 + 2 * NXW * 16 + (GAP ? (NM + NXW) * 16 : 0)];
   float* gred = red + NM * 16 + 2 * NXW * 16;  // SYM: the gaps, matrix waves then x waves
   // spec source: the block's rows relaxed onto layer L-1, the MFMA B operand [4 SPEC][16 rows]
   __shared__ float vts[SPEC > 0 ? SPEC * 64 : 1];
@@ -2331,7 +2385,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
         const float ah = a * (a >= 0.f ? p[0] : p[1]);
         beta = fmaf(fminf(a, 0.f), p[2], beta);
         beta = fmaf(ah, p[3], beta);
-        if constexpr (SYM) gap = fmaf(fabsf(a), p[2], gap);
+        if constexpr (GAP) gap = fmaf(fabsf(a), p[2], gap);
         hn[ks] = ah;
       }
     };
@@ -2397,7 +2451,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     red[NM * 16 + XB * 16 + lane] = beta;
     red[NM * 16 + (NXW + XB) * 16 + lane] = l1;
   }
-  if constexpr (SYM) {
+  if constexpr (GAP) {
     gap += __shfl_xor(gap, 16, 64);
     gap += __shfl_xor(gap, 32, 64);
     if (lane < 16) gred[(NM + XB) * 16 + lane] = gap;
@@ -2452,7 +2506,10 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     fc.code[pi] = (int8_t)rx.code;
   } else {
     if (q >= Q || (SPEC > 0 && (int)r >= fc.nspec)) return;
-    Acc a{tb, 0.f, ta};
+    float tg = 0.f;
+    if constexpr (GAP)
+      for (int w = 0; w < NXW; ++w) tg += gred[(NM + w) * 16 + lane];
+    Acc a{tb, 0.f, ta, tg};
     // (spec source: no running bias from an earlier stage)
     sink_finish<MODE_BOUND>(s, a, q, q / R, r, SPEC > 0);
   }
@@ -3561,7 +3618,7 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
                                                   long ldq, long Q, Sink s) {
   extern __shared__ float lds[];
   float* tile = lds;                            // [out_c][32]
-  float* red = lds + (long)t.out_c * 32;        // [NWAVE][3][32]
+  float* red = lds + (long)t.out_c * 32;        // [NWAVE][4][32]
   const int lane = threadIdx.x & 63, wave = wave_id(), nw = blockDim.x >> 6;
   const int n = lane & 31, h = lane >> 5;
   const long q0 = (long)blockIdx.x * 32;
@@ -3646,6 +3703,7 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
             const float ah = a * (a >= 0.f ? p0[g][e] : p1[g][e]);
             sum.beta = fmaf(fminf(a, 0.f), p2[g][e], sum.beta);
             sum.beta = fmaf(ah, p3[g][e], sum.beta);
+            sum.gap = fmaf(fabsf(a), p2[g][e], sum.gap);
             s.out[(long)i * s.ldq + q] = ah;
           } else {
             sum.lin = fmaf(a, p0[g][e], sum.lin);
@@ -5629,7 +5687,8 @@ struct WinLaunch {
   size_t lds = 0;
   int threads = 0;
 };
-bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out) {
+// (sym: one row per neuron, see k_win_pass)
+bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out, bool sym = false) {
   if (k < 2 || k >= net->L || k - 1 >= kWinMax) return false;
   for (int m = 1; m <= k; ++m)
     if (net->T[m - 1].kind != LIRPA_CONV2D) return false;
@@ -5640,7 +5699,8 @@ bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out) {
   d.H = tk.out_h;
   d.W = tk.out_w;
   d.C = tk.out_c;
-  d.G = (tk.out_c + 7) / 8;
+  d.nwin = sym && tk.out_c <= 8 ? 2 : 1;
+  d.G = sym ? (tk.out_c + 15) / 16 : (tk.out_c + 7) / 8;
   d.K = tk.k;
   d.Wk = tk.W;
   d.bk = tk.b;
@@ -5675,9 +5735,9 @@ bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out) {
       l.noff = net->off[m];
       const double ent = (double)w * w * 4 * l.Cq;
       slot[m & 1] = std::max(slot[m & 1], 3 * (ent * 32 + 16));
-      if (o + slot[0] + slot[1] + ent * 16 > kWinLds) return false;
+      if (o + slot[0] + slot[1] + ent * 16 * d.nwin > kWinLds) return false;
       l.o_prm = (int)o;
-      o += ent * 16;
+      o += ent * 16 * d.nwin;
       if (grad) {
         l.o_at = (int)o;
         o += ent * 64;
@@ -5696,17 +5756,18 @@ bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out) {
   d.o_red = (int)o;
   // four waves a block where several blocks share a CU, else eight
   q.threads = o <= 53 * 1024 ? 256 : 512;
-  q.lds = (size_t)o + (q.threads / 64) * 32 * 4 + 128;
+  q.lds = (size_t)o + (q.threads / 64) * 48 * 4 + 128;
   *out = q;
   return true;
 }
 
 // Whether pass k runs k_win_pass: its reverse sweep in a gradient plan (every chain of
-// convolutions but the pass 2 that k_pass2_window_grad takes), its bound (what no specialised
-// window kernel takes).
+// convolutions but the pass 2 that k_pass2_window_grad takes), its bound (sym: with one row per
+// neuron every chain but the pass 2 of k_pass2_window; else what no specialised window kernel
+// takes).
 // (split: Plan::split, here and below)
 bool win_grad_pass(const lirpa_net* net, int k, bool split);
-bool win_bound_pass(const lirpa_net* net, int k, bool split);
+bool win_bound_pass(const lirpa_net* net, int k, bool split, bool sym);
 
 // Whether the final pass of a plain bound takes its last two layers in k_final_fc.
 bool final_fc_covers(const lirpa_net* net) {
@@ -5755,7 +5816,7 @@ bool fc_split_desc(const lirpa_net* net, int m, int kind, bool split, FcLaunch* 
   const FragJob f = frag_job(net, m, kind);
   for (int nt = 4; nt >= 1; nt /= 2) {
     const double plane = (double)f.nks * 4 * nt * 256;
-    const double lds = kind ? plane / 2 : 3 * plane + (kFcThreads / 64) * 3 * 16 * nt * 4;
+    const double lds = kind ? plane / 2 : 3 * plane + (kFcThreads / 64) * 4 * 16 * nt * 4;
     if (lds > kWinLds || (nt > 1 && Q < 16L * nt * 512)) continue;
     *out = FcLaunch{{kind ? t.in_c : t.out_c, kind ? t.out_c : t.in_c, f.nks, f.nmt, (int)plane,
                      nullptr},
@@ -5818,7 +5879,7 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0, bool split =
                     (mode == 1 && pass2_grad_kernel_for(net) != nullptr);
   // passes that keep everything on chip in both directions
   auto onchip = [&](int k) {
-    return (k == 2 && win2) || (mode == 1 ? win_grad_pass(net, k, split) : win_bound_pass(net, k, split));
+    return (k == 2 && win2) || (mode == 1 ? win_grad_pass(net, k, split) : win_bound_pass(net, k, split, false));
   };
   for (int k = 2; k <= L; ++k) {
     long R = (k < L) ? 2 * net->n[k] : S;
@@ -5946,7 +6007,7 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0, bool split =
   for (int k = 2; k < L; ++k) {
     WinLaunch q;
     const bool gw = mode == 1 && win_grad_pass(net, k, split);
-    if (!(gw || win_bound_pass(net, k, split)) || !win_desc(net, k, gw, &q)) continue;
+    if (!(gw || win_bound_pass(net, k, split, true)) || !win_desc(net, k, gw, &q)) continue;
     for (int m = 1; m < k; ++m) {
       if (!p.off_fb[m]) {
         p.off_fb[m] = o;
@@ -6120,7 +6181,7 @@ bool conv_split_desc(const lirpa_layer& t, int m, int dir, SplitLaunch* out) {
   c.rowb = (int)row;
   // four waves a block where several blocks share a CU, else eight
   q.threads = lds <= 53 * 1024 ? 256 : 512;
-  q.lds = (size_t)lds + (q.threads / 64) * 3 * 16 * 4;
+  q.lds = (size_t)lds + (q.threads / 64) * 4 * 16 * 4;
   *out = q;
   return true;
 }
@@ -6157,7 +6218,7 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
       // output tiles in sequence
       const bool wide = nblk32 <= 256;
       const int nwv = wide ? 16 : 8;
-      size_t lds = ((size_t)t.out_c * 32 + (size_t)nwv * 3 * 32) * sizeof(float);
+      size_t lds = ((size_t)t.out_c * 32 + (size_t)nwv * 4 * 32) * sizeof(float);
       return launch_k(tag((std::string("fcT") + sfx).c_str(), m, pass), st, [&] {
         if (wide)
           hipLaunchKernelGGL((k_fcT_mfma<MODE, 16>), dim3(nblk32), dim3(1024), lds, st, t, in,
@@ -6190,7 +6251,7 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
     const unsigned nblk16 = (unsigned)round_up((Q + 15) / 16, 16);
     const size_t cs = (size_t)t.out_w * 16 + (80 - (t.out_w * 16) % 64) % 64;
     // x0 is staged in LDS only when the linear term is not folded into the layer-1 bias
-    size_t lds = (2 * (size_t)t.out_c * cs + (size_t)nw * 3 * 16 +
+    size_t lds = (2 * (size_t)t.out_c * cs + (size_t)nw * 4 * 16 +
                   (MODE == MODE_BOUND && s.x0 ? (size_t)t.in_c * t.in_h * t.in_w : 0)) *
                  sizeof(float);
     return launch_k(tag((std::string("convT") + sfx).c_str(), m, pass), st, [&] {
@@ -6236,9 +6297,16 @@ struct Chunk {
   const float* alpha;
   hipStream_t st;
   bool tape = false;   // record the gradient tape (mode-1 plan)
+  bool sym = false;    // this pass carries one row per neuron (Sink::gap)
   const float* lp = nullptr;  // the parent sub-domains' l, u (chunk's first row) or null
   const float* up = nullptr;
 };
+
+// The running gaps of a pass that carries one row per neuron (Chunk::sym): such a pass uses half
+// of the running biases' array, and the other half holds them.
+float* gap_of(const Chunk& c, long R) {
+  return c.sym ? at<float>(c.ws, c.p->off_beta) + c.nb * R : nullptr;
+}
 
 // Sink that relaxes onto ReLU layer m and stores into `out`.
 Sink slab_sink(const Chunk& c, int m, float* out, long ldq, long R) {
@@ -6256,6 +6324,7 @@ Sink slab_sink(const Chunk& c, int m, float* out, long ldq, long R) {
   s.bias_hw = 1;
   (void)t;
   s.beta = at<float>(c.ws, c.p->off_beta);
+  s.gap = gap_of(c, R);
   s.R = R;
   return s;
 }
@@ -6266,6 +6335,7 @@ Sink bound_sink(const Chunk& c, long R, float* lo, float* hi, long bstride, long
   s.x0 = c.net->L >= 2 ? nullptr : c.x0;
   s.eps = c.eps;
   s.beta = at<float>(c.ws, c.p->off_beta);
+  s.gap = gap_of(c, R);
   s.R = R;
   s.lo = lo;
   s.hi = hi;
@@ -6382,7 +6452,7 @@ ConvT2Kernel convT2_bound_for(const lirpa_net* net, int* nwaves, size_t* lds) {
     const int cs = w1 * 16 + (80 - (w1 * 16) % 64) % 64;
     const int cs1 = 16 * 16 + 16;
     *nwaves = ci + ns + 3;
-    *lds = (size_t)(2 * co * cs + 3 * rsl * ci * cs1 + 2 * 2 * 4 * rsl * ci * 16 + (ns + 3) * 16) *
+    *lds = (size_t)(2 * co * cs + 3 * rsl * ci * cs1 + 2 * 2 * 4 * rsl * ci * 16 + (2 * ns + 3) * 16) *
            sizeof(float);
   };
   // T_2: Conv(8 -> 8, k3, s1, p1), 16x16 -> 16x16.  A stride-2 T_2 (8 -> 16 channels)
@@ -6710,12 +6780,12 @@ bool win_grad_pass(const lirpa_net* net, int k, bool split) {
   return split && !(k == 2 && pass2_grad_kernel_for(net)) && win_desc(net, k, true, &q);
 }
 
-bool win_bound_pass(const lirpa_net* net, int k, bool split) {
+bool win_bound_pass(const lirpa_net* net, int k, bool split, bool sym) {
   int nw = 0;
   if (!split) return false;
   if (k == 2 && pass2_kernel_for(net, &nw)) return false;
-  if (k == 3 && pass3_kernel_for(net)) return false;
-  if (k == 4 && pass4_kernel_for(net)) return false;
+  if (!sym && k == 3 && pass3_kernel_for(net)) return false;
+  if (!sym && k == 4 && pass4_kernel_for(net)) return false;
   WinLaunch q;
   return win_desc(net, k, false, &q);
 }
@@ -6725,9 +6795,11 @@ int win_pass(const Chunk& c, int k, bool grad) {
   const lirpa_net* net = c.net;
   WinLaunch q;
   const bool sp = c.p->split;
-  if (!(grad ? win_grad_pass(net, k, sp) : win_bound_pass(net, k, sp)) ||
-      !win_desc(net, k, grad, &q))
-    return 1;
+  if (!(grad ? win_grad_pass(net, k, sp) : win_bound_pass(net, k, sp, !c.alpha))) return 1;
+  // without given slopes one row per neuron does (where its LDS, with two windows' relaxations,
+  // still fits)
+  const bool sym = !grad && !c.alpha && win_desc(net, k, false, &q, true);
+  if (!sym && !win_desc(net, k, grad, &q)) return 1;
   for (int m = 1; m < k; ++m) {
     q.d.L[m].fb = at<uint4v>(c.ws, c.p->off_fb[m]);
     if (grad) q.d.L[m].ff = at<uint4v>(c.ws, c.p->off_ff[m]);
@@ -6749,16 +6821,12 @@ int win_pass(const Chunk& c, int k, bool grad) {
     a.part = at<float>(c.ws, c.p->off_wpart);
     a.pflag = at<unsigned char>(c.ws, c.p->off_wflag);
   }
-  const void* kern = grad ? reinterpret_cast<const void*>(k_win_pass<true>)
-                          : reinterpret_cast<const void*>(k_win_pass<false>);
-  if (int e = reserve_lds(kern, q.lds)) return e;
-  const unsigned blocks = (unsigned)(c.nb * q.d.G * q.d.H * q.d.W);
+  auto kern = grad ? k_win_pass<true, false> : (sym ? k_win_pass<false, true> : k_win_pass<false, false>);
+  if (int e = reserve_lds(reinterpret_cast<const void*>(kern), q.lds)) return e;
+  const unsigned blocks =
+      (unsigned)(c.nb * q.d.G * q.d.H * ((q.d.W + q.d.nwin - 1) / q.d.nwin));
   if (int e = launch_k(tag(grad ? "win_grad" : "win_bound", 1, k), c.st, [&] {
-        if (grad)
-          hipLaunchKernelGGL(k_win_pass<true>, dim3(blocks), dim3(q.threads), q.lds, c.st, q.d, a);
-        else
-          hipLaunchKernelGGL(k_win_pass<false>, dim3(blocks), dim3(q.threads), q.lds, c.st, q.d,
-                             a);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(q.threads), q.lds, c.st, q.d, a);
       }))
     return e;
   if (!grad) return LIRPA_OK;
@@ -6783,7 +6851,7 @@ bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool split) {
   if (k == 2) return pass2_kernel_for(net, &nw) != nullptr;
   if (k == 4 && pass4_kernel_for(net)) return true;
   if (k == 3 && pass3_kernel_for(net)) return true;
-  if (win_bound_pass(net, k, split)) return true;
+  if (win_bound_pass(net, k, split, false)) return true;
   if (!fc_bound_for(net, k, &nw)) return false;
   // fc_open_ok holds for every chunk of at most Bc sub-domains when it holds for Bc
   Chunk c{};
@@ -6827,7 +6895,11 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    if (k == 4 && (!c.tape || win_grad_pass(net, k, c.p->split))) {
+    // (with one row per neuron k_win_pass is the faster kernel: 1,024 sub-domains of the
+    // four-convolution net, pass 3 3.28 -> 2.31 ms, pass 4 2.58 -> 2.40; with two it is not,
+    // 4.30 and 4.49)
+    const bool symwin = !c.alpha && win_bound_pass(net, k, c.p->split, true);
+    if (k == 4 && !symwin && (!c.tape || win_grad_pass(net, k, c.p->split))) {
       int e = pass4_window(c);
       if (e != 1) {
         if (e) return e;
@@ -6835,7 +6907,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    if (k == 3 && (!c.tape || win_grad_pass(net, k, c.p->split))) {
+    if (k == 3 && !symwin && (!c.tape || win_grad_pass(net, k, c.p->split))) {
       int e = pass3_window(c);
       if (e != 1) {
         if (e) return e;
@@ -6858,6 +6930,16 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
+    // Without given slopes one row per neuron gives both bounds (Sink::gap); 16 rows of a block
+    // still span at most two sub-domains, and the rows of a pair one.
+    Chunk cs = c;
+    cs.sym = !c.tape && !c.alpha && nk % 2 == 0 && nk >= 16;
+    const Chunk& c = cs;  // (hides the chunk of the other passes)
+    if (c.sym) {
+      R = nk;
+      Q = c.nb * R;
+      ldq = round_up(Q, 64);
+    }
     {
       int e = fc_open_stage(c, k, R, Q, ldq);
       if (e != 1) {
@@ -6873,8 +6955,11 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
     s.tape = tape_of(c, k, k - 1);
     const float* wT = c.p->off_wT[k] ? at<float>(c.ws, c.p->off_wT[k]) : nullptr;
     if (int e = launch_k(tag("init_rows", k, k), c.st, [&] {
-          if (wT)
-            hipLaunchKernelGGL(k_init_fc_rows, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0,
+          if (wT && net->n[k - 1] >= 512)
+            hipLaunchKernelGGL(k_init_fc_rows<16>, dim3((unsigned)((Q + 63) / 64)), dim3(1024), 0,
+                               c.st, dlayer(net->T[k - 1]), wT, Q, s);
+          else if (wT)
+            hipLaunchKernelGGL(k_init_fc_rows<4>, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0,
                                c.st, dlayer(net->T[k - 1]), wT, Q, s);
           else
             hipLaunchKernelGGL(k_init_rows<MODE_SLAB>, grid_for(Q), dim3(kBlock), 0, c.st,

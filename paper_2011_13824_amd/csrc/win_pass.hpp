@@ -49,6 +49,7 @@ struct WinDesc {
   int k;            // the pass
   int H, W, C, G;   // h^(k); groups of rows per position
   int K;            // of T_k
+  int nwin;         // windows a block (SYM)
   const float* Wk;
   const float* bk;
   int o_red, o_x;   // LDS: reductions; reverse sweep: signs of A_x, [position][row][quad][4] bytes
@@ -170,7 +171,11 @@ __device__ __forceinline__ void put_split(char* pl, int plane, int o, const floa
 // and r + 8 of a block are +-e_j of channel 8 g + r).  GRAD = true: the reverse sweep of the
 // pass; the rows with weight of a position are numbered in the order (channel, sign) and group
 // g takes rows 16 g .. 16 g + 15; a block without any stops after its flag.
-template <bool GRAD>
+// SYM (bounds without given slopes): one row per neuron gives both bounds (Sink::gap), so the 16
+// rows are 16 channels of a position, or, with 8 channels or fewer, those of two neighbouring
+// positions (nwin = 2: rows 0-7 and 8-15, each in its own window's coordinates; the windows'
+// relaxations stand one behind the other).
+template <bool GRAD, bool SYM>
 __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
   // (kernel arguments are read in place: a by-value struct indexed at run time would be copied
   // to scratch)
@@ -179,15 +184,17 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
   extern __shared__ char wsm[];
   const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = wave_id(), nw = nt >> 6;
   const int n = lane & 15, G = lane >> 4;
+  const int nwin = SYM ? d.nwin : 1, nbx = (d.W + nwin - 1) / nwin;  // blocks along x
+  const int win = SYM && nwin == 2 ? n >> 3 : 0;  // this row's window
   unsigned blk = xcd_range(blockIdx.x);
   const unsigned blk0 = blk;
-  const int px = (int)(blk % (unsigned)d.W); blk /= (unsigned)d.W;
+  const int px = (int)(blk % (unsigned)nbx) * nwin; blk /= (unsigned)nbx;
   const int py = (int)(blk % (unsigned)d.H); blk /= (unsigned)d.H;
   const int g = (int)(blk % (unsigned)d.G); blk /= (unsigned)d.G;
   const long b = blk;
   const int k = d.k;
-  float* red = reinterpret_cast<float*>(wsm + d.o_red);   // [nw][2][16]
-  float* wrow = red + nw * 32;                            // GRAD: [16] row weights
+  float* red = reinterpret_cast<float*>(wsm + d.o_red);   // [nw][3][16]
+  float* wrow = red + nw * 48;                            // GRAD: [16] row weights
   int* rid = reinterpret_cast<int*>(wrow + 16);           // GRAD: [16] 2 channel + (sign -)
 
   if constexpr (GRAD) {
@@ -228,27 +235,30 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
     const int oy = py * d.L[m].S - d.L[m].P, ox = px * d.L[m].S - d.L[m].P;
     float4v* prm = reinterpret_cast<float4v*>(wsm + d.L[m].o_prm);
     const long pb = b * a.pstride + d.L[m].poff, po = d.L[m].poff;
-    for (int e = tid; e < w * w * Cp; e += nt) {
+    const int ent = w * w * Cp;
+    for (int e2 = tid; e2 < nwin * ent; e2 += nt) {
       // (columns fastest: neighbouring threads read neighbouring neurons)
+      const int wi = SYM && e2 >= ent, e = e2 - wi * ent;
       const int xx = e % w, yy = (e / w) % w, c = e / (w * w);
-      const int y = oy + yy, x = ox + xx;
+      const int y = oy + yy, x = ox + xx + wi * d.L[m].S;
       float4v v = {0.f, 0.f, 0.f, 0.f};
       if (c < C && y >= 0 && y < H && x >= 0 && x < W) {
         const long i = ((long)c * H + y) * W + x;
         v = float4v{a.a_lo[pb + i], a.a_up[pb + i], a.b_up[pb + i], a.bias[po + i]};
       }
-      prm[(yy * w + xx) * Cp + c] = v;
+      prm[wi * ent + (yy * w + xx) * Cp + c] = v;
     }
   }
   __syncthreads();
 
   // the rows of W_k, relaxed onto g^(k-1): thread = (row, quad of channels of a position)
-  float beta = 0.f;
+  float beta = 0.f, gap = 0.f;
   {
     const int m = k - 1;
     const int w = d.K, Cq = d.L[m].Cq, C = d.L[m].C, plane = d.L[m].plane;
     char* pl = wsm + d.L[m].o_pl;
-    const float4v* prm = reinterpret_cast<const float4v*>(wsm + d.L[m].o_prm);
+    const float4v* prm =
+        reinterpret_cast<const float4v*>(wsm + d.L[m].o_prm) + win * (w * w * 4 * Cq);
     if (tid < 3) *reinterpret_cast<uint4v*>(pl + (tid + 1) * plane - 16) = uint4v{0, 0, 0, 0};
     const int row = tid & 15;
     int ch;
@@ -256,6 +266,9 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
     if constexpr (GRAD) {
       ch = rid[row] >> 1;
       sgn = (rid[row] & 1) ? -1.f : 1.f;
+    } else if constexpr (SYM) {
+      ch = min(nwin == 2 ? row & 7 : 16 * g + row, d.C - 1);
+      sgn = 1.f;
     } else {
       ch = min(8 * g + (row & 7), d.C - 1);
       sgn = row >= 8 ? -1.f : 1.f;
@@ -274,6 +287,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
         if constexpr (!GRAD) {
           beta = fmaf(fminf(at[r], 0.f), p[2], beta);
           beta = fmaf(v[r], p[3], beta);
+          if constexpr (SYM) gap = fmaf(fabsf(at[r]), p[2], gap);
         }
       }
       put_split(pl, plane, ((pos * 16 + row) * Cq + cq) * 8, v);
@@ -300,7 +314,8 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
       for (int p = 0; p < 3; ++p) B[p] = *reinterpret_cast<const uint4v*>(src + p * plane + o);
     };
     if (m > 1) {
-      const float4v* prm = reinterpret_cast<const float4v*>(wsm + d.L[m - 1].o_prm);
+      const float4v* prm =
+          reinterpret_cast<const float4v*>(wsm + d.L[m - 1].o_prm) + win * (wd * wd * 4 * Cqd);
       char* pl = wsm + d.L[m - 1].o_pl;
       const int pld = d.L[m - 1].plane, oat = d.L[m - 1].o_at;
       if (tid < 3) *reinterpret_cast<uint4v*>(pl + (tid + 1) * pld - 16) = uint4v{0, 0, 0, 0};
@@ -318,6 +333,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
                            if constexpr (!GRAD) {
                              beta = fmaf(fminf(dv[r], 0.f), p[2], beta);
                              beta = fmaf(v[r], p[3], beta);
+                             if constexpr (SYM) gap = fmaf(fabsf(dv[r]), p[2], gap);
                            }
                          }
                          put_split(pl, pld, ((pos * 16 + n) * Cqd + cq) * 8, v);
@@ -327,7 +343,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
                        });
     } else {
       const int H = d.L[0].H, W = d.L[0].W;
-      const int oy = py * d.L[0].S - d.L[0].P, ox = px * d.L[0].S - d.L[0].P;
+      const int oy = py * d.L[0].S - d.L[0].P, ox = (px + win) * d.L[0].S - d.L[0].P;
       unsigned* xs = reinterpret_cast<unsigned*>(wsm + d.o_x);
       win_stage<false>(
           d.L[m].fb, d.L[m].nmt, d.L[m].nks, na, na, wave, nw, load,
@@ -353,29 +369,34 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
 
   if constexpr (!GRAD) {
     // a thread's beta: row tid % 16 in the fill and n in the stages are the same row
-    beta += __shfl_xor(beta, 16, 64);
-    l1 += __shfl_xor(l1, 16, 64);
-    beta += __shfl_xor(beta, 32, 64);
-    l1 += __shfl_xor(l1, 32, 64);
-    if (lane < 16) {
-      red[wave * 32 + lane] = beta;
-      red[wave * 32 + 16 + lane] = l1;
+    float v3[3] = {beta, l1, gap};
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      v3[e] += __shfl_xor(v3[e], 16, 64);
+      v3[e] += __shfl_xor(v3[e], 32, 64);
+      if (lane < 16) red[(wave * 3 + e) * 16 + lane] = v3[e];
     }
     __syncthreads();
     if (tid >= 16) return;
-    const int ch = 8 * g + (tid & 7);
-    if (ch >= d.C) return;
-    float tb = (tid >= 8 ? -1.f : 1.f) * d.bk[ch], ta = 0.f;
+    const bool neg = !SYM && tid >= 8;
+    const int ch = SYM ? (nwin == 2 ? tid & 7 : 16 * g + tid) : 8 * g + (tid & 7);
+    if (ch >= d.C || px + win >= d.W) return;
+    float tb = (neg ? -1.f : 1.f) * d.bk[ch], ta = 0.f, tg = 0.f;
     for (int w = 0; w < nw; ++w) {
-      tb += red[w * 32 + tid];
-      ta += red[w * 32 + 16 + tid];
+      tb += red[(w * 3 + 0) * 16 + tid];
+      ta += red[(w * 3 + 1) * 16 + tid];
+      tg += red[(w * 3 + 2) * 16 + tid];
     }
     const float v = tb - a.eps * ta;
-    const long j = b * a.n_relu + a.noff_k + ((long)ch * d.H + py) * d.W + px;
-    if (tid >= 8)
-      a.hi[j] = -v;
-    else
+    const long j = b * a.n_relu + a.noff_k + ((long)ch * d.H + py) * d.W + px + win;
+    if constexpr (SYM) {
       a.lo[j] = v;
+      a.hi[j] = (tb + tg) + a.eps * ta;
+    } else if (neg) {
+      a.hi[j] = -v;
+    } else {
+      a.lo[j] = v;
+    }
   } else {
     // the witness x0 - eps sign(A_x) forward: G_1 = z1 - eps W_1 sign(A_x), G_m = b_m + W_m z,
     // each G's adjoint terms summed over the 16 rows, z = the row's line applied to G
