@@ -38,7 +38,7 @@ __device__ __forceinline__ void row_park(const RowTask& t, char* slot, int rowb,
 struct ConvSplit {
   int C, Cq, H, W;      // input map of the stage (channels in quads)
   int Cd, Cqd, Hd, Wd;  // output map
-  int K, s, t, pad, nks, nmt, NS, rowb;
+  int K, s, t, ex, pad, nks, nmt, NS, rowb;  // (ex: FragJob; of T^T only)
   const uint4v* frag;
 };
 
@@ -66,7 +66,8 @@ __device__ __forceinline__ float4v conv_dot(const uint4v (&A)[KS ? KS : 1][3], c
 
 constexpr int kRowTasks = 2;  // prefetched tasks a thread
 
-// T_m^T: output (iy, ix) = (s ay + py - pad, s ax + px - pad), inputs (ay - jy, ax - jx).
+// T_m^T: output (iy, ix) = (s ay + py - pad, s ex ax + px - pad), inputs (ay - jy,
+// ex ax + ex - 1 - jx).
 template <int MODE, int KS>
 __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* __restrict__ in,
                                                      unsigned ldq, unsigned Q, Sink s) {
@@ -107,7 +108,8 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
   park(0);
   __syncthreads();
 
-  const int nay = (c.Hd - 1 + c.pad) / c.s + 1, nax = (c.Wd - 1 + c.pad) / c.s + 1;
+  const int sx = c.s * c.ex, tx = c.t + c.ex - 1;
+  const int nay = (c.Hd - 1 + c.pad) / c.s + 1, nax = (c.Wd - 1 + c.pad) / sx + 1;
   // M tiles dealt to the waves; with fewer tiles than waves, nw / nmt waves share a tile's columns
   const int share = nw / c.nmt > 1 ? nw / c.nmt : 1;
   const int mt0 = wave / share, xs0 = wave - mt0 * share, mstep = (nw + share - 1) / share;
@@ -129,10 +131,10 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
         }
       }
       const int qd = mt * 4 + G, ph = qd / c.Cqd, cq = qd - ph * c.Cqd;
-      const int iy = c.s * ay + ph / c.s - c.pad;
-      const bool oky = ph < c.s * c.s && iy >= 0 && iy < c.Hd && qok;
+      const int iy = c.s * ay + ph / sx - c.pad;
+      const bool oky = ph < c.s * sx && iy >= 0 && iy < c.Hd && qok;
       for (int ax = xs0; ax < nax; ax += share) {
-        const int ix = c.s * ax + ph % c.s - c.pad;
+        const int ix = sx * ax + ph % sx - c.pad;
         const bool ok = oky && ix >= 0 && ix < c.Wd;
         unsigned i[4];
         float lo[4], up[4], bu[4], bz[4];
@@ -151,8 +153,8 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
         }
         const float4v d = conv_dot<KS, false>(A, fm, c.nks, [&](int ks, uint4v (&B)[3]) {
           const int ck = ks * 4 + G, j = ck / c2, cc = ck - j * c2;
-          const int jy = j / c.t, yy = ay - jy, xx = ax - (j - jy * c.t);
-          const bool in_ = j < c.t * c.t && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
+          const int jy = j / tx, yy = ay - jy, xx = c.ex * ax + (c.ex - 1) - (j - jy * tx);
+          const bool in_ = j < c.t * tx && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
           int sl = sy - jy;
           sl += sl < 0 ? NS : 0;
           const int o = in_ ? sl * slotb + ((xx * 16 + n) * c2 + cc) * 16 : c.rowb - 16;

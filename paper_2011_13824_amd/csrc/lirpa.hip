@@ -5680,12 +5680,29 @@ long pass2_blocks(const lirpa_net* net, long nb) {
 // (split: k_win_pass may run)
 bool pass_on_chip(const lirpa_net* net, int k, long Bc, bool split);
 
+// Split fragments of layer m (kind 0: T^T, 1: T), shared by k_win_pass and the split stages.
+// The channels below T_m come in eights, those of x and the rows that only feed an epilogue in
+// quads.
+FragJob frag_job(const lirpa_net* net, int m, int kind) {
+  const lirpa_layer& t = net->T[m - 1];
+  const bool fc = t.kind == LIRPA_LINEAR;  // (a 1x1 convolution of a 1x1 map)
+  const int k = fc ? 1 : t.k, st = fc ? 1 : t.stride, tt = (k + st - 1) / st;
+  const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
+  const int cqo = 2 * ((t.out_c + 7) / 8);
+  // (a convolution's T^T of unit stride onto 8 channels or fewer: two columns a position)
+  const int ex = !kind && !fc && st == 1 && cqi <= 2 ? 2 : 1;
+  FragJob f{t.W, t.in_c, t.out_c, k, st, tt, ex, cqi, cqo, kind, 0, 0, 0, nullptr};
+  f.nmt = kind ? (4 * cqo + 15) / 16 : (st * st * ex * 4 * cqi + 15) / 16;
+  f.nks = kind ? (k * k * 4 * cqi + 31) / 32 : (tt * (tt + ex - 1) * 4 * cqo + 31) / 32;
+  return f;
+}
 // k_win_pass for pass k: its windows and LDS layout.  False when a layer up to k is no
 // convolution, or the windows do not fit in LDS.
 struct WinLaunch {
   WinDesc d;
   size_t lds = 0;
   int threads = 0;
+  int ks = 0;  // most K steps of a stage
 };
 // (sym: one row per neuron, see k_win_pass)
 bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out, bool sym = false) {
@@ -5726,11 +5743,13 @@ bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out, bool sym =
       l.K = tm.k;
       l.s = tm.stride;
       l.t = (tm.k + tm.stride - 1) / tm.stride;
-      const int cqi = m - 1 >= 1 ? 2 * ((tm.in_c + 7) / 8) : (tm.in_c + 3) / 4;
-      l.nmt = (l.s * l.s * 4 * cqi + 15) / 16;
-      l.nks = (l.t * l.t * 4 * l.Cq + 31) / 32;
-      l.nmtf = (4 * l.Cq + 15) / 16;
-      l.nksf = (l.K * l.K * 4 * cqi + 31) / 32;
+      const FragJob b = frag_job(net, m, 0), f = frag_job(net, m, 1);
+      l.ex = b.ex;
+      l.nmt = b.nmt;
+      l.nks = b.nks;
+      l.nmtf = f.nmt;
+      l.nksf = f.nks;
+      q.ks = std::max(q.ks, std::max(l.nks, grad ? l.nksf : 0));
       l.poff = net->poff[m];
       l.noff = net->off[m];
       const double ent = (double)w * w * 4 * l.Cq;
@@ -5778,20 +5797,6 @@ bool final_fc_covers(const lirpa_net* net) {
   return ks == 8 || ks == 16 || ks == 25 || ks == 32;
 }
 
-// Split fragments of layer m (kind 0: T^T, 1: T), shared by k_win_pass and the split stages.
-// The channels below T_m come in eights, those of x and the rows that only feed an epilogue in
-// quads.
-FragJob frag_job(const lirpa_net* net, int m, int kind) {
-  const lirpa_layer& t = net->T[m - 1];
-  const bool fc = t.kind == LIRPA_LINEAR;  // (a 1x1 convolution of a 1x1 map)
-  const int k = fc ? 1 : t.k, st = fc ? 1 : t.stride, tt = (k + st - 1) / st;
-  const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
-  const int cqo = 2 * ((t.out_c + 7) / 8);
-  FragJob f{t.W, t.in_c, t.out_c, k, st, tt, cqi, cqo, kind, 0, 0, 0, nullptr};
-  f.nmt = kind ? (4 * cqo + 15) / 16 : (st * st * 4 * cqi + 15) / 16;
-  f.nks = kind ? (k * k * 4 * cqi + 31) / 32 : (tt * tt * 4 * cqo + 31) / 32;
-  return f;
-}
 size_t frag_bytes(const lirpa_net* net, int m, int kind) {
   const FragJob f = frag_job(net, m, kind);
   return (size_t)f.nmt * f.nks * 3072;
@@ -6147,6 +6152,7 @@ bool conv_split_desc(const lirpa_layer& t, int m, int dir, SplitLaunch* out) {
   c.K = t.k;
   c.s = t.stride;
   c.t = (t.k + t.stride - 1) / t.stride;
+  c.ex = 1;
   c.pad = t.pad;
   // channels come in eights, those of x in quads (as in frag_job)
   const int q8i = 2 * ((t.in_c + 7) / 8), q8o = 2 * ((t.out_c + 7) / 8);
@@ -6160,8 +6166,9 @@ bool conv_split_desc(const lirpa_layer& t, int m, int dir, SplitLaunch* out) {
     c.Hd = t.in_h;
     c.Wd = t.in_w;
     c.NS = c.t + 1;
-    c.nmt = (c.s * c.s * 4 * c.Cqd + 15) / 16;
-    c.nks = (c.t * c.t * 4 * c.Cq + 31) / 32;
+    c.ex = c.s == 1 && c.Cqd <= 2 ? 2 : 1;  // (as in frag_job)
+    c.nmt = (c.s * c.s * c.ex * 4 * c.Cqd + 15) / 16;
+    c.nks = (c.t * (c.t + c.ex - 1) * 4 * c.Cq + 31) / 32;
   } else {
     c.C = t.in_c;
     c.Cq = dir == 2 ? (t.in_c + 3) / 4 : q8i;
@@ -6821,7 +6828,15 @@ int win_pass(const Chunk& c, int k, bool grad) {
     a.part = at<float>(c.ws, c.p->off_wpart);
     a.pflag = at<unsigned char>(c.ws, c.p->off_wflag);
   }
-  auto kern = grad ? k_win_pass<true, false> : (sym ? k_win_pass<false, true> : k_win_pass<false, false>);
+  // (the fewer K steps a stage has, the more waves the registers leave a SIMD)
+  auto pick = [&](auto ks) {
+    constexpr int KS = decltype(ks)::value;
+    return grad ? k_win_pass<true, false, KS>
+                : (sym ? k_win_pass<false, true, KS> : k_win_pass<false, false, KS>);
+  };
+  auto kern = q.ks <= 2 ? pick(std::integral_constant<int, 2>())
+                        : (q.ks == 3 ? pick(std::integral_constant<int, 3>())
+                                     : pick(std::integral_constant<int, 4>()));
   if (int e = reserve_lds(reinterpret_cast<const void*>(kern), q.lds)) return e;
   const unsigned blocks =
       (unsigned)(c.nb * q.d.G * q.d.H * ((q.d.W + q.d.nwin - 1) / q.d.nwin));

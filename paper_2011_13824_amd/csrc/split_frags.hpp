@@ -27,12 +27,14 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsign
 // Split weights of one layer in the order of the matrix operand: dst[(mt ks + k) 3 + part][lane],
 // 8 bf16 each, for M tile mt and K step k.  Lane l holds row mt 16 + l % 16, entries
 // 8 (l / 16) .. + 7 of the step's 32.
-//   kind 0, T^T:  row (phase py s + px, input channel ci of 4 Cqi), entry (j = jy t + jx, output
-//                 channel of 4 Cqo);
+//   kind 0, T^T:  row (phase py s ex + px, input channel ci of 4 Cqi), entry (j = jy tx + jx,
+//                 output channel of 4 Cqo); ex = 2 (unit stride, 8 channels or fewer) takes two
+//                 neighbouring output columns as phases, over tx = t + 1 input columns, so that
+//                 the tile's 16 rows are used;
 //   kind 1, T:    row output channel, entry (tap, input channel of 4 Cqi).
 struct FragJob {
   const float* W;  // [out_c][in_c][k][k]
-  int in_c, out_c, k, s, t, Cqi, Cqo, kind, nmt, nks, blk;
+  int in_c, out_c, k, s, t, ex, Cqi, Cqo, kind, nmt, nks, blk;
   uint4v* dst;
 };
 constexpr int kFragJobs = 16;  // in one launch
@@ -51,8 +53,10 @@ __device__ __forceinline__ void frag_entry(const Job& f, int idx) {
     if (f.kind == 0) {
       const int ci = M % (4 * f.Cqi), ph = M / (4 * f.Cqi);
       const int co = kk % (4 * f.Cqo), j = kk / (4 * f.Cqo);
-      const int ky = ph / f.s + f.s * (j / f.t), kx = ph % f.s + f.s * (j % f.t);
-      if (ph < f.s * f.s && j < f.t * f.t && ci < f.in_c && co < f.out_c && ky < f.k && kx < f.k)
+      const int sx = f.s * f.ex, tx = f.t + f.ex - 1;
+      const int ky = ph / sx + f.s * (j / tx), kx = ph % sx + f.s * (j % tx - (f.ex - 1));
+      if (ph < f.s * sx && j < f.t * tx && ci < f.in_c && co < f.out_c && ky < f.k && kx >= 0 &&
+          kx < f.k)
         v[e] = f.W[(((long)co * f.in_c + ci) * f.k + ky) * f.k + kx];
     } else {
       const int ci = kk % (4 * f.Cqi), tap = kk / (4 * f.Cqi);

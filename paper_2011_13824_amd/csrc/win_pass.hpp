@@ -35,6 +35,7 @@ struct WinLayer {
   int C;
   int S, P;         // window origin y S - P
   int K, s, t;      // of T_m
+  int ex;           // output columns a T_m^T position takes per phase (FragJob)
   int nks, nmt;     // T_m^T fragments
   const uint4v* fb;
   int nksf, nmtf;   // T_m fragments
@@ -145,15 +146,22 @@ __device__ __forceinline__ void win_tiles_any(const uint4v* __restrict__ frag, i
   }
 }
 
-template <bool SIGN, class Load, class Emit>
+// (MAXKS: the most K steps whose fragments the kernel's registers hold)
+template <int MAXKS, bool SIGN, class Load, class Emit>
 __device__ __forceinline__ void win_stage(const uint4v* __restrict__ frag, int nmt, int nks, int ny,
                                           int nx, int wave, int nw, Load load, Emit emit) {
   switch (nks) {
     case 1: return win_tiles<1, SIGN>(frag, nmt, ny, nx, wave, nw, load, emit);
     case 2: return win_tiles<2, SIGN>(frag, nmt, ny, nx, wave, nw, load, emit);
-    case 3: return win_tiles<3, SIGN>(frag, nmt, ny, nx, wave, nw, load, emit);
-    case 4: return win_tiles<4, SIGN>(frag, nmt, ny, nx, wave, nw, load, emit);
-    default: return win_tiles_any<SIGN>(frag, nmt, nks, ny, nx, wave, nw, load, emit);
+    case 3:
+      if constexpr (MAXKS >= 3) return win_tiles<3, SIGN>(frag, nmt, ny, nx, wave, nw, load, emit);
+      break;
+    case 4:
+      if constexpr (MAXKS >= 4) return win_tiles<4, SIGN>(frag, nmt, ny, nx, wave, nw, load, emit);
+      break;
+    default:
+      if constexpr (MAXKS >= 4)
+        return win_tiles_any<SIGN>(frag, nmt, nks, ny, nx, wave, nw, load, emit);
   }
 }
 
@@ -175,7 +183,7 @@ __device__ __forceinline__ void put_split(char* pl, int plane, int o, const floa
 // rows are 16 channels of a position, or, with 8 channels or fewer, those of two neighbouring
 // positions (nwin = 2: rows 0-7 and 8-15, each in its own window's coordinates; the windows'
 // relaxations stand one behind the other).
-template <bool GRAD, bool SYM>
+template <bool GRAD, bool SYM, int MAXKS>
 __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
   // (kernel arguments are read in place: a by-value struct indexed at run time would be copied
   // to scratch)
@@ -302,13 +310,15 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
   for (int m = k - 1; m >= 1; --m) {
     const int w = d.L[m].w, s = d.L[m].s, t = d.L[m].t, Cq = d.L[m].Cq, plane = d.L[m].plane;
     const char* src = wsm + d.L[m].o_pl;
-    const int wd = d.L[m - 1].w, Cqd = d.L[m - 1].Cq, na = w + t - 1;
+    const int wd = d.L[m - 1].w, Cqd = d.L[m - 1].Cq;
+    const int ex = d.L[m].ex, sx = s * ex, tx = t + ex - 1;
+    const int na = w + t - 1, nax = (na + ex - 1) / ex;
     const int c2 = Cq / 2;  // 16-byte chunks per (position, row)
     // this lane's chunk of K step ks: tap pair (jy, jx), 8 output channels
     auto load = [&](int ks, int y, int x, uint4v (&B)[3]) {
       const int ck = ks * 4 + G, j = ck / c2, cc = ck - j * c2;
-      const int yy = y - j / t, xx = x - j % t;
-      const bool ok = j < t * t && yy >= 0 && yy < w && xx >= 0 && xx < w;
+      const int yy = y - j / tx, xx = ex * x + (ex - 1) - j % tx;
+      const bool ok = j < t * tx && yy >= 0 && yy < w && xx >= 0 && xx < w;
       const int o = ok ? (((yy * w + xx) * 16 + n) * c2 + cc) * 16 : plane - 16;
 #pragma unroll
       for (int p = 0; p < 3; ++p) B[p] = *reinterpret_cast<const uint4v*>(src + p * plane + o);
@@ -319,11 +329,11 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
       char* pl = wsm + d.L[m - 1].o_pl;
       const int pld = d.L[m - 1].plane, oat = d.L[m - 1].o_at;
       if (tid < 3) *reinterpret_cast<uint4v*>(pl + (tid + 1) * pld - 16) = uint4v{0, 0, 0, 0};
-      win_stage<false>(d.L[m].fb, d.L[m].nmt, d.L[m].nks, na, na, wave, nw, load,
+      win_stage<MAXKS, false>(d.L[m].fb, d.L[m].nmt, d.L[m].nks, na, nax, wave, nw, load,
                        [&](int mt, int y, int x, const float4v& dv) {
                          const int qd = mt * 4 + G, ph = qd / Cqd, cq = qd - ph * Cqd;
-                         const int iy = s * y + ph / s, ix = s * x + ph % s;
-                         if (ph >= s * s || iy >= wd || ix >= wd) return;
+                         const int iy = s * y + ph / sx, ix = sx * x + ph % sx;
+                         if (ph >= s * sx || iy >= wd || ix >= wd) return;
                          const int pos = iy * wd + ix;
                          float4v v;
 #pragma unroll
@@ -345,12 +355,12 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
       const int H = d.L[0].H, W = d.L[0].W;
       const int oy = py * d.L[0].S - d.L[0].P, ox = (px + win) * d.L[0].S - d.L[0].P;
       unsigned* xs = reinterpret_cast<unsigned*>(wsm + d.o_x);
-      win_stage<false>(
-          d.L[m].fb, d.L[m].nmt, d.L[m].nks, na, na, wave, nw, load,
+      win_stage<MAXKS, false>(
+          d.L[m].fb, d.L[m].nmt, d.L[m].nks, na, nax, wave, nw, load,
           [&](int mt, int y, int x, const float4v& dv) {
             const int qd = mt * 4 + G, ph = qd / Cqd, cq = qd - ph * Cqd;
-            const int iy = s * y + ph / s, ix = s * x + ph % s;
-            if (ph >= s * s || iy >= wd || ix >= wd) return;
+            const int iy = s * y + ph / sx, ix = sx * x + ph % sx;
+            if (ph >= s * sx || iy >= wd || ix >= wd) return;
             const bool in = oy + iy >= 0 && oy + iy < H && ox + ix >= 0 && ox + ix < W;
             if constexpr (GRAD) {
               // sign in the high byte of a bf16 +-2 (0x40, 0xc0)
@@ -457,7 +467,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
       (void)C;
       if (m == 1) {
         const unsigned* xs = reinterpret_cast<const unsigned*>(wsm + d.o_x);
-        win_stage<true>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, w, wave, nw,
+        win_stage<MAXKS, true>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, w, wave, nw,
                         [&](int ks, int y, int x, uint4v (&B)[3]) {
                           uint4v v;
 #pragma unroll
@@ -478,7 +488,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
       } else {
         const char* src = wsm + d.L[m - 1].o_pl;
         const int plane = d.L[m - 1].plane, c2 = Cqb / 2;
-        win_stage<false>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, w, wave, nw,
+        win_stage<MAXKS, false>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, w, wave, nw,
                          [&](int ks, int y, int x, uint4v (&B)[3]) {
                            const int ck = ks * 4 + G, tap = min(ck / c2, K * K - 1), cc = ck % c2;
                            const int iy = y * s + tap / K, ix = x * s + tap % K;
