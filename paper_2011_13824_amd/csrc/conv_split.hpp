@@ -6,6 +6,11 @@
 // [slot][part][x][row][channel], channels padded to eight; the next step's are loaded into
 // registers before the step's matrix work and parked after it, one barrier a step.  Each wave
 // keeps the fragments of its M tile in registers as long as the tile does not change.
+// What bounds them: the epilogue's loads and stores, four bytes a lane (rows of 16 are half a
+// line), more than the matrix work.  Measured, 255 sub-domains of a 28x28 1-16-32-channel net
+// with two rows per neuron: T_2^T of pass 3 70 ms per lane, 0.62 here (41 GFLOP), T_1^T 7.4 and
+// 0.44.  Witness forward of the four-convolution net's pass 5 (12,800 rows, 8 channels): 0.275 ms
+// a layer with the fp32 kernel of those shapes, 0.18 here with two columns a tile.
 
 // Input row loader: task = (column x, quad of channels, quad of rows q): four 16-byte loads,
 // transposed into four 8-byte stores per part.
@@ -38,7 +43,7 @@ __device__ __forceinline__ void row_park(const RowTask& t, char* slot, int rowb,
 struct ConvSplit {
   int C, Cq, H, W;      // input map of the stage (channels in quads)
   int Cd, Cqd, Hd, Wd;  // output map
-  int K, s, t, ex, pad, nks, nmt, NS, rowb;  // (ex: FragJob; of T^T only)
+  int K, s, t, ex, pad, nks, nmt, NS, rowb;  // (ex: FragJob)
   const uint4v* frag;
 };
 
@@ -328,8 +333,11 @@ __global__ void __launch_bounds__(512)
             for (int p = 0; p < 3; ++p) A[k][p] = fm[(k * 3 + p) * 64];
         }
       }
-      const int cq = mt * 4 + G;
-      for (int ox = xs0; ox < c.Wd; ox += share) {
+      const int qd = mt * 4 + G, ph = qd / c.Cqd, cq = qd - ph * c.Cqd;
+      const int kw = c.K + c.s * (c.ex - 1), nbx = (c.Wd + c.ex - 1) / c.ex;
+      for (int bx = xs0; bx < nbx; bx += share) {
+        const int ox = c.ex * bx + ph;
+        const bool okx = ph < c.ex && ox < c.Wd;  // (the same for the lanes a sum runs over)
         float lo[4], up[4], bu[4], bz[4], tp[4];
         unsigned i[4];
 #pragma unroll
@@ -337,7 +345,7 @@ __global__ void __launch_bounds__(512)
           const int co = 4 * cq + r;
           i[r] = ((unsigned)co * c.Hd + oy) * c.Wd + ox;
           lo[r] = up[r] = bu[r] = bz[r] = tp[r] = 0.f;
-          if (co < c.Cd && qok) {
+          if (co < c.Cd && qok && okx) {
             bz[r] = bias[i[r]];
             if (fz) tp[r] = tape[(size_t)i[r] * ldq + q];
             if (fz && zout) {
@@ -353,9 +361,9 @@ __global__ void __launch_bounds__(512)
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
               const int qi = (ks * 4 + G) * 2 + h, tap = qi / c.Cq, cc = qi - tap * c.Cq;
-              const int ky = tap / c.K, yy = oy * c.s - c.pad + ky;
-              const int xx = ox * c.s - c.pad + tap - ky * c.K;
-              const bool in_ = tap < c.K * c.K && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
+              const int ky = tap / kw, yy = oy * c.s - c.pad + ky;
+              const int xx = c.ex * bx * c.s - c.pad + tap - ky * kw;
+              const bool in_ = tap < c.K * kw && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
               const int o = in_ ? (yy % NS) * slotb + ((xx * 16 + n) * c.Cq + cc) * 4 : 0;
               const unsigned u = in_ ? *reinterpret_cast<const unsigned*>(csm + o) : 0u;
               v[2 * h] = __builtin_amdgcn_perm(u, 0u, 0x05000400u);
@@ -366,9 +374,9 @@ __global__ void __launch_bounds__(512)
             B[2] = v;
           } else {
             const int ck = ks * 4 + G, tap = ck / c2, cc = ck - tap * c2;
-            const int ky = tap / c.K, yy = oy * c.s - c.pad + ky;
-            const int xx = ox * c.s - c.pad + tap - ky * c.K;
-            const bool in_ = tap < c.K * c.K && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
+            const int ky = tap / kw, yy = oy * c.s - c.pad + ky;
+            const int xx = c.ex * bx * c.s - c.pad + tap - ky * kw;
+            const bool in_ = tap < c.K * kw && yy >= 0 && yy < c.H && xx >= 0 && xx < c.W;
             const int o = in_ ? (yy % NS) * slotb + ((xx * 16 + n) * c2 + cc) * 16 : c.rowb - 16;
 #pragma unroll
             for (int p = 0; p < 3; ++p)
@@ -388,7 +396,7 @@ __global__ void __launch_bounds__(512)
             da[r] = sum8(fz ? (wq * tneg) * gv[r] : 0.f);
             db[r] = sum8(fz ? wq * tneg : 0.f);
           }
-          if ((n & 7) == 0 && 4 * cq < c.Cd) {
+          if ((n & 7) == 0 && 4 * cq < c.Cd && okx) {
             float* dst = part + (size_t)(q0 / 8 + (n >> 3)) * 3 * (npos * c.Cd) +
                          (size_t)(oy * c.Wd + ox) * c.Cd + 4 * cq;
             *reinterpret_cast<float4v*>(dst) = sa;
@@ -396,7 +404,7 @@ __global__ void __launch_bounds__(512)
             *reinterpret_cast<float4v*>(dst + 2 * npos * c.Cd) = db;
           }
         }
-        if (!qok || wq == 0.f) continue;
+        if (!qok || wq == 0.f || !okx) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           if (4 * cq + r >= c.Cd) continue;

@@ -5,7 +5,9 @@
 // ([chunk of 8 inputs][row], 16 bytes a part), and the waves take two tiles of 16 outputs at a
 // time, streaming the weight fragments from the cache one K step ahead.  Two output tiles per
 // operand read keep the LDS at half its rate; NT = 4 row tiles per fragment read keep the cache
-// at a quarter of its own.
+// at a quarter of its own.  Measured on a 784-256 layer and 102,400 rows (41 GFLOP): T^T with its
+// sign tape 1.03 ms with the fp32 kernel, 0.31 here (the byte stores of the tape bound it);
+// witness forward 2.61 and 0.26.
 
 constexpr int kFcThreads = 512;
 

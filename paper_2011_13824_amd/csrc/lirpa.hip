@@ -5689,11 +5689,13 @@ FragJob frag_job(const lirpa_net* net, int m, int kind) {
   const int k = fc ? 1 : t.k, st = fc ? 1 : t.stride, tt = (k + st - 1) / st;
   const int cqi = m > 1 ? 2 * ((t.in_c + 7) / 8) : (t.in_c + 3) / 4;
   const int cqo = 2 * ((t.out_c + 7) / 8);
-  // (a convolution's T^T of unit stride onto 8 channels or fewer: two columns a position)
-  const int ex = !kind && !fc && st == 1 && cqi <= 2 ? 2 : 1;
+  // (a convolution's T^T of unit stride onto 8 channels or fewer takes two columns a position,
+  // a T of 8 output channels or fewer the same)
+  const int ex = !fc && (kind ? cqo <= 2 : st == 1 && cqi <= 2) ? 2 : 1;
   FragJob f{t.W, t.in_c, t.out_c, k, st, tt, ex, cqi, cqo, kind, 0, 0, 0, nullptr};
-  f.nmt = kind ? (4 * cqo + 15) / 16 : (st * st * ex * 4 * cqi + 15) / 16;
-  f.nks = kind ? (k * k * 4 * cqi + 31) / 32 : (tt * (tt + ex - 1) * 4 * cqo + 31) / 32;
+  f.nmt = kind ? (ex * 4 * cqo + 15) / 16 : (st * st * ex * 4 * cqi + 15) / 16;
+  f.nks = kind ? (k * (k + st * (ex - 1)) * 4 * cqi + 31) / 32
+               : (tt * (tt + ex - 1) * 4 * cqo + 31) / 32;
   return f;
 }
 // k_win_pass for pass k: its windows and LDS layout.  False when a layer up to k is no
@@ -5745,6 +5747,7 @@ bool win_desc(const lirpa_net* net, int k, bool grad, WinLaunch* out, bool sym =
       l.t = (tm.k + tm.stride - 1) / tm.stride;
       const FragJob b = frag_job(net, m, 0), f = frag_job(net, m, 1);
       l.ex = b.ex;
+      l.exf = f.ex;
       l.nmt = b.nmt;
       l.nks = b.nks;
       l.nmtf = f.nmt;
@@ -6175,12 +6178,14 @@ bool conv_split_desc(const lirpa_layer& t, int m, int dir, SplitLaunch* out) {
     c.H = t.in_h;
     c.W = t.in_w;
     c.Cd = t.out_c;
-    c.Cqd = (t.out_c + 3) / 4;
     c.Hd = t.out_h;
     c.Wd = t.out_w;
     c.NS = c.K + c.s;
-    c.nmt = (4 * c.Cqd + 15) / 16;
-    c.nks = (c.K * c.K * 4 * c.Cq + 31) / 32;
+    const int cqo = 2 * ((t.out_c + 7) / 8);
+    c.ex = cqo <= 2 ? 2 : 1;  // (as in frag_job)
+    c.Cqd = cqo;
+    c.nmt = (c.ex * 4 * cqo + 15) / 16;
+    c.nks = (c.K * (c.K + c.s * (c.ex - 1)) * 4 * c.Cq + 31) / 32;
   }
   const double row = (double)c.W * 16 * c.Cq * (dir == 2 ? 4 : 8) + (dir == 2 ? 0 : 16);
   const double lds = row * (dir == 2 ? 1 : 3) * c.NS;
@@ -6766,7 +6771,10 @@ Pass4Kernel pass4_kernel_for(const lirpa_net* net) {
 }
 
 // Whether layer m's stages run the split kernels: convolutions without a kernel of their own
-// whose ring fits in LDS.
+// whose ring fits in LDS; and every witness forward onto 8 channels or fewer, where k_fwd_conv
+// leaves half of its matrix tile empty (12,800 rows of the four-convolution net's pass 5, layers
+// 1 to 3: 0.270, 0.278, 0.279 ms with it, 0.188, 0.179, 0.181 split; with 16 channels and more it
+// is the faster one, 18,400 rows 0.21 against 0.24 ms).
 bool split_back(const lirpa_net* net, int m, bool split) {
   const lirpa_layer& t = net->T[m - 1];
   int nw = 0;
@@ -6778,7 +6786,7 @@ bool split_back(const lirpa_net* net, int m, bool split) {
 bool split_fwd(const lirpa_net* net, int m, bool split) {
   const lirpa_layer& t = net->T[m - 1];
   SplitLaunch q;
-  return split && t.kind == LIRPA_CONV2D && !fwd_conv_for(t, true, false) &&
+  return split && t.kind == LIRPA_CONV2D && (t.out_c <= 8 || !fwd_conv_for(t, true, false)) &&
          conv_split_desc(t, m, m == 1 ? 2 : 1, &q);
 }
 
@@ -6846,8 +6854,6 @@ int win_pass(const Chunk& c, int k, bool grad) {
     return e;
   if (!grad) return LIRPA_OK;
   for (int m = k - 1; m >= 1; --m) {
-    const long off = net->off[m];
-    (void)off;
     if (int e = launch_k(tag("win_gather", m, k), c.st, [&] {
           hipLaunchKernelGGL(k_win_gather, grid_for(c.nb * net->n[m]), dim3(kBlock), 0, c.st,
                              c.nb, q.d.L[m], m, q.d.H, q.d.W, q.d.G, q.d.npart, a.part, a.pflag,
@@ -7312,15 +7318,15 @@ int grad_chunk(const Chunk& c, int full) {
       const unsigned nblk16 = (unsigned)round_up((Q + 15) / 16, 16);
       FwdKernel fk = fwd_conv_for(net->T[m - 1], m == 1, zout != nullptr);
       // fused adjoint sums (groups of 8 rows aligned to the sub-domains) where R allows it
+      // an FC-opened pass recorded no tape over its first stage's input: rebuild it from W_P
+      const bool wtape = m == P - 1 && fc_open_ok(c, P, R);
       SplitLaunch sq;
-      const bool fsplit = !fk && split_fwd(net, m, p.split) &&
+      const bool fsplit = !wtape && split_fwd(net, m, p.split) &&
                           conv_split_desc(net->T[m - 1], m, m == 1 ? 2 : 1, &sq);
       FcLaunch fs;
       const bool fsign = m == 1 && fc_split_desc(net, 1, 1, p.split, &fs, Q);
       const bool fused = (fk || ((fsplit || fsign) && t.out_c % 4 == 0)) && P < L && R % 8 == 0 &&
                          p.off_gpart != 0;
-      // an FC-opened pass recorded no tape over its first stage's input: rebuild it from W_P
-      const bool wtape = m == P - 1 && fc_open_ok(c, P, R);
       const float* tapeW = wtape ? net->T[P - 1].W : nullptr;
       const int tnk = wtape ? (int)net->n[P] : 0;
       float* gpart = fused ? at<float>(c.ws, p.off_gpart) : nullptr;
@@ -7721,16 +7727,19 @@ int optimize_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float 
 int bound_ul_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float eps,
                  const float* C, int S, int B, const int8_t* split, const float* alpha, float* lb,
                  float* ub, float* l_out, float* u_out, int8_t* code_out, void* ws,
-                 hipStream_t stream) {
+                 hipStream_t stream, bool ready = false) {
   const long nL = net->n[net->L];
   float* C2 = at<float>(ws, p.off_spec);
-  if (int e = launch_k("spec_pm", stream, [&] {
-        hipLaunchKernelGGL(k_spec_pm, grid_for((long)S * nL), dim3(kBlock), 0, stream,
-                           (long)S * nL, C, C2, 1);
-      }))
-    return e;
   // the intermediate passes are shared; the final pass bounds the 2S rows [C; -C]
-  if (int e = layer1_bounds(net, p, ws, x0, eps, C2, 2 * S, stream)) return e;
+  // (ready: an earlier call with this plan, workspace, net, x0, eps and C has done this part)
+  if (!ready) {
+    if (int e = launch_k("spec_pm", stream, [&] {
+          hipLaunchKernelGGL(k_spec_pm, grid_for((long)S * nL), dim3(kBlock), 0, stream,
+                             (long)S * nL, C, C2, 1);
+        }))
+      return e;
+    if (int e = layer1_bounds(net, p, ws, x0, eps, C2, 2 * S, stream)) return e;
+  }
   float* lb2 = at<float>(ws, p.off_lb2);
   for (long b0 = 0; b0 < B; b0 += Bc) {
     Chunk c = make_chunk(net, p, ws, x0, eps, 2 * S, B, b0, split, alpha, l_out, u_out, stream);
@@ -7821,7 +7830,7 @@ int check_bab_params(const lirpa_bab_params& bp) {
 // optimises the slopes from where they are (fresh: from the heuristic start) first.
 int bab_bound_children(lirpa_net* net, const BabPlan& q, void* ws, const float* x0, float eps,
                        const float* c, long nb, int steps, bool fresh,
-                       const lirpa_bab_params& bp, hipStream_t st) {
+                       const lirpa_bab_params& bp, bool* ready, hipStream_t st) {
   void* inner = at<char>(ws, q.inner);
   int8_t* mask = at<int8_t>(ws, q.cmask);
   float* alpha = q.alpha ? at<float>(ws, q.calpha) : nullptr;
@@ -7843,14 +7852,18 @@ int bab_bound_children(lirpa_net* net, const BabPlan& q, void* ws, const float* 
       return e;
   }
   // the upper bound (and l, u, codes) at the slopes the lower side ended with
+  // (a plan for every batch of the search: without optimised slopes nothing else writes the inner
+  // workspace, and what depends on the net, the box and the property alone is set up once)
   Plan p;
-  const long Bc = fit_chunk(net, 1, nb, q.inner_bytes, &p, 2);
+  const long Bc = fit_chunk(net, 1, q.nc, q.inner_bytes, &p, 2);
   if (Bc < 1) return fail(LIRPA_ENOMEM, "branch and bound: inner workspace too small");
   const bool opt = q.alpha && (steps > 0 || fresh);
+  const bool was_ready = *ready;
+  *ready = !q.alpha;
   if (int e = bound_ul_run(net, p, Bc, x0, eps, c, 1, (int)nb, mask, alpha,
                            opt ? at<float>(ws, q.clbu) : lo, at<float>(ws, q.chi),
                            at<float>(ws, q.cl), at<float>(ws, q.cu), at<int8_t>(ws, q.ccode),
-                           inner, st))
+                           inner, st, was_ready))
     return e;
   return launch_k("bab_branch", st, [&] {
     hipLaunchKernelGGL(k_bab_branch, dim3((unsigned)nb), dim3(kBlock), 0, st, net->n_relu,
@@ -7912,7 +7925,8 @@ int bab_run(lirpa_net* net, const BabPlan& q, const float* x0, float eps, const 
                            at<BabSummary>(ws, q.sum));
       }))
     return e;
-  if (int e = bab_bound_children(net, q, ws, x0, eps, c, 1, bp.root_steps, true, bp, st))
+  bool ready = false;
+  if (int e = bab_bound_children(net, q, ws, x0, eps, c, 1, bp.root_steps, true, bp, &ready, st))
     return e;
   int cur = 0;
   long N = 0;
@@ -7960,7 +7974,7 @@ int bab_run(lirpa_net* net, const BabPlan& q, const float* x0, float eps, const 
         return e;
     cur = 1 - cur;
     // line 7: (optimised) LiRPA on the 2k children, from their parents' slopes
-    if (int e = bab_bound_children(net, q, ws, x0, eps, c, 2 * k, bp.steps, false, bp, st))
+    if (int e = bab_bound_children(net, q, ws, x0, eps, c, 2 * k, bp.steps, false, bp, &ready, st))
       return e;
     res->domains_bounded += 2 * k;
     // lines 8-10

@@ -31,7 +31,9 @@ __device__ __forceinline__ void split_pair(float a, float b, unsigned& h, unsign
 //                 output channel of 4 Cqo); ex = 2 (unit stride, 8 channels or fewer) takes two
 //                 neighbouring output columns as phases, over tx = t + 1 input columns, so that
 //                 the tile's 16 rows are used;
-//   kind 1, T:    row output channel, entry (tap, input channel of 4 Cqi).
+//   kind 1, T:    row (column phase p, output channel of 4 Cqo), entry (tap ky kw + kx, input
+//                 channel of 4 Cqi), kw = k + s (ex - 1); ex = 2 (8 channels or fewer) takes two
+//                 neighbouring output columns, the second at the taps from kx = s on.
 struct FragJob {
   const float* W;  // [out_c][in_c][k][k]
   int in_c, out_c, k, s, t, ex, Cqi, Cqo, kind, nmt, nks, blk;
@@ -59,9 +61,11 @@ __device__ __forceinline__ void frag_entry(const Job& f, int idx) {
           kx < f.k)
         v[e] = f.W[(((long)co * f.in_c + ci) * f.k + ky) * f.k + kx];
     } else {
-      const int ci = kk % (4 * f.Cqi), tap = kk / (4 * f.Cqi);
-      if (M < f.out_c && tap < f.k * f.k && ci < f.in_c)
-        v[e] = f.W[((long)M * f.in_c + ci) * f.k * f.k + tap];
+      const int ci = kk % (4 * f.Cqi), tap = kk / (4 * f.Cqi), kw = f.k + f.s * (f.ex - 1);
+      const int co = M % (4 * f.Cqo), p = M / (4 * f.Cqo);
+      const int ky = tap / kw, kx = tap % kw - f.s * p;
+      if (co < f.out_c && p < f.ex && ky < f.k && kx >= 0 && kx < f.k && ci < f.in_c)
+        v[e] = f.W[(((long)co * f.in_c + ci) * f.k + ky) * f.k + kx];
     }
   }
   uint4v h, m, l;

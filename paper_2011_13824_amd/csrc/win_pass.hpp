@@ -19,6 +19,13 @@
 // ky = p + s j of the inputs a - j, j < t = ceil(K / s), for every phase p < s alike.  So one
 // GEMM per block position a serves all s^2 phases: M = (phase, input channel of T_m),
 // K = (tap pair j, output channel), N = the 16 rows.
+//
+// What bounds it: instructions, the relaxation and split of every window entry and the operand
+// addresses before the matrix work (a block of the four-convolution net's pass 3 issues about
+// 1,700 per wave beside 120 matrix instructions; more positions in flight change nothing).
+// Measured (ms, before and after): 64 sub-domains of the four-convolution net, ten reverse sweeps
+// of passes 3 and 4 with their bounds, dense slabs 209, here 12.2; 255 sub-domains of a 28x28
+// 1-16-32-channel net, pass 2, per-lane gathers 57, here 0.26.
 
 constexpr int kWinMax = 6;   // most layers below the pass's own
 constexpr int kWinLds = 160 * 1024;
@@ -35,7 +42,7 @@ struct WinLayer {
   int C;
   int S, P;         // window origin y S - P
   int K, s, t;      // of T_m
-  int ex;           // output columns a T_m^T position takes per phase (FragJob)
+  int ex, exf;      // output columns a position of T_m^T, T_m takes (FragJob)
   int nks, nmt;     // T_m^T fragments
   const uint4v* fb;
   int nksf, nmtf;   // T_m fragments
@@ -66,7 +73,6 @@ struct WinArgs {
   float eps;
   float* lo;        // bounds of the chunk (whole rows of n_relu)
   float* hi;
-  const int8_t* code;
   const float* gl;  // adjoints of the bounds (whole rows)
   const float* gu;
   float* part;
@@ -412,7 +418,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
     // each G's adjoint terms summed over the 16 rows, z = the row's line applied to G
     const float wn = wrow[n];
     for (int m = 1; m < k; ++m) {
-      const int w = d.L[m].w, s = d.L[m].s, K = d.L[m].K, Cq = d.L[m].Cq, C = d.L[m].C;
+      const int w = d.L[m].w, s = d.L[m].s, K = d.L[m].K, Cq = d.L[m].Cq;
       const int wb = d.L[m - 1].w, Cqb = d.L[m - 1].Cq;
       const int H = d.L[m].H, W = d.L[m].W;
       const int oy = py * d.L[m].S - d.L[m].P, ox = px * d.L[m].S - d.L[m].P;
@@ -422,12 +428,13 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
       const float* atb = reinterpret_cast<const float*>(wsm + d.L[m].o_at);
       const float gs = m == 1 ? -0.5f * a.eps : 1.f;  // (the signs are stored as +-2)
       float* out = a.part + (long)blk0 * d.npart + d.L[m].part;
-      const int8_t* cd = a.code + b * a.n_relu + d.L[m].noff;
-      auto emit = [&](int mt, int y, int x, const float4v& dv) {
-        const int cq = mt * 4 + G;
-        const int yy = oy + y, xx = ox + x;
-        const bool in = yy >= 0 && yy < H && xx >= 0 && xx < W;  // uniform
-        const bool okq = cq < Cq;
+      const int ex = d.L[m].exf, kw = K + s * (ex - 1), nbx = (w + ex - 1) / ex;
+      auto emit = [&](int mt, int y, int bx, const float4v& dv) {
+        const int qd = mt * 4 + G, p = qd / Cq, cq = qd - p * Cq;
+        const int x = ex * bx + p, yy = oy + y, xx = ox + x;
+        // (the same for the 16 lanes that a sum runs over)
+        const bool in = yy >= 0 && yy < H && xx >= 0 && xx < W;
+        const bool okq = p < ex && x < w;
         const int pos = y * w + x;
         float4v at = {0.f, 0.f, 0.f, 0.f}, z = at, sa = at, da = at, db = at;
         if (okq) {
@@ -444,7 +451,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
           }
           if (m + 1 < k) put_split(pl, pld, ((pos * 16 + n) * Cq + cq) * 8, z);
         }
-        if (!in) return;  // (positions outside the map have no neuron)
+        if (!in || !okq) return;  // (positions outside the map have no neuron)
 #pragma unroll
         for (int r = 0; r < 4; ++r) sa[r] = row_sum16(sa[r]);
         if (m > 1) {
@@ -463,18 +470,17 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
           }
         }
       };
-      (void)cd;
-      (void)C;
       if (m == 1) {
         const unsigned* xs = reinterpret_cast<const unsigned*>(wsm + d.o_x);
-        win_stage<MAXKS, true>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, w, wave, nw,
+        win_stage<MAXKS, true>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, nbx, wave, nw,
                         [&](int ks, int y, int x, uint4v (&B)[3]) {
                           uint4v v;
 #pragma unroll
                           for (int h = 0; h < 2; ++h) {
                             const int qi = (ks * 4 + G) * 2 + h;
-                            const int tap = min(qi / Cqb, K * K - 1), cq = qi % Cqb;
-                            const int iy = y * s + tap / K, ix = x * s + tap % K;
+                            const int tap = min(qi / Cqb, K * kw - 1), cq = qi % Cqb;
+                            const int iy = y * s + tap / kw;
+                            const int ix = min(ex * x * s + tap % kw, wb - 1);
                             const unsigned u = xs[((iy * wb + ix) * 16 + n) * Cqb + cq];
                             // bytes to the high halves of bf16 pairs
                             v[2 * h] = __builtin_amdgcn_perm(u, 0u, 0x05000400u);
@@ -488,10 +494,11 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
       } else {
         const char* src = wsm + d.L[m - 1].o_pl;
         const int plane = d.L[m - 1].plane, c2 = Cqb / 2;
-        win_stage<MAXKS, false>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, w, wave, nw,
+        win_stage<MAXKS, false>(d.L[m].ff, d.L[m].nmtf, d.L[m].nksf, w, nbx, wave, nw,
                          [&](int ks, int y, int x, uint4v (&B)[3]) {
-                           const int ck = ks * 4 + G, tap = min(ck / c2, K * K - 1), cc = ck % c2;
-                           const int iy = y * s + tap / K, ix = x * s + tap % K;
+                           const int ck = ks * 4 + G, tap = min(ck / c2, K * kw - 1), cc = ck % c2;
+                           const int iy = y * s + tap / kw;
+                           const int ix = min(ex * x * s + tap % kw, wb - 1);
                            const int o = (((iy * wb + ix) * 16 + n) * c2 + cc) * 16;
 #pragma unroll
                            for (int p = 0; p < 3; ++p)
