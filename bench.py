@@ -275,15 +275,37 @@ def unstable_fractions(net, x0, w, C, split, alpha):
     return fr
 
 
+def split_classes(work, layers, one_row):
+    """The same work under the names of the split-operand kernels, which run where their shapes
+    apply.  one_row: bounds without given slopes carry one row per neuron instead of two in every
+    intermediate pass, so those passes' counts halve."""
+    L = len(layers)
+    out = {}
+    for cls, (f, b) in work.items():
+        k = int(cls.split("pass")[-1].rstrip("]")) if "[" in cls else L
+        if one_row and 2 <= k < L and not cls.startswith("relax_params"):
+            f, b = f / 2, b / 2
+        out[cls] = (f, b)
+        for old, new in (("pass3_window", "win_bound"), ("pass4_window", "win_bound"),
+                         ("fcT_relax", "fcT_split_relax"), ("fcT_bound", "fcT_split_bound"),
+                         ("convT_relax", "convT_split_relax"),
+                         ("convT_bound", "convT_split_bound")):
+            if cls.startswith(old + "["):
+                out[new + cls[len(old):]] = (f, b)
+    return out
+
+
 def traffic_record(workload, kernel):
     """HBM bytes per launch of a kernel class, as measured by rocprofv3 (FETCH_SIZE and
     WRITE_SIZE, scaled by a copy of known size) and recorded under profiles/ for this exact
-    library build (sha256 of lirpa.hip followed by build.py); None when no record matches."""
+    library build (sha256 of every file under csrc/ in order of their names, then build.py); None
+    when no record matches."""
     import glob
     import hashlib
     pkg = os.path.join(ROOT, "paper_2011_13824_amd")
     h = hashlib.sha256()
-    for f in (os.path.join(pkg, "csrc", "lirpa.hip"), os.path.join(pkg, "build.py")):
+    src = sorted(glob.glob(os.path.join(pkg, "csrc", "*")))
+    for f in src + [os.path.join(pkg, "build.py")]:
         with open(f, "rb") as fh:
             h.update(fh.read())
     sha = h.hexdigest()
@@ -426,7 +448,7 @@ def main():
     times = lirpa.lirpa_timing_end()
     torch.cuda.synchronize()
     fr = unstable_fractions(net, x0, w, C, split, alpha) if optimise else None
-    work = stage_work(w.layers, S, B, fr)
+    work = split_classes(stage_work(w.layers, S, B, fr), w.layers, not optimise)
     executed = {}
     if optimise:
         work.update(grad_work(w.layers, S, B, layer2_stats(net, x0, w, C, split, alpha), fr))
