@@ -7125,26 +7125,32 @@ int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0
     total += (long)S * (net->n[net->L - 1] + 1);
   }
   // the split weight fragments that this call's kernels read; a net with more of them than a
-  // launch carries takes more launches
-  int m = 1, kind = 0, blocks = (int)grid_for(total).x;
-  job.frag_blk = blocks;
-  do {
-    job.nfrag = 0;
-    for (; m <= net->L && job.nfrag < kFragJobs; kind ? (++m, kind = 0) : kind = 1) {
+  // launch carries takes more launches, of fragments alone
+  FragJob frag[2 * kMaxLayers];
+  int nfrag = 0, next = 0;
+  for (int m = 1; m <= net->L; ++m)
+    for (int kind = 0; kind < 2; ++kind) {
       const size_t off = kind ? p.off_ff[m] : p.off_fb[m];
       if (!off) continue;
       FragJob f = frag_job(net, m, kind);
       f.dst = at<uint4v>(ws, off);
       f.blk = (f.nmt * f.nks * 64 + kBlock - 1) / kBlock;
-      blocks += f.blk;
-      job.frag[job.nfrag++] = f;
+      frag[nfrag++] = f;
+    }
+  int blocks = (int)grid_for(total).x;
+  do {  // (every launch has blocks: the first its own, a further one a job's)
+    job.frag_blk = blocks;
+    job.nfrag = 0;
+    for (; next < nfrag && job.nfrag < kFragJobs; ++next) {
+      blocks += frag[next].blk;
+      job.frag[job.nfrag++] = frag[next];
     }
     if (int e = launch_k(tag("setup", 1, 1), st, [&] {
           hipLaunchKernelGGL(k_setup, dim3((unsigned)blocks), dim3(kBlock), 0, st, job);
         }))
       return e;
-    job.frag_blk = blocks = 0;  // further launches: fragments alone
-  } while (m <= net->L);
+    blocks = 0;
+  } while (next < nfrag);
   return LIRPA_OK;
 }
 

@@ -49,8 +49,8 @@ def _gpu():
     lirpa.load()
 
 
-def close(name, got, want):
-    excess = np.abs(got - want) - 1e-5 * (1 + np.abs(want))
+def close(name, got, want, tol=1e-5):
+    excess = np.abs(got - want) - tol * (1 + np.abs(want))
     print(f"{name}: max |gpu - oracle| = {np.abs(got - want).max():.3g}", flush=True)
     assert np.all(excess <= 0), f"{name}: off by {excess.max():.3g} beyond tolerance"
 
@@ -79,6 +79,30 @@ def test_windows(name, B):
     close(f"{name} grad lb", lb.cpu().double().numpy(), lr)
     check_grad(f"{name} grad", g.cpu().double().numpy(), gr, split,
                lambda b, j: one_sided(rnet, x0, eps, C, split, alpha, b, j))
+
+
+@pytest.mark.parametrize("convs", [8, 10, 16])
+def test_many_convolutions(convs):
+    # every convolution has weight fragments of its own in each direction, and a set-up launch
+    # carries 16 of them: 8 layers fill one launch in a gradient call, 10 one and a part of the
+    # next, 16 one in a bound and two in a gradient.  (Up to 17 chained sums where the nets above
+    # have four: four times their tolerance.)
+    arch = [wl.conv(1, 6, 4, 3, 1, 1)] + [wl.conv(4, 6, 4, 3, 1, 1)] * (convs - 1) + [wl.fc(144, 3)]
+    layers = wl.random_net(arch, convs)
+    x0 = np.random.default_rng(convs).uniform(0, 1, 36).astype(np.float32)
+    eps, C = 0.16 / convs, wl.margin_spec(3, 0)
+    rnet = ref.RefNet(layers)
+    alpha = np.random.default_rng(1).uniform(0.05, 0.95, (2, rnet.n_relu)).astype(np.float32)
+    net = lirpa.Network(layers)
+    for a in (None, alpha):
+        lb = net.bound(dev(x0), eps, dev(C), None, dev(a), B=2)
+        lr = ref.bound(rnet, x0, eps, C, None, a)[0]
+        close(f"{convs} lb", lb.cpu().double().numpy(), np.broadcast_to(lr, (2, 2)), 4e-5)
+    lb, g = net.bound_grad(dev(x0), eps, dev(C), None, dev(alpha))
+    lr, gr = ref.bound_grad(rnet, x0, eps, C, None, alpha)
+    close(f"{convs} grad lb", lb.cpu().double().numpy(), lr, 4e-5)
+    check_grad(f"{convs} grad", g.cpu().double().numpy(), gr, None,
+               lambda b, j: one_sided(rnet, x0, eps, C, None, alpha, b, j))
 
 
 @pytest.mark.parametrize("mode", ["bound", "grad"])
