@@ -501,7 +501,10 @@ struct SetupJob {
   const float* C;
   DLayer tL;
   int S;
-  // split weight fragments: the blocks from frag_blk on, frag[k].blk of them per job
+};
+// ... and the split weight fragments of a call that reads any: the blocks from frag_blk on,
+// frag[k].blk of them per job.
+struct SetupFrags : SetupJob {
   int frag_blk, nfrag;
   FragJob frag[kFragJobs];
 };
@@ -545,15 +548,20 @@ __device__ __forceinline__ void layer1_neuron(const Job& job, long j, int g) {
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_setup(SetupJob job_) {
-  const __attribute__((address_space(4))) SetupJob& job =
-      *(const __attribute__((address_space(4))) SetupJob*)__builtin_amdgcn_kernarg_segment_ptr();
-  if ((int)blockIdx.x >= job.frag_blk) {
-    int fb = (int)blockIdx.x - job.frag_blk, k = 0;
-    while (k + 1 < job.nfrag && fb >= job.frag[k].blk) fb -= job.frag[k++].blk;
-    const int idx = fb * (int)blockDim.x + (int)threadIdx.x;
-    if (idx < job.frag[k].nmt * job.frag[k].nks * 64) frag_entry(job.frag[k], idx);
-    return;
+// (Job: SetupJob, or SetupFrags where there are fragments, whose 1.3 KB of arguments and twice the
+// registers a call without them does not pay for)
+template <class Job>
+__global__ void __launch_bounds__(kBlock) k_setup(Job job_) {
+  const __attribute__((address_space(4))) Job& job =
+      *(const __attribute__((address_space(4))) Job*)__builtin_amdgcn_kernarg_segment_ptr();
+  if constexpr (std::is_same_v<Job, SetupFrags>) {
+    if ((int)blockIdx.x >= job.frag_blk) {
+      int fb = (int)blockIdx.x - job.frag_blk, k = 0;
+      while (k + 1 < job.nfrag && fb >= job.frag[k].blk) fb -= job.frag[k++].blk;
+      const int idx = fb * (int)blockDim.x + (int)threadIdx.x;
+      if (idx < job.frag[k].nmt * job.frag[k].nks * 64) frag_entry(job.frag[k], idx);
+      return;
+    }
   }
   long e = blockIdx.x * (long)blockDim.x + threadIdx.x;
   if (e < 16 * job.n1) {  // a group of 16 lanes never straddles the segment's end
@@ -7083,7 +7091,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
 int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0, float eps,
                   const float* C, int S, hipStream_t st) {
   long n1 = net->n[1];
-  SetupJob job{};
+  SetupFrags job{};
   job.t1 = dlayer(net->T[0]);
   job.x0 = x0;
   job.eps = eps;
@@ -7138,6 +7146,11 @@ int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0
       frag[nfrag++] = f;
     }
   int blocks = (int)grid_for(total).x;
+  if (nfrag == 0)
+    return launch_k(tag("setup", 1, 1), st, [&] {
+      hipLaunchKernelGGL(k_setup<SetupJob>, dim3((unsigned)blocks), dim3(kBlock), 0, st,
+                         static_cast<const SetupJob&>(job));
+    });
   do {  // (every launch has blocks: the first its own, a further one a job's)
     job.frag_blk = blocks;
     job.nfrag = 0;
@@ -7146,7 +7159,8 @@ int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0
       job.frag[job.nfrag++] = frag[next];
     }
     if (int e = launch_k(tag("setup", 1, 1), st, [&] {
-          hipLaunchKernelGGL(k_setup, dim3((unsigned)blocks), dim3(kBlock), 0, st, job);
+          hipLaunchKernelGGL(k_setup<SetupFrags>, dim3((unsigned)blocks), dim3(kBlock), 0, st,
+                             job);
         }))
       return e;
     blocks = 0;
