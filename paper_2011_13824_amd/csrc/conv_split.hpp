@@ -73,7 +73,8 @@ constexpr int kRowTasks = 2;  // prefetched tasks a thread
 
 // T_m^T: output (iy, ix) = (s ay + py - pad, s ex ax + px - pad), inputs (ay - jy,
 // ex ax + ex - 1 - jx).
-template <int MODE, int KS>
+// (SYM: a relaxing stage of a pass with one row per neuron, see Sink)
+template <int MODE, int KS, bool SYM>
 __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* __restrict__ in,
                                                      unsigned ldq, unsigned Q, Sink s) {
   extern __shared__ char csm[];
@@ -177,7 +178,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
             const float ah = a * (a >= 0.f ? lo[r] : up[r]);
             beta = fmaf(fminf(a, 0.f), bu[r], beta);
             beta = fmaf(ah, bz[r], beta);
-            gap = fmaf(fabsf(a), bu[r], gap);
+            if constexpr (SYM) gap = fmaf(fabsf(a), bu[r], gap);
             s.out[idx] = ah;
           } else {
             if (s.tsign) s.tsign[idx] = sign8(a);
@@ -190,8 +191,10 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     park(ay + 1);
     __syncthreads();
   }
-  gap += __shfl_xor(gap, 16, 64);
-  gap += __shfl_xor(gap, 32, 64);
+  if constexpr (SYM) {
+    gap += __shfl_xor(gap, 16, 64);
+    gap += __shfl_xor(gap, 32, 64);
+  }
   beta += __shfl_xor(beta, 16, 64);
   lin += __shfl_xor(lin, 16, 64);
   l1 += __shfl_xor(l1, 16, 64);
@@ -202,7 +205,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     red[(wave * 4 + 0) * 16 + lane] = beta;
     red[(wave * 4 + 1) * 16 + lane] = lin;
     red[(wave * 4 + 2) * 16 + lane] = l1;
-    red[(wave * 4 + 3) * 16 + lane] = gap;
+    if constexpr (SYM) red[(wave * 4 + 3) * 16 + lane] = gap;
   }
   __syncthreads();
   if (tid >= 16 || !qok) return;
@@ -211,7 +214,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     tot.beta += red[(w * 4 + 0) * 16 + tid];
     tot.lin += red[(w * 4 + 1) * 16 + tid];
     tot.l1 += red[(w * 4 + 2) * 16 + tid];
-    tot.gap += red[(w * 4 + 3) * 16 + tid];
+    if constexpr (SYM) tot.gap += red[(w * 4 + 3) * 16 + tid];
   }
   sink_finish<MODE>(s, tot, q, b, q % (unsigned)s.R, false);
 }

@@ -18,8 +18,9 @@ struct FcSplit {
   const uint4v* frag;
 };
 
-// T^T: out[i] = sum_o W[o][i] in[o].
-template <int MODE, int NT>
+// T^T: out[i] = sum_o W[o][i] in[o].  (SYM: a relaxing stage of a pass with one row per neuron,
+// see Sink)
+template <int MODE, int NT, bool SYM>
 __global__ void __launch_bounds__(kFcThreads)
     k_fcT_split(FcSplit c, const float* __restrict__ in, unsigned ldq, unsigned Q, Sink s) {
   extern __shared__ char fsm[];
@@ -127,7 +128,7 @@ __global__ void __launch_bounds__(kFcThreads)
             const float ah = a * (a >= 0.f ? pl[r] : pu[r]);
             beta[t] = fmaf(fminf(a, 0.f), pc[r], beta[t]);
             beta[t] = fmaf(ah, pz[r], beta[t]);
-            gap[t] = fmaf(fabsf(a), pc[r], gap[t]);
+            if constexpr (SYM) gap[t] = fmaf(fabsf(a), pc[r], gap[t]);
             s.out[idx] = ah;
           } else {
             if (s.tsign) s.tsign[idx] = sign8(a);
@@ -142,7 +143,7 @@ __global__ void __launch_bounds__(kFcThreads)
   for (int t = 0; t < NT; ++t) {
     float v[4] = {beta[t], lin[t], l1[t], gap[t]};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < (SYM ? 4 : 3); ++e) {
       v[e] += __shfl_xor(v[e], 16, 64);
       v[e] += __shfl_xor(v[e], 32, 64);
       if (lane < 16) red[(wave * 4 + e) * NQ + 16 * t + lane] = v[e];
@@ -156,7 +157,7 @@ __global__ void __launch_bounds__(kFcThreads)
     tot.beta += red[(w * 4 + 0) * NQ + tid];
     tot.lin += red[(w * 4 + 1) * NQ + tid];
     tot.l1 += red[(w * 4 + 2) * NQ + tid];
-    tot.gap += red[(w * 4 + 3) * NQ + tid];
+    if constexpr (SYM) tot.gap += red[(w * 4 + 3) * NQ + tid];
   }
   sink_finish<MODE>(s, tot, q, q / (unsigned)s.R, q % (unsigned)s.R, false);
 }

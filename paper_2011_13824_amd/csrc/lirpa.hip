@@ -413,10 +413,10 @@ __global__ void __launch_bounds__(kBlock) k_init_rows(DLayer t, const float* __r
 // (float4 parameter loads), and the rows' bias terms are summed through LDS in a fixed order.
 // 16 waves from 512 coefficients on: a wave's loop over them is a chain of cache latencies (1,568
 // coefficients, 25,500 rows: 0.306 ms with 4 waves, 0.119 with 16).
-template <int NW>
+template <int NW, bool SYM>
 __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float* __restrict__ WT,
                                                           long Q, Sink s) {
-  __shared__ float red[2][NW][64];
+  __shared__ float red[SYM ? 2 : 1][NW][64];
   const int lane = threadIdx.x & 63, w = wave_id();
   const long q = blockIdx.x * 64L + lane;
   const bool ok = q < Q;
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float*
         if (s.tape) s.tape[idx] = a;
         const float ah = a >= 0.f ? a * lo[u] : a * up[u];
         beta = fmaf(fminf(a, 0.f), bu[u], beta);
-        gap = fmaf(fabsf(a), bu[u], gap);
+        if constexpr (SYM) gap = fmaf(fabsf(a), bu[u], gap);
         beta = fmaf(ah, s.bias[(unsigned)(i + u) / hw], beta);
         s.out[idx] = ah;
       }
@@ -454,22 +454,23 @@ __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float*
       if (s.tape) s.tape[idx] = a;
       const float ah = a >= 0.f ? a * s.a_lo[pb + i] : a * s.a_up[pb + i];
       beta = fmaf(fminf(a, 0.f), s.b_up[pb + i], beta);
-      gap = fmaf(fabsf(a), s.b_up[pb + i], gap);
+      if constexpr (SYM) gap = fmaf(fabsf(a), s.b_up[pb + i], gap);
       beta = fmaf(ah, s.bias[(unsigned)i / hw], beta);
       s.out[idx] = ah;
     }
   }
   red[0][w][lane] = beta;
-  red[1][w][lane] = gap;
+  if constexpr (SYM) red[1][w][lane] = gap;
   __syncthreads();
   if (w == 0 && ok) {
-    float tb = red[0][0][lane], tg = red[1][0][lane];
-    for (int e = 1; e < NW; ++e) {
-      tb += red[0][e][lane];
-      tg += red[1][e][lane];
-    }
+    float tb = red[0][0][lane];
+    for (int e = 1; e < NW; ++e) tb += red[0][e][lane];
     s.beta[q] = sgn * t.b[j] + tb;
-    if (s.gap) s.gap[q] = tg;
+    if constexpr (SYM) {
+      float tg = red[1][0][lane];
+      for (int e = 1; e < NW; ++e) tg += red[1][e][lane];
+      s.gap[q] = tg;
+    }
   }
 }
 
@@ -683,19 +684,19 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // Reduce (beta, lin, l1) of the two lane halves and of the waves of the block, then finish the
 // rows q0..q0+31.  red: LDS scratch of nw*4*32 floats.
-template <int MODE>
+template <int MODE, bool SYM = false>
 __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red, long q0, long Q,
                                              bool add_beta_from_acc) {
   const int lane = threadIdx.x & 63, wave = wave_id(), nw = blockDim.x >> 6;
   acc.beta += __shfl_xor(acc.beta, 32, 64);
   acc.lin += __shfl_xor(acc.lin, 32, 64);
   acc.l1 += __shfl_xor(acc.l1, 32, 64);
-  acc.gap += __shfl_xor(acc.gap, 32, 64);
+  if constexpr (SYM) acc.gap += __shfl_xor(acc.gap, 32, 64);
   if (lane < 32) {
     red[(wave * 4 + 0) * 32 + lane] = acc.beta;
     red[(wave * 4 + 1) * 32 + lane] = acc.lin;
     red[(wave * 4 + 2) * 32 + lane] = acc.l1;
-    red[(wave * 4 + 3) * 32 + lane] = acc.gap;
+    if constexpr (SYM) red[(wave * 4 + 3) * 32 + lane] = acc.gap;
   }
   __syncthreads();
   if (wave != 0 || lane >= 32) return;
@@ -706,7 +707,7 @@ __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red,
     t.beta += red[(w * 4 + 0) * 32 + lane];
     t.lin += red[(w * 4 + 1) * 32 + lane];
     t.l1 += red[(w * 4 + 2) * 32 + lane];
-    t.gap += red[(w * 4 + 3) * 32 + lane];
+    if constexpr (SYM) t.gap += red[(w * 4 + 3) * 32 + lane];
   }
   (void)add_beta_from_acc;
   sink_finish<MODE>(s, t, q, q / s.R, q % s.R, false);
@@ -727,7 +728,7 @@ __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red,
 // (relaxation of layer m-1 plus bias, or concretisation) before the group starts its next row.
 // The y1 loop is unrolled over the rotation period so every register index is static.
 template <int K, int S, int P, int H1, int W1, int H0, int W0, int CO, int CPW, int NW,
-          int MODE, bool TAPE>
+          int MODE, bool TAPE, bool SYM>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MODE == MODE_BOUND && !TAPE ? (CO <= 8 ? 4 : 3) : 1, MODE == MODE_BOUND && !TAPE ? 8 : 2)))
 k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, Sink s) {
   static_assert(K <= 4 && S <= K && CO % 4 == 0 && W0 % 4 == 0, "unsupported geometry");
@@ -848,7 +849,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
           const float ah = a >= 0.f ? a * lo[j] : a * up[j];
           beta = fmaf(fminf(a, 0.f), bu[j], beta);
           beta = fmaf(ah, bz[j], beta);
-          gap = fmaf(fabsf(a), bu[j], gap);
+          if constexpr (SYM) gap = fmaf(fabsf(a), bu[j], gap);
           s.out[idx] = ah;
         }
       }
@@ -1032,8 +1033,10 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
   }
 
   // sum over lane groups and waves, then finish rows q0..q0+15
-  gap += __shfl_xor(gap, 16, 64);
-  gap += __shfl_xor(gap, 32, 64);
+  if constexpr (SYM) {
+    gap += __shfl_xor(gap, 16, 64);
+    gap += __shfl_xor(gap, 32, 64);
+  }
   beta += __shfl_xor(beta, 16, 64);
   lin += __shfl_xor(lin, 16, 64);
   l1 += __shfl_xor(l1, 16, 64);
@@ -1045,7 +1048,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
     red[(wave * 4 + 0) * 16 + lane] = beta;
     red[(wave * 4 + 1) * 16 + lane] = lin;
     red[(wave * 4 + 2) * 16 + lane] = l1;
-    red[(wave * 4 + 3) * 16 + lane] = gap;
+    if constexpr (SYM) red[(wave * 4 + 3) * 16 + lane] = gap;
   }
   __syncthreads();
   if (wave != 0 || lane >= 16 || !qok) return;
@@ -1054,7 +1057,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
     tot.beta += red[(w * 4 + 0) * 16 + lane];
     tot.lin += red[(w * 4 + 1) * 16 + lane];
     tot.l1 += red[(w * 4 + 2) * 16 + lane];
-    tot.gap += red[(w * 4 + 3) * 16 + lane];
+    if constexpr (SYM) tot.gap += red[(w * 4 + 3) * 16 + lane];
   }
   sink_finish<MODE>(s, tot, q, b, q % (unsigned)s.R, false);
 }
@@ -1078,11 +1081,12 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
 // turned into relaxed coefficients (with their intercept and bias terms) after them.  The slab
 // that would hold these coefficients is never written or read.
 template <int K, int S, int P, int H1, int W1, int H0, int W0, int CO, int CI, int CPW, int NS,
-          bool TAPE, bool FC>
+          bool TAPE, bool FC, bool SYM>
 __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 : (CI / CPW + NS <= 12 ? 6 : 1))
     k_convT_relax_ws(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, Sink s,
                      FcSrc fc) {
   static_assert(W0 == 16 && K <= 4 && S <= K && CO % 4 == 0 && CI % CPW == 0, "geometry");
+  static_assert(!SYM || !TAPE, "one row per neuron: bounds without a tape");
   static_assert((H1 - 1) * S - P + K >= H0, "every output row is reached by an input row");
   constexpr int NM = CI / CPW;                   // matrix waves
   constexpr int NTM = 64 * NM;
@@ -1112,8 +1116,8 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   __shared__ float tiles[3][TILE];
   __shared__ float rows[2][RB];
   __shared__ float pars[3][PB];
-  __shared__ float red[NS * 16], gred[NS * 16];
-  __shared__ float red_fc[FC ? NM * 16 : 1], gred_fc[FC ? NM * 16 : 1];
+  __shared__ float red[NS * 16], gred[SYM ? NS * 16 : 1];
+  __shared__ float red_fc[FC ? NM * 16 : 1], gred_fc[FC && SYM ? NM * 16 : 1];
 
   const int lane = threadIdx.x & 63, wave = wave_id();
   const unsigned q0 = xcd_tile(blockIdx.x) * 16u;
@@ -1278,7 +1282,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
             fbeta_a = fmaf(ha, g_bz[k], fbeta_a);
             fbeta_b = fmaf(fminf(b, 0.f), g_bu[k][e], fbeta_b);
             fbeta_b = fmaf(hb, g_bz[k], fbeta_b);
-            if constexpr (!TAPE) {
+            if constexpr (SYM) {
               fgap_a = fmaf(fabsf(a), g_bu[k][e], fgap_a);
               fgap_b = fmaf(fabsf(b), g_bu[k][e], fgap_b);
             }
@@ -1381,14 +1385,18 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
       for (int o = 8; o < 64; o <<= 1) {
         fbeta_a += __shfl_xor(fbeta_a, o, 64);
         fbeta_b += __shfl_xor(fbeta_b, o, 64);
-        fgap_a += __shfl_xor(fgap_a, o, 64);
-        fgap_b += __shfl_xor(fgap_b, o, 64);
+        if constexpr (SYM) {
+          fgap_a += __shfl_xor(fgap_a, o, 64);
+          fgap_b += __shfl_xor(fgap_b, o, 64);
+        }
       }
       if (lane < 8) {
         red_fc[wave * 16 + 2 * lane] = fbeta_a;
         red_fc[wave * 16 + 2 * lane + 1] = fbeta_b;
-        gred_fc[wave * 16 + 2 * lane] = fgap_a;
-        gred_fc[wave * 16 + 2 * lane + 1] = fgap_b;
+        if constexpr (SYM) {
+          gred_fc[wave * 16 + 2 * lane] = fgap_a;
+          gred_fc[wave * 16 + 2 * lane + 1] = fgap_b;
+        }
       }
     }
     lds_barrier();  // the storers' final reduction
@@ -1430,7 +1438,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
         const float ah = a[j] * (pos ? lo[j] : up[j]);
         beta = fmaf(pos ? 0.f : a[j], bu[j], beta);
         beta = fmaf(ah, bz[j], beta);
-        if constexpr (!TAPE) gap = fmaf(fabsf(a[j]), bu[j], gap);
+        if constexpr (SYM) gap = fmaf(fabsf(a[j]), bu[j], gap);
         store_row(s.out + base, lane_boff, ah);
       }
     }
@@ -1445,22 +1453,26 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   stage(H1);
   beta += __shfl_xor(beta, 16, 64);
   beta += __shfl_xor(beta, 32, 64);
-  gap += __shfl_xor(gap, 16, 64);
-  gap += __shfl_xor(gap, 32, 64);
+  if constexpr (SYM) {
+    gap += __shfl_xor(gap, 16, 64);
+    gap += __shfl_xor(gap, 32, 64);
+    if (lane < 16) gred[ws * 16 + lane] = gap;
+  }
   if (lane < 16) red[ws * 16 + lane] = beta;
-  if (lane < 16) gred[ws * 16 + lane] = gap;
   lds_barrier();
   if (ws != 0 || lane >= 16 || !qok) return;
   float tot = 0.f, tg = 0.f;
   for (int w = 0; w < NS; ++w) tot += red[w * 16 + lane];
-  for (int w = 0; w < NS; ++w) tg += gred[w * 16 + lane];
+  if constexpr (SYM)
+    for (int w = 0; w < NS; ++w) tg += gred[w * 16 + lane];
   if constexpr (FC) {
     // the rows' own bias +-b_k[j] and the terms of the relaxation that built them
     const unsigned r = q % R, nk = (unsigned)fc.nk;
     float fb = r < nk ? fc.b[r] : -fc.b[r - nk];
     for (int w = 0; w < NM; ++w) fb += red_fc[w * 16 + lane];
     tot += fb;
-    for (int w = 0; w < NM; ++w) tg += gred_fc[w * 16 + lane];
+    if constexpr (SYM)
+      for (int w = 0; w < NM; ++w) tg += gred_fc[w * 16 + lane];
   }
   Acc a{tot, 0.f, 0.f, tg};
   sink_finish<MODE_SLAB>(s, a, q, q / R, q % R, FC);
@@ -1479,7 +1491,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
 //     order, with the rotating lane-group scheme, accumulating ||A_x||_1 per row.
 // The bound of each row is then beta - eps ||A_x||_1 (the linear term sits in the layer-1 bias).
 template <int K, int S, int P, int H1, int W1, int H0, int W0, int CO, int CI, int NS, int K1,
-          int S1, int P1, int HX, int WX, int C0>
+          int S1, int P1, int HX, int WX, int C0, bool SYM>
 __global__ void __launch_bounds__(64 * (CI + NS + C0))
     k_convT2_bound(DLayer t, DLayer t1, const float* __restrict__ in, unsigned ldq, unsigned Q,
                    Sink s) {
@@ -1678,7 +1690,7 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
           if (qok) {
             beta = fmaf(pos ? 0.f : a, bu[j], beta);
             beta = fmaf(ah, bz[j], beta);
-            gap = fmaf(fabsf(a), bu[j], gap);
+            if constexpr (SYM) gap = fmaf(fabsf(a), bu[j], gap);
           }
           row[x * 16] = ah;
         }
@@ -1691,10 +1703,12 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
     }
     beta += __shfl_xor(beta, 16, 64);
     beta += __shfl_xor(beta, 32, 64);
-    gap += __shfl_xor(gap, 16, 64);
-    gap += __shfl_xor(gap, 32, 64);
     if (lane < 16) red[ws * 16 + lane] = beta;
-    if (lane < 16) red[(NS + C0 + ws) * 16 + lane] = gap;
+    if constexpr (SYM) {
+      gap += __shfl_xor(gap, 16, 64);
+      gap += __shfl_xor(gap, 32, 64);
+      if (lane < 16) red[(NS + C0 + ws) * 16 + lane] = gap;
+    }
     lds_barrier();
     return;
   }
@@ -1785,7 +1799,8 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
   for (int w = 0; w < NS; ++w) tb += red[w * 16 + lane];
   for (int w = 0; w < C0; ++w) ta += red[(NS + w) * 16 + lane];
   float tg = 0.f;
-  for (int w = 0; w < NS; ++w) tg += red[(NS + C0 + w) * 16 + lane];
+  if constexpr (SYM)
+    for (int w = 0; w < NS; ++w) tg += red[(NS + C0 + w) * 16 + lane];
   Acc a{tb, 0.f, ta, tg};
   sink_finish<MODE_BOUND>(s, a, q, q / R, q % R, false);
 }
@@ -1855,7 +1870,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   static_assert(NBS == 2 || NBS == 3, "sub-domains per block");
   static_assert(SPEC == 0 || !FC, "the spec source replaces the slab source");
   static_assert(!TAPE || FC, "tapes are written for the FC source only");
-  static_assert(!SYM || (FC && !TAPE), "one row per neuron: plain bounds of the FC source");
+  static_assert(!SYM || (!TAPE && SPEC == 0), "one row per neuron: plain bounds of a pass");
   constexpr int NMT_S = CO * W1 / 16;  // spec source: 16-entry tiles of an input row
   static_assert(SPEC == 0 || (NMT_S % (CI / CPW) == 0 && W1 % 4 == 0), "spec tiles per wave");
   static_assert(SPEC == 0 || NMT_S / (CI / CPW) <= 2, "spec operands: two tiles per wave");
@@ -1873,8 +1888,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   __shared__ float tiles[2][TILE];
   __shared__ float ring[2][SLOT];
   __shared__ float4v pars[2][PSLOT4];
-  constexpr bool GAP = SYM || (!FC && SPEC == 0);  // (the slab source: where Sink::gap asks for it)
-  __shared__ float red[NM * 16 + 2 * NXW * 16 + (GAP ? (NM + NXW) * 16 : 0)];
+  __shared__ float red[NM * 16 + 2 * NXW * 16 + (SYM ? (NM + NXW) * 16 : 0)];
   float* gred = red + NM * 16 + 2 * NXW * 16;  // SYM: the gaps, matrix waves then x waves
   // spec source: the block's rows relaxed onto layer L-1, the MFMA B operand [4 SPEC][16 rows]
   __shared__ float vts[SPEC > 0 ? SPEC * 64 : 1];
@@ -2393,7 +2407,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
         const float ah = a * (a >= 0.f ? p[0] : p[1]);
         beta = fmaf(fminf(a, 0.f), p[2], beta);
         beta = fmaf(ah, p[3], beta);
-        if constexpr (GAP) gap = fmaf(fabsf(a), p[2], gap);
+        if constexpr (SYM) gap = fmaf(fabsf(a), p[2], gap);
         hn[ks] = ah;
       }
     };
@@ -2459,7 +2473,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     red[NM * 16 + XB * 16 + lane] = beta;
     red[NM * 16 + (NXW + XB) * 16 + lane] = l1;
   }
-  if constexpr (GAP) {
+  if constexpr (SYM) {
     gap += __shfl_xor(gap, 16, 64);
     gap += __shfl_xor(gap, 32, 64);
     if (lane < 16) gred[(NM + XB) * 16 + lane] = gap;
@@ -2515,7 +2529,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   } else {
     if (q >= Q || (SPEC > 0 && (int)r >= fc.nspec)) return;
     float tg = 0.f;
-    if constexpr (GAP)
+    if constexpr (SYM)
       for (int w = 0; w < NXW; ++w) tg += gred[(NM + w) * 16 + lane];
     Acc a{tb, 0.f, ta, tg};
     // (spec source: no running bias from an earlier stage)
@@ -3621,7 +3635,7 @@ __global__ void __launch_bounds__(kBlock)
 // and 8 waves; the block's inputs in[.][q0..q0+31] sit in LDS, each wave takes every 8th tile of
 // 32 output features i, K runs over o two at a time with the A operand (W, read straight from
 // memory, L2-resident) fetched one group of 16 steps ahead.  Epilogue as in the other stages.
-template <int MODE, int NWAVE>
+template <int MODE, int NWAVE, bool SYM>
 __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* __restrict__ in,
                                                   long ldq, long Q, Sink s) {
   extern __shared__ float lds[];
@@ -3711,7 +3725,7 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
             const float ah = a * (a >= 0.f ? p0[g][e] : p1[g][e]);
             sum.beta = fmaf(fminf(a, 0.f), p2[g][e], sum.beta);
             sum.beta = fmaf(ah, p3[g][e], sum.beta);
-            sum.gap = fmaf(fabsf(a), p2[g][e], sum.gap);
+            if constexpr (SYM) sum.gap = fmaf(fabsf(a), p2[g][e], sum.gap);
             s.out[(long)i * s.ldq + q] = ah;
           } else {
             sum.lin = fmaf(a, p0[g][e], sum.lin);
@@ -3720,7 +3734,7 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
         }
     }
   }
-  block_finish<MODE>(s, sum, red, q0, Q, false);
+  block_finish<MODE, SYM>(s, sum, red, q0, Q, false);
 }
 
 // The final pass's first two stages when T_L and T_{L-1} are fully connected, 16 rows
@@ -6080,7 +6094,7 @@ using ConvTKernel = void (*)(DLayer, const float*, unsigned, unsigned, Sink);
 // 32x32, k4 s2 p1 from 8 or 16 to 16 or 32 channels on 16x16, k3 s1 p1 8 to 8 on 16x16);
 // everything else uses the per-lane gather kernel.  One wave per channel ci, two
 // channels per wave above 8.
-template <int MODE, bool TAPE>
+template <int MODE, bool TAPE, bool SYM>
 ConvTKernel<MODE> convT_mfma_pick(const DLayer& t, int* nwaves) {
   const bool g_s2_32 = t.k == 4 && t.stride == 2 && t.pad == 1 && t.out_h == 16 &&
                        t.out_w == 16 && t.in_h == 32 && t.in_w == 32;
@@ -6090,27 +6104,27 @@ ConvTKernel<MODE> convT_mfma_pick(const DLayer& t, int* nwaves) {
                        t.out_w == 16 && t.in_h == 16 && t.in_w == 16;
   if (g_s2_32 && t.in_c == 3 && t.out_c == 8) {
     *nwaves = 3;
-    return k_convT_mfma<4, 2, 1, 16, 16, 32, 32, 8, 1, 3, MODE, TAPE>;
+    return k_convT_mfma<4, 2, 1, 16, 16, 32, 32, 8, 1, 3, MODE, TAPE, SYM>;
   }
   if (g_s2_32 && t.in_c == 3 && t.out_c == 16) {
     *nwaves = 3;
-    return k_convT_mfma<4, 2, 1, 16, 16, 32, 32, 16, 1, 3, MODE, TAPE>;
+    return k_convT_mfma<4, 2, 1, 16, 16, 32, 32, 16, 1, 3, MODE, TAPE, SYM>;
   }
   if (g_s2_16 && t.in_c == 8 && t.out_c == 16) {
     *nwaves = 8;
-    return k_convT_mfma<4, 2, 1, 8, 8, 16, 16, 16, 1, 8, MODE, TAPE>;
+    return k_convT_mfma<4, 2, 1, 8, 8, 16, 16, 16, 1, 8, MODE, TAPE, SYM>;
   }
   if (g_s2_16 && t.in_c == 8 && t.out_c == 8) {
     *nwaves = 8;
-    return k_convT_mfma<4, 2, 1, 8, 8, 16, 16, 8, 1, 8, MODE, TAPE>;
+    return k_convT_mfma<4, 2, 1, 8, 8, 16, 16, 8, 1, 8, MODE, TAPE, SYM>;
   }
   if (g_s2_16 && t.in_c == 16 && t.out_c == 32) {
     *nwaves = 8;
-    return k_convT_mfma<4, 2, 1, 8, 8, 16, 16, 32, 2, 8, MODE, TAPE>;
+    return k_convT_mfma<4, 2, 1, 8, 8, 16, 16, 32, 2, 8, MODE, TAPE, SYM>;
   }
   if (g_s1_16 && t.in_c == 8 && t.out_c == 8) {
     *nwaves = 8;
-    return k_convT_mfma<3, 1, 1, 16, 16, 16, 16, 8, 1, 8, MODE, TAPE>;
+    return k_convT_mfma<3, 1, 1, 16, 16, 16, 16, 8, 1, 8, MODE, TAPE, SYM>;
   }
   return nullptr;
 }
@@ -6120,39 +6134,44 @@ ConvTKernel<MODE> convT_mfma_pick(const DLayer& t, int* nwaves) {
 // everything else uses the per-lane gather kernel.  One wave per channel ci, two
 // channels per wave above 8.
 template <int MODE>
-ConvTKernel<MODE> convT_mfma_for(const DLayer& t, bool tape, int* nwaves) {
-  return tape ? convT_mfma_pick<MODE, true>(t, nwaves) : convT_mfma_pick<MODE, false>(t, nwaves);
+ConvTKernel<MODE> convT_mfma_for(const DLayer& t, bool tape, int* nwaves, bool sym = false) {
+  if (tape) return convT_mfma_pick<MODE, true, false>(t, nwaves);
+  return sym ? convT_mfma_pick<MODE, false, MODE == MODE_SLAB>(t, nwaves)
+             : convT_mfma_pick<MODE, false, false>(t, nwaves);
 }
 
 // Wave-specialised relaxing stage for the 16-wide output geometries; null when not covered.
 // fc: the variant that builds its input from the fully connected layer above (bound passes
-// only).  *nwaves: matrix + storer waves; *lds: dynamic LDS bytes.
+// only); sym: the variant with one row per neuron (without a tape).  *nwaves: matrix + storer waves; *lds: dynamic LDS bytes.
 using WsKernel = void (*)(DLayer, const float*, unsigned, unsigned, Sink, FcSrc);
 template <int K, int S, int P, int H1, int W1, int H0, int W0, int CO, int CI, int CPW, int NS>
-WsKernel convT_ws_inst(bool tape, bool fc, int* nwaves, size_t* lds) {
+WsKernel convT_ws_inst(bool tape, bool fc, bool sym, int* nwaves, size_t* lds) {
   *nwaves = CI / CPW + NS;
   *lds = 0;  // all LDS of the kernel is static
-  if (fc)
-    return tape ? k_convT_relax_ws<K, S, P, H1, W1, H0, W0, CO, CI, CPW, NS, true, true>
-                : k_convT_relax_ws<K, S, P, H1, W1, H0, W0, CO, CI, CPW, NS, false, true>;
-  return tape ? k_convT_relax_ws<K, S, P, H1, W1, H0, W0, CO, CI, CPW, NS, true, false>
-              : k_convT_relax_ws<K, S, P, H1, W1, H0, W0, CO, CI, CPW, NS, false, false>;
+  auto pick = [&](auto fc_) -> WsKernel {
+    constexpr bool FC = decltype(fc_)::value;
+    if (tape) return k_convT_relax_ws<K, S, P, H1, W1, H0, W0, CO, CI, CPW, NS, true, FC, false>;
+    return sym ? k_convT_relax_ws<K, S, P, H1, W1, H0, W0, CO, CI, CPW, NS, false, FC, true>
+               : k_convT_relax_ws<K, S, P, H1, W1, H0, W0, CO, CI, CPW, NS, false, FC, false>;
+  };
+  return fc ? pick(std::true_type()) : pick(std::false_type());
 }
 
-WsKernel convT_ws_for(const DLayer& t, bool tape, bool fc, int* nwaves, size_t* lds) {
+WsKernel convT_ws_for(const DLayer& t, bool tape, bool fc, int* nwaves, size_t* lds,
+                      bool sym = false) {
   const bool g_s2_16 = t.k == 4 && t.stride == 2 && t.pad == 1 && t.out_h == 8 && t.out_w == 8 &&
                        t.in_h == 16 && t.in_w == 16;
   const bool g_s1_16 = t.k == 3 && t.stride == 1 && t.pad == 1 && t.out_h == 16 &&
                        t.out_w == 16 && t.in_h == 16 && t.in_w == 16;
   if (g_s2_16 && t.in_c == 8 && t.out_c == 16)
-    return fc ? convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 16, 8, 1, 4>(tape, fc, nwaves, lds)
-              : convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4>(tape, fc, nwaves, lds);
+    return fc ? convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 16, 8, 1, 4>(tape, fc, sym, nwaves, lds)
+              : convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4>(tape, fc, sym, nwaves, lds);
   if (g_s2_16 && t.in_c == 8 && t.out_c == 8)
-    return convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 8, 8, 1, 4>(tape, fc, nwaves, lds);
+    return convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 8, 8, 1, 4>(tape, fc, sym, nwaves, lds);
   if (g_s2_16 && t.in_c == 16 && t.out_c == 32)
-    return convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4>(tape, fc, nwaves, lds);
+    return convT_ws_inst<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4>(tape, fc, sym, nwaves, lds);
   if (g_s1_16 && t.in_c == 8 && t.out_c == 8 && !fc)
-    return convT_ws_inst<3, 1, 1, 16, 16, 16, 16, 8, 8, 1, 4>(tape, fc, nwaves, lds);
+    return convT_ws_inst<3, 1, 1, 16, 16, 16, 16, 8, 8, 1, 4>(tape, fc, sym, nwaves, lds);
   return nullptr;
 }
 
@@ -6219,13 +6238,22 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
                  const Sink& s, const uint4v* fb, hipStream_t st) {
   DLayer t = dlayer(net->T[m - 1]);
   const char* sfx = MODE == MODE_SLAB ? "_relax" : "_bound";
+  // (the relaxing kernels' form of a pass that carries one row per neuron; the concretising ones
+  // have nothing to add to its gaps)
+  constexpr bool SYM = MODE == MODE_SLAB;
+  const bool sym = SYM && s.gap != nullptr;
   const unsigned nblk32 = (unsigned)((Q + 31) / 32);
   if (t.kind == LIRPA_LINEAR) {
     FcLaunch f;
     if (fb && fc_split_desc(net, m, 0, true, &f, Q)) {
       f.c.frag = fb;
-      auto kern = f.nt == 4 ? k_fcT_split<MODE, 4>
-                            : (f.nt == 2 ? k_fcT_split<MODE, 2> : k_fcT_split<MODE, 1>);
+      auto pick = [&](auto nt) {
+        constexpr int NT = decltype(nt)::value;
+        return sym ? k_fcT_split<MODE, NT, SYM> : k_fcT_split<MODE, NT, false>;
+      };
+      auto kern = f.nt == 4 ? pick(std::integral_constant<int, 4>())
+                            : (f.nt == 2 ? pick(std::integral_constant<int, 2>())
+                                         : pick(std::integral_constant<int, 1>()));
       if (int e = reserve_lds(reinterpret_cast<const void*>(kern), f.lds)) return e;
       const unsigned nb = (unsigned)round_up((Q + 16 * f.nt - 1) / (16 * f.nt), 8);
       return launch_k(tag((std::string("fcT_split") + sfx).c_str(), m, pass), st, [&] {
@@ -6239,13 +6267,10 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
       const bool wide = nblk32 <= 256;
       const int nwv = wide ? 16 : 8;
       size_t lds = ((size_t)t.out_c * 32 + (size_t)nwv * 4 * 32) * sizeof(float);
+      auto kern = wide ? (sym ? k_fcT_mfma<MODE, 16, SYM> : k_fcT_mfma<MODE, 16, false>)
+                       : (sym ? k_fcT_mfma<MODE, 8, SYM> : k_fcT_mfma<MODE, 8, false>);
       return launch_k(tag((std::string("fcT") + sfx).c_str(), m, pass), st, [&] {
-        if (wide)
-          hipLaunchKernelGGL((k_fcT_mfma<MODE, 16>), dim3(nblk32), dim3(1024), lds, st, t, in,
-                             ldq, Q, s);
-        else
-          hipLaunchKernelGGL((k_fcT_mfma<MODE, 8>), dim3(nblk32), dim3(512), lds, st, t, in, ldq,
-                             Q, s);
+        hipLaunchKernelGGL(kern, dim3(nblk32), dim3(64 * nwv), lds, st, t, in, ldq, Q, s);
       });
     }
     return launch_k(tag((std::string("fcT_lane") + sfx).c_str(), m, pass), st, [&] {
@@ -6257,7 +6282,7 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
     if (s.R >= 16) {
       int nwt = 0;
       size_t lds = 0;
-      if (WsKernel kern = convT_ws_for(t, s.tape != nullptr, false, &nwt, &lds)) {
+      if (WsKernel kern = convT_ws_for(t, s.tape != nullptr, false, &nwt, &lds, sym)) {
         const unsigned nblk16 = (unsigned)round_up((Q + 15) / 16, 16);
         return launch_k(tag("convT_relax", m, pass), st, [&] {
           hipLaunchKernelGGL(kern, dim3(nblk16), dim3(64 * nwt), lds, st, t, in, (unsigned)ldq,
@@ -6267,7 +6292,7 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
     }
   }
   const bool tape = MODE == MODE_SLAB ? s.tape != nullptr : s.tsign != nullptr;
-  if (ConvTKernel<MODE> kern = convT_mfma_for<MODE>(t, tape, &nw)) {
+  if (ConvTKernel<MODE> kern = convT_mfma_for<MODE>(t, tape, &nw, sym)) {
     const unsigned nblk16 = (unsigned)round_up((Q + 15) / 16, 16);
     const size_t cs = (size_t)t.out_w * 16 + (80 - (t.out_w * 16) % 64) % 64;
     // x0 is staged in LDS only when the linear term is not folded into the layer-1 bias
@@ -6282,12 +6307,16 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
   SplitLaunch q;
   if (fb && conv_split_desc(net->T[m - 1], m, 0, &q)) {
     q.c.frag = fb;
-    auto kern = k_convT_split<MODE, 0>;
+    auto pick = [&](auto ks) {
+      constexpr int KS = decltype(ks)::value;
+      return sym ? k_convT_split<MODE, KS, SYM> : k_convT_split<MODE, KS, false>;
+    };
+    auto kern = pick(std::integral_constant<int, 0>());
     switch (q.c.nks) {
-      case 1: kern = k_convT_split<MODE, 1>; break;
-      case 2: kern = k_convT_split<MODE, 2>; break;
-      case 3: kern = k_convT_split<MODE, 3>; break;
-      case 4: kern = k_convT_split<MODE, 4>; break;
+      case 1: kern = pick(std::integral_constant<int, 1>()); break;
+      case 2: kern = pick(std::integral_constant<int, 2>()); break;
+      case 3: kern = pick(std::integral_constant<int, 3>()); break;
+      case 4: kern = pick(std::integral_constant<int, 4>()); break;
       default: break;
     }
     if (int e = reserve_lds(reinterpret_cast<const void*>(kern), q.lds)) return e;
@@ -6408,7 +6437,7 @@ using FcBoundKernel = void (*)(DLayer, DLayer, const float*, unsigned, unsigned,
 // (spec: the variant that takes the final pass's spec rows from C W_L through a closing
 // Linear layer of 97..100 features; conv 3 -> 8 -> 16 channels, three sub-domains per block;
 // tape: the FC variant that also writes the reverse sweep's tape over g^(1) and sign tape;
-// sym: the FC variant with one row per neuron)
+// sym: the FC variant, or the slab variant of two sub-domains per block, with one row per neuron)
 FcBoundKernel conv12_bound_for(const lirpa_net* net, bool fc, int nbs, int* nwaves,
                                bool spec = false, bool tape = false, bool sym = false) {
   if (net->L < 3) return nullptr;
@@ -6437,6 +6466,9 @@ FcBoundKernel conv12_bound_for(const lirpa_net* net, bool fc, int nbs, int* nwav
       return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, true, 2, 0,
                               false, true>;
     if (fc) return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, true, 2>;
+    if (sym)
+      return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, false, 2, 0,
+                              false, true>;
     if (nbs == 2)
       return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, false, 2>;
     return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 16, 8, 2, 4, 2, 1, 32, 32, 3, 4, false, 3>;
@@ -6452,6 +6484,9 @@ FcBoundKernel conv12_bound_for(const lirpa_net* net, bool fc, int nbs, int* nwav
       return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, true, 2, 0,
                               false, true>;
     if (fc) return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, true, 2>;
+    if (sym)
+      return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, false, 2, 0,
+                              false, true>;
     return k_convT_fc_bound<4, 2, 1, 8, 8, 16, 16, 32, 16, 2, 4, 2, 1, 32, 32, 3, 4, false, 2>;
   }
   return nullptr;
@@ -6460,7 +6495,8 @@ FcBoundKernel conv12_bound_for(const lirpa_net* net, bool fc, int nbs, int* nwav
 // Fused last two stages (T_2^T + relaxation of layer 1, T_1^T + concretisation) when both
 // layers are convolutions of a covered geometry; null otherwise.  *nwaves, *lds as launched.
 using ConvT2Kernel = void (*)(DLayer, DLayer, const float*, unsigned, unsigned, Sink);
-ConvT2Kernel convT2_bound_for(const lirpa_net* net, int* nwaves, size_t* lds) {
+// (sym: one row per neuron)
+ConvT2Kernel convT2_bound_for(const lirpa_net* net, bool sym, int* nwaves, size_t* lds) {
   if (net->L < 3) return nullptr;
   const lirpa_layer &a = net->T[0], &t = net->T[1];
   if (a.kind != LIRPA_CONV2D || t.kind != LIRPA_CONV2D) return nullptr;
@@ -6481,7 +6517,8 @@ ConvT2Kernel convT2_bound_for(const lirpa_net* net, int* nwaves, size_t* lds) {
   if (t.k == 3 && t.stride == 1 && t.pad == 1 && t.in_c == 8 && t.out_c == 8 && t.in_h == 16 &&
       t.out_h == 16 && t.out_w == 16) {
     set(8, 8, 16, 3, 1, 4);
-    return k_convT2_bound<3, 1, 1, 16, 16, 16, 16, 8, 8, 4, 4, 2, 1, 32, 32, 3>;
+    return sym ? k_convT2_bound<3, 1, 1, 16, 16, 16, 16, 8, 8, 4, 4, 2, 1, 32, 32, 3, true>
+               : k_convT2_bound<3, 1, 1, 16, 16, 16, 16, 8, 8, 4, 4, 2, 1, 32, 32, 3, false>;
   }
   return nullptr;
 }
@@ -6500,7 +6537,7 @@ int run_stages(const Chunk& c, int pass, int mtop, long R, long Q, long ldq, flo
     if (m == 2 && !c.tape && R >= 8) {
       // T_2^T, the layer-1 relaxation, T_1^T and the concretisation in one kernel
       int nw = 0;
-      if (FcBoundKernel kern = conv12_bound_for(c.net, false, R >= 16 ? 2 : 3, &nw)) {
+      if (FcBoundKernel kern = conv12_bound_for(c.net, false, R >= 16 ? 2 : 3, &nw, false, false, c.sym)) {
         Sink s = slab_sink(c, 1, nullptr, ldq, R);
         const Sink sb = bound_sink(c, R, lo, hi, bstride, n_half);
         s.eps = sb.eps;
@@ -6520,7 +6557,7 @@ int run_stages(const Chunk& c, int pass, int mtop, long R, long Q, long ldq, flo
     if (m == 2 && !c.tape && R >= 16) {
       int nw = 0;
       size_t lds = 0;
-      if (ConvT2Kernel kern = convT2_bound_for(c.net, &nw, &lds)) {
+      if (ConvT2Kernel kern = convT2_bound_for(c.net, c.sym, &nw, &lds)) {
         Sink s = slab_sink(c, 1, nullptr, ldq, R);
         Sink sb = bound_sink(c, R, lo, hi, bstride, n_half);
         s.eps = sb.eps;
@@ -6673,7 +6710,7 @@ int fc_open_stage(const Chunk& c, int k, long R, long Q, long ldq) {
   int nw = 0;
   size_t lds = 0;
   DLayer t = dlayer(cv);
-  WsKernel kern = convT_ws_for(t, c.tape, true, &nw, &lds);
+  WsKernel kern = convT_ws_for(t, c.tape, true, &nw, &lds, c.sym);
   Sink s = slab_sink(c, k - 2, at<float>(c.ws, c.p->off_slab0), ldq, R);
   s.tape = tape_of(c, k, k - 2);
   FcSrc f{};
@@ -6983,13 +7020,13 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
     Sink s = slab_sink(c, k - 1, at<float>(c.ws, c.p->off_slab0), ldq, R);
     s.tape = tape_of(c, k, k - 1);
     const float* wT = c.p->off_wT[k] ? at<float>(c.ws, c.p->off_wT[k]) : nullptr;
+    auto kfc = net->n[k - 1] >= 512 ? (c.sym ? k_init_fc_rows<16, true> : k_init_fc_rows<16, false>)
+                                    : (c.sym ? k_init_fc_rows<4, true> : k_init_fc_rows<4, false>);
     if (int e = launch_k(tag("init_rows", k, k), c.st, [&] {
-          if (wT && net->n[k - 1] >= 512)
-            hipLaunchKernelGGL(k_init_fc_rows<16>, dim3((unsigned)((Q + 63) / 64)), dim3(1024), 0,
-                               c.st, dlayer(net->T[k - 1]), wT, Q, s);
-          else if (wT)
-            hipLaunchKernelGGL(k_init_fc_rows<4>, dim3((unsigned)((Q + 63) / 64)), dim3(256), 0,
-                               c.st, dlayer(net->T[k - 1]), wT, Q, s);
+          if (wT)
+            hipLaunchKernelGGL(kfc, dim3((unsigned)((Q + 63) / 64)),
+                               dim3(net->n[k - 1] >= 512 ? 1024 : 256), 0, c.st,
+                               dlayer(net->T[k - 1]), wT, Q, s);
           else
             hipLaunchKernelGGL(k_init_rows<MODE_SLAB>, grid_for(Q), dim3(kBlock), 0, c.st,
                                dlayer(net->T[k - 1]), wT, Q, s);
