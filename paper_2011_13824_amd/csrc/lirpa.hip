@@ -5621,6 +5621,7 @@ struct Plan {
   size_t off_psel = 0;  // its position pairs of layer-2 tiles per sub-domain
   // split weight fragments of the receptive-field passes (k_win_pass), by layer: T^T, T
   size_t off_fb[kMaxLayers + 1] = {}, off_ff[kMaxLayers + 1] = {};
+  bool fb_sym[kMaxLayers + 1] = {};  // T^T fragments that only passes without given slopes read
   size_t off_wpart = 0, off_wflag = 0;  // their reverse sweep's partial sums and block flags
   long fwd_floats = 0;
   // lower and upper bounds in one call: the spec rows [C; -C] (or -C alone) and, for the bound,
@@ -6038,11 +6039,14 @@ Plan make_plan(const lirpa_net* net, long S, long Bc, int mode = 0, bool split =
     WinLaunch q;
     const bool gw = mode == 1 && win_grad_pass(net, k, split);
     if (!(gw || win_bound_pass(net, k, split, true)) || !win_desc(net, k, gw, &q)) continue;
+    const bool always = gw || win_bound_pass(net, k, split, false);
     for (int m = 1; m < k; ++m) {
       if (!p.off_fb[m]) {
         p.off_fb[m] = o;
         o = align256(o + frag_bytes(net, m, 0));
+        p.fb_sym[m] = true;
       }
+      if (always) p.fb_sym[m] = false;
       if (gw && !p.off_ff[m]) {
         p.off_ff[m] = o;
         o = align256(o + frag_bytes(net, m, 1));
@@ -7124,9 +7128,10 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
 }
 
 // Exact layer-1 bounds, shared by every sub-domain: rows +-e_j of h^(1) through T_1, then
-// concretised (no relaxation in front of layer 1).
+// concretised (no relaxation in front of layer 1).  slopes: every bound of the call is given its
+// lower slopes.
 int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0, float eps,
-                  const float* C, int S, hipStream_t st) {
+                  const float* C, int S, bool slopes, hipStream_t st) {
   long n1 = net->n[1];
   SetupFrags job{};
   job.t1 = dlayer(net->T[0]);
@@ -7176,7 +7181,7 @@ int layer1_bounds(const lirpa_net* net, const Plan& p, void* ws, const float* x0
   for (int m = 1; m <= net->L; ++m)
     for (int kind = 0; kind < 2; ++kind) {
       const size_t off = kind ? p.off_ff[m] : p.off_fb[m];
-      if (!off) continue;
+      if (!off || (kind == 0 && slopes && p.fb_sym[m])) continue;
       FragJob f = frag_job(net, m, kind);
       f.dst = at<uint4v>(ws, off);
       f.blk = (f.nmt * f.nks * 64 + kBlock - 1) / kBlock;
@@ -7678,7 +7683,7 @@ int bound_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float eps
                                l_par, u_par, stream);
       e != 1)
     return e;
-  if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, stream)) return e;
+  if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, alpha != nullptr, stream)) return e;
   for (long b0 = 0; b0 < B; b0 += Bc) {
     Chunk c = make_chunk(net, p, ws, x0, eps, S, B, b0, split, alpha, l_out, u_out, stream);
     if (l_par) {
@@ -7729,7 +7734,7 @@ int optimize_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float 
                  const float* C, int S, int B, const int8_t* split, float* alpha, float* adam_m,
                  float* adam_v, const lirpa_opt_params& op, float* lb_best, float* lb_trace,
                  void* ws, hipStream_t stream) {
-  if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, stream)) return e;
+  if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, !op.fresh, stream)) return e;
   for (long b0 = 0; b0 < B; b0 += Bc) {
     Chunk c = make_chunk(net, p, ws, x0, eps, S, B, b0, split, alpha, nullptr, nullptr, stream);
     long na = c.nb * net->n_relu, ns = c.nb * S;
@@ -7795,7 +7800,7 @@ int bound_ul_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float 
                              (long)S * nL, C, C2, 1);
         }))
       return e;
-    if (int e = layer1_bounds(net, p, ws, x0, eps, C2, 2 * S, stream)) return e;
+    if (int e = layer1_bounds(net, p, ws, x0, eps, C2, 2 * S, alpha != nullptr, stream)) return e;
   }
   float* lb2 = at<float>(ws, p.off_lb2);
   for (long b0 = 0; b0 < B; b0 += Bc) {
@@ -8172,7 +8177,7 @@ int lirpa_bound_grad(lirpa_net* net, const float* x0, float eps, const float* C,
                 make_plan(net, S, 1, 1).total);
   if (int e = validate_report(stream)) return e;
   if (int e = validate_enqueue(net, x0, C, S, B, split, alpha, stream)) return e;
-  if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, stream)) return e;
+  if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, true, stream)) return e;
   for (long b0 = 0; b0 < B; b0 += Bc) {
     Chunk c = make_chunk(net, p, ws, x0, eps, S, B, b0, split, alpha, nullptr, nullptr, stream);
     if (int e = bound_chunk(c, C, lb + b0 * S)) return e;
