@@ -119,7 +119,8 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
   // M tiles dealt to the waves; with fewer tiles than waves, nw / nmt waves share a tile's columns
   const int share = nw / c.nmt > 1 ? nw / c.nmt : 1;
   const int mt0 = wave / share, xs0 = wave - mt0 * share, mstep = (nw + share - 1) / share;
-  float beta = 0.f, lin = 0.f, l1 = 0.f, gap = 0.f;
+  RowBias<SYM> rb;
+  float lin = 0.f, l1 = 0.f;
   uint4v A[KS ? KS : 1][3];
   int cur = -1;
   for (int ay = 0; ay < nay; ++ay) {
@@ -175,10 +176,8 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
           const unsigned idx = i[r] * ldq + q;
           if constexpr (MODE == MODE_SLAB) {
             if (s.tape) s.tape[idx] = a;
-            const float ah = a * (a >= 0.f ? lo[r] : up[r]);
-            beta = fmaf(fminf(a, 0.f), bu[r], beta);
-            beta = fmaf(ah, bz[r], beta);
-            if constexpr (SYM) gap = fmaf(fabsf(a), bu[r], gap);
+            const float ah = a * rb.slope(a, lo[r], up[r]);
+            rb.add(a, fminf(a, 0.f), ah, bu[r], bz[r]);
             s.out[idx] = ah;
           } else {
             if (s.tsign) s.tsign[idx] = sign8(a);
@@ -191,9 +190,11 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     park(ay + 1);
     __syncthreads();
   }
+  float beta = rb.lo(), up = 0.f;
   if constexpr (SYM) {
-    gap += __shfl_xor(gap, 16, 64);
-    gap += __shfl_xor(gap, 32, 64);
+    up = rb.up();
+    up += __shfl_xor(up, 16, 64);
+    up += __shfl_xor(up, 32, 64);
   }
   beta += __shfl_xor(beta, 16, 64);
   lin += __shfl_xor(lin, 16, 64);
@@ -205,7 +206,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     red[(wave * 4 + 0) * 16 + lane] = beta;
     red[(wave * 4 + 1) * 16 + lane] = lin;
     red[(wave * 4 + 2) * 16 + lane] = l1;
-    if constexpr (SYM) red[(wave * 4 + 3) * 16 + lane] = gap;
+    if constexpr (SYM) red[(wave * 4 + 3) * 16 + lane] = up;
   }
   __syncthreads();
   if (tid >= 16 || !qok) return;
@@ -214,7 +215,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     tot.beta += red[(w * 4 + 0) * 16 + tid];
     tot.lin += red[(w * 4 + 1) * 16 + tid];
     tot.l1 += red[(w * 4 + 2) * 16 + tid];
-    if constexpr (SYM) tot.gap += red[(w * 4 + 3) * 16 + tid];
+    if constexpr (SYM) tot.up += red[(w * 4 + 3) * 16 + tid];
   }
   sink_finish<MODE>(s, tot, q, b, q % (unsigned)s.R, false);
 }

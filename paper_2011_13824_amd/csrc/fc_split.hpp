@@ -47,13 +47,14 @@ __global__ void __launch_bounds__(kFcThreads)
   unsigned qn[NT];
   bool qok[NT];
   long pb[NT];
-  float beta[NT], lin[NT], l1[NT], gap[NT];
+  RowBias<SYM> rb[NT];
+  float lin[NT], l1[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     qn[t] = q0 + 16 * t + n;
     qok[t] = qn[t] < Q;
     pb[t] = (long)(qok[t] ? qn[t] / (unsigned)s.R : 0u) * s.pstride;
-    beta[t] = lin[t] = l1[t] = gap[t] = 0.f;
+    lin[t] = l1[t] = 0.f;
   }
   const char* bp = fsm + n * 16;
   for (int mp = wave; 2 * mp < c.nmt; mp += NW) {
@@ -125,10 +126,8 @@ __global__ void __launch_bounds__(kFcThreads)
           const size_t idx = (size_t)(unsigned)(i0 + r) * ldq + qn[t];
           if constexpr (MODE == MODE_SLAB) {
             if (s.tape) s.tape[idx] = a;
-            const float ah = a * (a >= 0.f ? pl[r] : pu[r]);
-            beta[t] = fmaf(fminf(a, 0.f), pc[r], beta[t]);
-            beta[t] = fmaf(ah, pz[r], beta[t]);
-            if constexpr (SYM) gap[t] = fmaf(fabsf(a), pc[r], gap[t]);
+            const float ah = a * rb[t].slope(a, pl[r], pu[r]);
+            rb[t].add(a, fminf(a, 0.f), ah, pc[r], pz[r]);
             s.out[idx] = ah;
           } else {
             if (s.tsign) s.tsign[idx] = sign8(a);
@@ -141,7 +140,7 @@ __global__ void __launch_bounds__(kFcThreads)
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    float v[4] = {beta[t], lin[t], l1[t], gap[t]};
+    float v[4] = {rb[t].lo(), lin[t], l1[t], rb[t].up()};
 #pragma unroll
     for (int e = 0; e < (SYM ? 4 : 3); ++e) {
       v[e] += __shfl_xor(v[e], 16, 64);
@@ -157,7 +156,7 @@ __global__ void __launch_bounds__(kFcThreads)
     tot.beta += red[(w * 4 + 0) * NQ + tid];
     tot.lin += red[(w * 4 + 1) * NQ + tid];
     tot.l1 += red[(w * 4 + 2) * NQ + tid];
-    if constexpr (SYM) tot.gap += red[(w * 4 + 3) * NQ + tid];
+    if constexpr (SYM) tot.up += red[(w * 4 + 3) * NQ + tid];
   }
   sink_finish<MODE>(s, tot, q, q / (unsigned)s.R, q % (unsigned)s.R, false);
 }

@@ -216,9 +216,10 @@ struct Sink {
   const float* x0;
   float eps;
   float* beta;  // running bias of each row, [Qp]
-  // one row per neuron (a pass without given slopes, whose row -e_j is the negative of +e_j):
-  // the running gap sum |a| b_up of each row; the row then gives lo and hi.  Else null.
-  float* gap;
+  // one row per neuron (a pass without given slopes, whose row -e_j is the negative of +e_j): the
+  // running bias of the upper bound, with the intercepts of the positive coefficients where beta
+  // has those of the negative ones (RowBias); the row then gives lo and hi.  Else null.
+  float* up;
   long R;       // rows per sub-domain
   float* lo;
   float* hi;
@@ -263,7 +264,34 @@ struct FcSrc {
 };
 
 struct Acc {
-  float beta, lin, l1, gap = 0.f;
+  float beta, lin, l1, up = 0.f;
+};
+
+// A row's bias terms over the entries it relaxes: intercepts of the negative coefficients and the
+// constants.  SYM (one row per neuron): the upper bound's as well, which has the intercepts of the
+// positive coefficients.  Each sign has a sum of its own: an upper bias taken as the lower one and
+// sum |a| b_up would cancel the negative intercepts, to rounding (boxes five times the usual
+// radius, 2-norm error of u against 64 bits: 784-256-256-10 net 1.35e-7, here 0.64e-7; the
+// four-convolution net 1.28e-7 and 0.63e-7) and to NaN where they overflow.  The slope of an entry
+// needs no sign there: without given slopes the two are the same.
+template <bool SYM>
+struct RowBias {
+  float beta = 0.f, neg = 0.f, pos = 0.f;  // (not SYM: beta with the intercepts)
+  // a before relaxation, an its negative part, ah after; intercept and constant of the entry
+  __device__ __forceinline__ void add(float a, float an, float ah, float bu, float bz) {
+    if constexpr (SYM) {
+      neg = fmaf(an, bu, neg);
+      pos = fmaf(fmaxf(a, 0.f), bu, pos);
+    } else {
+      beta = fmaf(an, bu, beta);
+    }
+    beta = fmaf(ah, bz, beta);
+  }
+  static __device__ __forceinline__ float slope(float a, float a_lo, float a_up) {
+    return !SYM && a >= 0.f ? a_lo : a_up;
+  }
+  __device__ __forceinline__ float lo() const { return SYM ? beta + neg : beta; }
+  __device__ __forceinline__ float up() const { return beta + pos; }
 };
 
 template <int MODE>
@@ -283,8 +311,12 @@ __device__ __forceinline__ void sink_put(const Sink& s, Acc& acc, long i, float 
       acc.beta = fmaf(a, s.b_up[pi], acc.beta);
       ah = a * s.a_up[pi];
     }
-    if (s.gap) acc.gap = fmaf(fabsf(a), s.b_up[pi], acc.gap);
-    acc.beta = fmaf(ah, s.bias[(unsigned)i / (unsigned)s.bias_hw], acc.beta);
+    const float bz = s.bias[(unsigned)i / (unsigned)s.bias_hw];
+    acc.beta = fmaf(ah, bz, acc.beta);
+    if (s.up) {
+      acc.up = fmaf(fmaxf(a, 0.f), s.b_up[pi], acc.up);
+      acc.up = fmaf(ah, bz, acc.up);
+    }
     s.out[i * s.ldq + q] = ah;
   } else {
     if (s.x0) acc.lin = fmaf(a, s.x0[i], acc.lin);
@@ -298,14 +330,14 @@ __device__ __forceinline__ void sink_finish(const Sink& s, const Acc& acc, long 
                                             bool first) {
   if constexpr (MODE == MODE_SLAB) {
     s.beta[q] = first ? acc.beta : s.beta[q] + acc.beta;
-    if (s.gap) s.gap[q] = first ? acc.gap : s.gap[q] + acc.gap;
+    if (s.up) s.up[q] = first ? acc.up : s.up[q] + acc.up;
   } else {
     float beta = first ? acc.beta : s.beta[q] + acc.beta;
     float v = acc.lin - s.eps * acc.l1 + beta;
-    if (s.gap) {
-      const float g = first ? acc.gap : s.gap[q] + acc.gap;
+    if (s.up) {
+      const float up = first ? acc.up : s.up[q] + acc.up;
       s.lo[b * s.bstride + r] = v;
-      s.hi[b * s.bstride + r] = acc.lin + s.eps * acc.l1 + (beta + g);
+      s.hi[b * s.bstride + r] = acc.lin + s.eps * acc.l1 + up;
       return;
     }
     if (r < s.n_half)
@@ -361,7 +393,7 @@ __device__ __forceinline__ void init_row(const DLayer& t, const float* __restric
   long j = r % nk;
   float sgn = r < nk ? 1.f : -1.f;
   int hw = t.out_h * t.out_w;
-  Acc acc{sgn * t.b[j / hw], 0.f, 0.f};
+  Acc acc{sgn * t.b[j / hw], 0.f, 0.f, sgn * t.b[j / hw]};
   if (t.kind == LIRPA_LINEAR) {
     if (WT)
       for (int i = 0; i < t.in_c; ++i)
@@ -429,7 +461,7 @@ __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float*
   const int i0 = w * chunk, i1 = min(nin, i0 + chunk);
   const long pb = b * s.pstride;
   const unsigned hw = (unsigned)s.bias_hw;
-  float beta = 0.f, gap = 0.f;
+  RowBias<SYM> rb;
   if (ok) {
     int i = i0;
     for (; i + 4 <= i1; i += 4) {
@@ -441,10 +473,8 @@ __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float*
         const float a = sgn * WT[(long)(i + u) * nk + j];
         const long idx = (long)(i + u) * s.ldq + q;
         if (s.tape) s.tape[idx] = a;
-        const float ah = a >= 0.f ? a * lo[u] : a * up[u];
-        beta = fmaf(fminf(a, 0.f), bu[u], beta);
-        if constexpr (SYM) gap = fmaf(fabsf(a), bu[u], gap);
-        beta = fmaf(ah, s.bias[(unsigned)(i + u) / hw], beta);
+        const float ah = a * rb.slope(a, lo[u], up[u]);
+        rb.add(a, fminf(a, 0.f), ah, bu[u], s.bias[(unsigned)(i + u) / hw]);
         s.out[idx] = ah;
       }
     }
@@ -452,24 +482,22 @@ __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float*
       const float a = sgn * WT[(long)i * nk + j];
       const long idx = (long)i * s.ldq + q;
       if (s.tape) s.tape[idx] = a;
-      const float ah = a >= 0.f ? a * s.a_lo[pb + i] : a * s.a_up[pb + i];
-      beta = fmaf(fminf(a, 0.f), s.b_up[pb + i], beta);
-      if constexpr (SYM) gap = fmaf(fabsf(a), s.b_up[pb + i], gap);
-      beta = fmaf(ah, s.bias[(unsigned)i / hw], beta);
+      const float ah = a * rb.slope(a, s.a_lo[pb + i], s.a_up[pb + i]);
+      rb.add(a, fminf(a, 0.f), ah, s.b_up[pb + i], s.bias[(unsigned)i / hw]);
       s.out[idx] = ah;
     }
   }
-  red[0][w][lane] = beta;
-  if constexpr (SYM) red[1][w][lane] = gap;
+  red[0][w][lane] = rb.lo();
+  if constexpr (SYM) red[1][w][lane] = rb.up();
   __syncthreads();
   if (w == 0 && ok) {
     float tb = red[0][0][lane];
     for (int e = 1; e < NW; ++e) tb += red[0][e][lane];
     s.beta[q] = sgn * t.b[j] + tb;
     if constexpr (SYM) {
-      float tg = red[1][0][lane];
-      for (int e = 1; e < NW; ++e) tg += red[1][e][lane];
-      s.gap[q] = tg;
+      float tu = red[1][0][lane];
+      for (int e = 1; e < NW; ++e) tu += red[1][e][lane];
+      s.up[q] = sgn * t.b[j] + tu;
     }
   }
 }
@@ -691,12 +719,12 @@ __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red,
   acc.beta += __shfl_xor(acc.beta, 32, 64);
   acc.lin += __shfl_xor(acc.lin, 32, 64);
   acc.l1 += __shfl_xor(acc.l1, 32, 64);
-  if constexpr (SYM) acc.gap += __shfl_xor(acc.gap, 32, 64);
+  if constexpr (SYM) acc.up += __shfl_xor(acc.up, 32, 64);
   if (lane < 32) {
     red[(wave * 4 + 0) * 32 + lane] = acc.beta;
     red[(wave * 4 + 1) * 32 + lane] = acc.lin;
     red[(wave * 4 + 2) * 32 + lane] = acc.l1;
-    if constexpr (SYM) red[(wave * 4 + 3) * 32 + lane] = acc.gap;
+    if constexpr (SYM) red[(wave * 4 + 3) * 32 + lane] = acc.up;
   }
   __syncthreads();
   if (wave != 0 || lane >= 32) return;
@@ -707,7 +735,7 @@ __device__ __forceinline__ void block_finish(const Sink& s, Acc acc, float* red,
     t.beta += red[(w * 4 + 0) * 32 + lane];
     t.lin += red[(w * 4 + 1) * 32 + lane];
     t.l1 += red[(w * 4 + 2) * 32 + lane];
-    if constexpr (SYM) t.gap += red[(w * 4 + 3) * 32 + lane];
+    if constexpr (SYM) t.up += red[(w * 4 + 3) * 32 + lane];
   }
   (void)add_beta_from_acc;
   sink_finish<MODE>(s, t, q, q / s.R, q % s.R, false);
@@ -784,7 +812,8 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
     }
   }
 
-  float beta = 0.f, lin = 0.f, l1 = 0.f, gap = 0.f;
+  RowBias<SYM> rb;
+  float lin = 0.f, l1 = 0.f;
   // Relaxation parameters of one output row (MODE_SLAB): loaded before the MFMAs of the step
   // that completes the row, so their latency hides behind the matrix work.
   constexpr int NQ = W0 / 4;
@@ -846,10 +875,8 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
           const float a = vals[4 * i + j];
           const unsigned idx = (rowi + 4 * i + j) * ldq + q;
           if constexpr (TAPE) s.tape[idx] = a;
-          const float ah = a >= 0.f ? a * lo[j] : a * up[j];
-          beta = fmaf(fminf(a, 0.f), bu[j], beta);
-          beta = fmaf(ah, bz[j], beta);
-          if constexpr (SYM) gap = fmaf(fabsf(a), bu[j], gap);
+          const float ah = a * rb.slope(a, lo[j], up[j]);
+          rb.add(a, fminf(a, 0.f), ah, bu[j], bz[j]);
           s.out[idx] = ah;
         }
       }
@@ -1033,9 +1060,11 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
   }
 
   // sum over lane groups and waves, then finish rows q0..q0+15
+  float beta = rb.lo(), up = 0.f;
   if constexpr (SYM) {
-    gap += __shfl_xor(gap, 16, 64);
-    gap += __shfl_xor(gap, 32, 64);
+    up = rb.up();
+    up += __shfl_xor(up, 16, 64);
+    up += __shfl_xor(up, 32, 64);
   }
   beta += __shfl_xor(beta, 16, 64);
   lin += __shfl_xor(lin, 16, 64);
@@ -1048,7 +1077,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
     red[(wave * 4 + 0) * 16 + lane] = beta;
     red[(wave * 4 + 1) * 16 + lane] = lin;
     red[(wave * 4 + 2) * 16 + lane] = l1;
-    if constexpr (SYM) red[(wave * 4 + 3) * 16 + lane] = gap;
+    if constexpr (SYM) red[(wave * 4 + 3) * 16 + lane] = up;
   }
   __syncthreads();
   if (wave != 0 || lane >= 16 || !qok) return;
@@ -1057,7 +1086,7 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
     tot.beta += red[(w * 4 + 0) * 16 + lane];
     tot.lin += red[(w * 4 + 1) * 16 + lane];
     tot.l1 += red[(w * 4 + 2) * 16 + lane];
-    if constexpr (SYM) tot.gap += red[(w * 4 + 3) * 16 + lane];
+    if constexpr (SYM) tot.up += red[(w * 4 + 3) * 16 + lane];
   }
   sink_finish<MODE>(s, tot, q, b, q % (unsigned)s.R, false);
 }
@@ -1233,7 +1262,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
     int g_lds[TPL];
     bool g_on[TPL];
     float4v g_xa[TPL], g_xb[TPL], g_lo[TPL], g_up[TPL], g_bu[TPL];
-    float fbeta_a = 0.f, fbeta_b = 0.f, fgap_a = 0.f, fgap_b = 0.f;
+    RowBias<SYM> fa, fb;
     if constexpr (FC) {
       const unsigned nin = CO * H1 * W1, nk = (unsigned)fc.nk;
 #pragma unroll
@@ -1276,16 +1305,10 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float a = g_sa[k] * g_xa[k][e], b = g_sb[k] * g_xb[k][e];
-            const float ha = a * (a >= 0.f ? g_lo[k][e] : g_up[k][e]);
-            const float hb = b * (b >= 0.f ? g_lo[k][e] : g_up[k][e]);
-            fbeta_a = fmaf(fminf(a, 0.f), g_bu[k][e], fbeta_a);
-            fbeta_a = fmaf(ha, g_bz[k], fbeta_a);
-            fbeta_b = fmaf(fminf(b, 0.f), g_bu[k][e], fbeta_b);
-            fbeta_b = fmaf(hb, g_bz[k], fbeta_b);
-            if constexpr (SYM) {
-              fgap_a = fmaf(fabsf(a), g_bu[k][e], fgap_a);
-              fgap_b = fmaf(fabsf(b), g_bu[k][e], fgap_b);
-            }
+            const float ha = a * fa.slope(a, g_lo[k][e], g_up[k][e]);
+            const float hb = b * fb.slope(b, g_lo[k][e], g_up[k][e]);
+            fa.add(a, fminf(a, 0.f), ha, g_bu[k][e], g_bz[k]);
+            fb.add(b, fminf(b, 0.f), hb, g_bu[k][e], g_bz[k]);
             *reinterpret_cast<float2v*>(buf + g_lds[k] + e * CO * 16) = float2v{ha, hb};
           }
         }
@@ -1381,21 +1404,26 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
     lds_barrier();
     if constexpr (FC) {
       // rows 2 qp, 2 qp + 1 of every task of this wave: lanes qp, qp + 8, ..., qp + 56
+      float fbeta_a = fa.lo(), fbeta_b = fb.lo(), fup_a = 0.f, fup_b = 0.f;
+      if constexpr (SYM) {
+        fup_a = fa.up();
+        fup_b = fb.up();
+      }
 #pragma unroll
       for (int o = 8; o < 64; o <<= 1) {
         fbeta_a += __shfl_xor(fbeta_a, o, 64);
         fbeta_b += __shfl_xor(fbeta_b, o, 64);
         if constexpr (SYM) {
-          fgap_a += __shfl_xor(fgap_a, o, 64);
-          fgap_b += __shfl_xor(fgap_b, o, 64);
+          fup_a += __shfl_xor(fup_a, o, 64);
+          fup_b += __shfl_xor(fup_b, o, 64);
         }
       }
       if (lane < 8) {
         red_fc[wave * 16 + 2 * lane] = fbeta_a;
         red_fc[wave * 16 + 2 * lane + 1] = fbeta_b;
         if constexpr (SYM) {
-          gred_fc[wave * 16 + 2 * lane] = fgap_a;
-          gred_fc[wave * 16 + 2 * lane + 1] = fgap_b;
+          gred_fc[wave * 16 + 2 * lane] = fup_a;
+          gred_fc[wave * 16 + 2 * lane + 1] = fup_b;
         }
       }
     }
@@ -1413,7 +1441,7 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   // past Q are stored too (never read as results) and the stores need no lane mask.  A store
   // address is a block-uniform row base plus this lane's 32-bit byte offset.
   const unsigned lane_boff = (4u * xg * ldq + qn) * 4u;
-  float beta = 0.f, gap = 0.f;
+  RowBias<SYM> rb;
   auto stage = [&](int e) {
     const int slot = e & 1;
     const float* pst = pars[e % 3];
@@ -1435,10 +1463,8 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
         const size_t base = (size_t)(row0 + j) * ldq + q0;  // uniform
         if constexpr (TAPE) store_row(s.tape + base, lane_boff, a[j]);
         const bool pos = a[j] >= 0.f;
-        const float ah = a[j] * (pos ? lo[j] : up[j]);
-        beta = fmaf(pos ? 0.f : a[j], bu[j], beta);
-        beta = fmaf(ah, bz[j], beta);
-        if constexpr (SYM) gap = fmaf(fabsf(a[j]), bu[j], gap);
+        const float ah = a[j] * (!SYM && pos ? lo[j] : up[j]);
+        rb.add(a[j], pos ? 0.f : a[j], ah, bu[j], bz[j]);
         store_row(s.out + base, lane_boff, ah);
       }
     }
@@ -1451,12 +1477,14 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   stage(H1 - 1);
   lds_barrier();
   stage(H1);
+  float beta = rb.lo();
   beta += __shfl_xor(beta, 16, 64);
   beta += __shfl_xor(beta, 32, 64);
   if constexpr (SYM) {
-    gap += __shfl_xor(gap, 16, 64);
-    gap += __shfl_xor(gap, 32, 64);
-    if (lane < 16) gred[ws * 16 + lane] = gap;
+    float up = rb.up();
+    up += __shfl_xor(up, 16, 64);
+    up += __shfl_xor(up, 32, 64);
+    if (lane < 16) gred[ws * 16 + lane] = up;
   }
   if (lane < 16) red[ws * 16 + lane] = beta;
   lds_barrier();
@@ -1468,11 +1496,13 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   if constexpr (FC) {
     // the rows' own bias +-b_k[j] and the terms of the relaxation that built them
     const unsigned r = q % R, nk = (unsigned)fc.nk;
-    float fb = r < nk ? fc.b[r] : -fc.b[r - nk];
+    float fb = r < nk ? fc.b[r] : -fc.b[r - nk], fu = fb;
     for (int w = 0; w < NM; ++w) fb += red_fc[w * 16 + lane];
     tot += fb;
-    if constexpr (SYM)
-      for (int w = 0; w < NM; ++w) tg += gred_fc[w * 16 + lane];
+    if constexpr (SYM) {
+      for (int w = 0; w < NM; ++w) fu += gred_fc[w * 16 + lane];
+      tg += fu;
+    }
   }
   Acc a{tot, 0.f, 0.f, tg};
   sink_finish<MODE_SLAB>(s, a, q, q / R, q % R, FC);
@@ -1665,7 +1695,7 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
     const unsigned q = q0 + qn;
     const bool qok = q < Q;
     const int bsel = qok ? (int)(q / R - b0) : 0;
-    float beta = 0.f, gap = 0.f;
+    RowBias<SYM> rb;
     auto stage = [&](int e) {
       float* slot = ring + (e % 3) * SLOT;
       const float* pslot = pars + (e & 1) * PB;
@@ -1686,12 +1716,8 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
           const int x = 4 * xg + j;
           const float a = row[x * 16];
           const bool pos = a >= 0.f;
-          const float ah = a * (pos ? lo[j] : up[j]);
-          if (qok) {
-            beta = fmaf(pos ? 0.f : a, bu[j], beta);
-            beta = fmaf(ah, bz[j], beta);
-            if constexpr (SYM) gap = fmaf(fabsf(a), bu[j], gap);
-          }
+          const float ah = a * (!SYM && pos ? lo[j] : up[j]);
+          if (qok) rb.add(a, pos ? 0.f : a, ah, bu[j], bz[j]);
           row[x * 16] = ah;
         }
       }
@@ -1701,13 +1727,15 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
       if (st >= 1 && st <= H1 + 1) stage(st - 1);
       lds_barrier();
     }
+    float beta = rb.lo();
     beta += __shfl_xor(beta, 16, 64);
     beta += __shfl_xor(beta, 32, 64);
     if (lane < 16) red[ws * 16 + lane] = beta;
     if constexpr (SYM) {
-      gap += __shfl_xor(gap, 16, 64);
-      gap += __shfl_xor(gap, 32, 64);
-      if (lane < 16) red[(NS + C0 + ws) * 16 + lane] = gap;
+      float up = rb.up();
+      up += __shfl_xor(up, 16, 64);
+      up += __shfl_xor(up, 32, 64);
+      if (lane < 16) red[(NS + C0 + ws) * 16 + lane] = up;
     }
     lds_barrier();
     return;
@@ -1835,9 +1863,9 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
 // padded width ldq, and hold zeros).
 // SYM (FC source, bounds without given slopes): every neuron's lower slope is its upper slope, so
 // the row -e_j is the negative of the row +e_j all the way down.  A row q is then +e_j alone
-// (R = n_k rows per sub-domain, even) and gives both bounds: with gap = sum |a| b_up over the
-// entries it relaxes, l = beta - eps ||A_x||_1 and u = beta + gap + eps ||A_x||_1 (the negated
-// row's intercepts are those of the positive entries).  Half the rows of a bound: the
+// (R = n_k rows per sub-domain, even) and gives both bounds: l = beta - eps ||A_x||_1 and
+// u = up + eps ||A_x||_1, up with the intercepts of the positive entries (those of the negated
+// row) instead of the negative ones' (RowBias).  Half the rows of a bound: the
 // pass of 400 sub-domains of the 8-16-channel net 0.440 -> 0.231 ms, of 1,024 of the
 // 16-32-channel net 2.84 -> 1.53.
 template <int K, int S, int P, int H1, int W1, int H0, int W0, int CO, int CI, int CPW, int K1,
@@ -1889,7 +1917,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   __shared__ float ring[2][SLOT];
   __shared__ float4v pars[2][PSLOT4];
   __shared__ float red[NM * 16 + 2 * NXW * 16 + (SYM ? (NM + NXW) * 16 : 0)];
-  float* gred = red + NM * 16 + 2 * NXW * 16;  // SYM: the gaps, matrix waves then x waves
+  float* gred = red + NM * 16 + 2 * NXW * 16;  // SYM: the upper biases, matrix waves then x waves
   // spec source: the block's rows relaxed onto layer L-1, the MFMA B operand [4 SPEC][16 rows]
   __shared__ float vts[SPEC > 0 ? SPEC * 64 : 1];
   // border exchange of the x waves (see there): [step parity][wave - 1][channel, column][lane]
@@ -1984,7 +2012,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     int g_lds[TPL];
     bool g_on[TPL];
     float4v g_xa[TPL], g_xb[TPL], g_lo[TPL], g_up[TPL], g_bu[TPL];
-    float fbeta_a = 0.f, fbeta_b = 0.f, fgap_a = 0.f, fgap_b = 0.f;
+    RowBias<SYM> fa, fb;
     if constexpr (FC) {
       const unsigned nin = CO * H1 * W1, nk = (unsigned)fc.nk;
 #pragma unroll
@@ -2027,16 +2055,10 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float a = g_sa[k] * g_xa[k][e], b = g_sb[k] * g_xb[k][e];
-            const float ha = a * (a >= 0.f ? g_lo[k][e] : g_up[k][e]);
-            const float hb = b * (b >= 0.f ? g_lo[k][e] : g_up[k][e]);
-            fbeta_a = fmaf(fminf(a, 0.f), g_bu[k][e], fbeta_a);
-            fbeta_a = fmaf(ha, g_bz[k], fbeta_a);
-            fbeta_b = fmaf(fminf(b, 0.f), g_bu[k][e], fbeta_b);
-            fbeta_b = fmaf(hb, g_bz[k], fbeta_b);
-            if constexpr (SYM) {
-              fgap_a = fmaf(fabsf(a), g_bu[k][e], fgap_a);
-              fgap_b = fmaf(fabsf(b), g_bu[k][e], fgap_b);
-            }
+            const float ha = a * fa.slope(a, g_lo[k][e], g_up[k][e]);
+            const float hb = b * fb.slope(b, g_lo[k][e], g_up[k][e]);
+            fa.add(a, fminf(a, 0.f), ha, g_bu[k][e], g_bz[k]);
+            fb.add(b, fminf(b, 0.f), hb, g_bu[k][e], g_bz[k]);
             *reinterpret_cast<float2v*>(buf + g_lds[k] + e * CO * 16) = float2v{ha, hb};
           }
         }
@@ -2220,21 +2242,26 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     lds_barrier();  // step H1 + 1
     if constexpr (FC) {
       // rows 2 qp, 2 qp + 1 of every task of this wave: lanes qp, qp + 8, ..., qp + 56
+      float fbeta_a = fa.lo(), fbeta_b = fb.lo(), fup_a = 0.f, fup_b = 0.f;
+      if constexpr (SYM) {
+        fup_a = fa.up();
+        fup_b = fb.up();
+      }
 #pragma unroll
       for (int o = 8; o < 64; o <<= 1) {
         fbeta_a += __shfl_xor(fbeta_a, o, 64);
         fbeta_b += __shfl_xor(fbeta_b, o, 64);
         if constexpr (SYM) {
-          fgap_a += __shfl_xor(fgap_a, o, 64);
-          fgap_b += __shfl_xor(fgap_b, o, 64);
+          fup_a += __shfl_xor(fup_a, o, 64);
+          fup_b += __shfl_xor(fup_b, o, 64);
         }
       }
       if (lane < 8) {
         red[wave * 16 + 2 * lane] = fbeta_a;
         red[wave * 16 + 2 * lane + 1] = fbeta_b;
         if constexpr (SYM) {
-          gred[wave * 16 + 2 * lane] = fgap_a;
-          gred[wave * 16 + 2 * lane + 1] = fgap_b;
+          gred[wave * 16 + 2 * lane] = fup_a;
+          gred[wave * 16 + 2 * lane + 1] = fup_b;
         }
       }
     }
@@ -2307,7 +2334,8 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     if (x >= S1 && (x - S1) / K1 < NF) v += od[c0][(x - S1) / K1][(x - S1) % K1];
     return v;
   };
-  float l1 = 0.f, beta = 0.f, gap = 0.f;
+  float l1 = 0.f;
+  RowBias<SYM> rb;
   float pend[C0 * NSH];  // right shared columns of the pending row
   bool pend_ok = false;
   int pend_y = 0;
@@ -2404,10 +2432,8 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
       for (int ks = 0; ks < KS1; ++ks) {
         const float a = an[x1 & 1][ks];
         const float4v p = pn[x1 & 1][ks];
-        const float ah = a * (a >= 0.f ? p[0] : p[1]);
-        beta = fmaf(fminf(a, 0.f), p[2], beta);
-        beta = fmaf(ah, p[3], beta);
-        if constexpr (SYM) gap = fmaf(fabsf(a), p[2], gap);
+        const float ah = a * rb.slope(a, p[0], p[1]);
+        rb.add(a, fminf(a, 0.f), ah, p[2], p[3]);
         hn[ks] = ah;
       }
     };
@@ -2467,6 +2493,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   resolve(NSTEP & 1);
   l1 += __shfl_xor(l1, 16, 64);
   l1 += __shfl_xor(l1, 32, 64);
+  float beta = rb.lo();
   beta += __shfl_xor(beta, 16, 64);
   beta += __shfl_xor(beta, 32, 64);
   if (lane < 16) {
@@ -2474,9 +2501,10 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     red[NM * 16 + (NXW + XB) * 16 + lane] = l1;
   }
   if constexpr (SYM) {
-    gap += __shfl_xor(gap, 16, 64);
-    gap += __shfl_xor(gap, 32, 64);
-    if (lane < 16) gred[(NM + XB) * 16 + lane] = gap;
+    float up = rb.up();
+    up += __shfl_xor(up, 16, 64);
+    up += __shfl_xor(up, 32, 64);
+    if (lane < 16) gred[(NM + XB) * 16 + lane] = up;
   }
   };
   if (xw == 0) xrun(std::integral_constant<int, 0>());
@@ -2505,9 +2533,9 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     const float v = tb - s.eps * ta;
     float uv;
     if constexpr (SYM) {
-      float gs = 0.f;
-      for (int w = 0; w < NM + NXW; ++w) gs += gred[w * 16 + lane];
-      uv = (tb + gs) + s.eps * ta;
+      float tu = fc.b[r];
+      for (int w = 0; w < NM + NXW; ++w) tu += gred[w * 16 + lane];
+      uv = tu + s.eps * ta;
       if (q >= Q) return;
     } else {
       uv = -__shfl_xor(v, 1, 64);
@@ -2694,7 +2722,7 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) - (SYM ? 1 : 0) 
     __syncthreads();
     if (xi + 1 < XW) pfetch(X1 + t2.stride);
     {
-      float bpart = 0.f, gpart = 0.f;
+      float bpart = 0.f, npart = 0.f, upart = 0.f;  // (SYM: intercepts apart, see RowBias)
 #pragma unroll
       for (int k = 0; k < NEP; ++k) {
         // (no early exit: the loop unrolls, so the arrays are indexed statically)
@@ -2702,15 +2730,19 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) - (SYM ? 1 : 0) 
         if (k + 1 < NEP || e < NE) {  // (only the last k can fall past NE)
           const float4v pr = prm[e];
           const float v = fmaf(wp[k], pr[0], wn[k] * pr[1]);
-          bpart = fmaf(wn[k], pr[2], bpart);
-          if constexpr (SYM) gpart = fmaf(wp[k] - wn[k], pr[2], gpart);
+          if constexpr (SYM) {
+            npart = fmaf(wn[k], pr[2], npart);
+            upart = fmaf(wp[k], pr[2], upart);
+          } else {
+            bpart = fmaf(wn[k], pr[2], bpart);
+          }
           // layer-1 bias and the linear term of the concretisation together: v (W1 x0 + b1)
           bpart = fmaf(v, pr[3], bpart);
           tile[toff[k % TP] + (k / TP) * TS * CS] = v;
         }
       }
-      bred[part * 16 + row] = bpart;
-      if constexpr (SYM) bred[(RPT + part) * 16 + row] = gpart;
+      bred[part * 16 + row] = SYM ? bpart + npart : bpart;
+      if constexpr (SYM) bred[(RPT + part) * 16 + row] = bpart + upart;
     }
     __syncthreads();
 
@@ -2782,9 +2814,9 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) - (SYM ? 1 : 0) 
       for (int q = 0; q < RPT; ++q) tb += bred[q * 16 + r];
       vb[xi][r] = tb - eps * ta;
       if constexpr (SYM) {
-        float gs = 0.f;
-        for (int q = 0; q < RPT; ++q) gs += bred[(RPT + q) * 16 + r];
-        vb[xi][16 + r] = (tb + gs) + eps * ta;
+        float tu = t2.b[pr.c2];
+        for (int q = 0; q < RPT; ++q) tu += bred[(RPT + q) * 16 + r];
+        vb[xi][16 + r] = tu + eps * ta;
       }
     }
   }
@@ -3654,6 +3686,7 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
   }
   __syncthreads();
   Acc sum{0.f, 0.f, 0.f};
+  RowBias<SYM> rb;
   const int KS = (nout + 1) / 2;
   constexpr int U = NWAVE > 8 ? 8 : 16;
   for (int mt = wave; mt * 32 < nin; mt += nw) {
@@ -3722,10 +3755,8 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
             if (s.tsign) s.tsign[(long)i * s.ldq + q] = sign8(a);
           }
           if constexpr (MODE == MODE_SLAB) {
-            const float ah = a * (a >= 0.f ? p0[g][e] : p1[g][e]);
-            sum.beta = fmaf(fminf(a, 0.f), p2[g][e], sum.beta);
-            sum.beta = fmaf(ah, p3[g][e], sum.beta);
-            if constexpr (SYM) sum.gap = fmaf(fabsf(a), p2[g][e], sum.gap);
+            const float ah = a * rb.slope(a, p0[g][e], p1[g][e]);
+            rb.add(a, fminf(a, 0.f), ah, p2[g][e], p3[g][e]);
             s.out[(long)i * s.ldq + q] = ah;
           } else {
             sum.lin = fmaf(a, p0[g][e], sum.lin);
@@ -3734,6 +3765,8 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
         }
     }
   }
+  sum.beta = rb.lo();
+  if constexpr (SYM) sum.up = rb.up();
   block_finish<MODE, SYM>(s, sum, red, q0, Q, false);
 }
 
@@ -6243,9 +6276,9 @@ int launch_stage(const lirpa_net* net, int m, int pass, const float* in, long ld
   DLayer t = dlayer(net->T[m - 1]);
   const char* sfx = MODE == MODE_SLAB ? "_relax" : "_bound";
   // (the relaxing kernels' form of a pass that carries one row per neuron; the concretising ones
-  // have nothing to add to its gaps)
+  // have nothing to add to its biases)
   constexpr bool SYM = MODE == MODE_SLAB;
-  const bool sym = SYM && s.gap != nullptr;
+  const bool sym = SYM && s.up != nullptr;
   const unsigned nblk32 = (unsigned)((Q + 31) / 32);
   if (t.kind == LIRPA_LINEAR) {
     FcLaunch f;
@@ -6350,14 +6383,14 @@ struct Chunk {
   const float* alpha;
   hipStream_t st;
   bool tape = false;   // record the gradient tape (mode-1 plan)
-  bool sym = false;    // this pass carries one row per neuron (Sink::gap)
+  bool sym = false;    // this pass carries one row per neuron (Sink::up)
   const float* lp = nullptr;  // the parent sub-domains' l, u (chunk's first row) or null
   const float* up = nullptr;
 };
 
-// The running gaps of a pass that carries one row per neuron (Chunk::sym): such a pass uses half
+// The upper biases of a pass that carries one row per neuron (Chunk::sym): such a pass uses half
 // of the running biases' array, and the other half holds them.
-float* gap_of(const Chunk& c, long R) {
+float* up_of(const Chunk& c, long R) {
   return c.sym ? at<float>(c.ws, c.p->off_beta) + c.nb * R : nullptr;
 }
 
@@ -6377,7 +6410,7 @@ Sink slab_sink(const Chunk& c, int m, float* out, long ldq, long R) {
   s.bias_hw = 1;
   (void)t;
   s.beta = at<float>(c.ws, c.p->off_beta);
-  s.gap = gap_of(c, R);
+  s.up = up_of(c, R);
   s.R = R;
   return s;
 }
@@ -6388,7 +6421,7 @@ Sink bound_sink(const Chunk& c, long R, float* lo, float* hi, long bstride, long
   s.x0 = c.net->L >= 2 ? nullptr : c.x0;
   s.eps = c.eps;
   s.beta = at<float>(c.ws, c.p->off_beta);
-  s.gap = gap_of(c, R);
+  s.up = up_of(c, R);
   s.R = R;
   s.lo = lo;
   s.hi = hi;
@@ -7000,7 +7033,7 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
         continue;
       }
     }
-    // Without given slopes one row per neuron gives both bounds (Sink::gap); 16 rows of a block
+    // Without given slopes one row per neuron gives both bounds (Sink::up); 16 rows of a block
     // still span at most two sub-domains, and the rows of a pair one.
     Chunk cs = c;
     cs.sym = !c.tape && !c.alpha && nk % 2 == 0 && nk >= 16;

@@ -185,7 +185,7 @@ __device__ __forceinline__ void put_split(char* pl, int plane, int o, const floa
 // and r + 8 of a block are +-e_j of channel 8 g + r).  GRAD = true: the reverse sweep of the
 // pass; the rows with weight of a position are numbered in the order (channel, sign) and group
 // g takes rows 16 g .. 16 g + 15; a block without any stops after its flag.
-// SYM (bounds without given slopes): one row per neuron gives both bounds (Sink::gap), so the 16
+// SYM (bounds without given slopes): one row per neuron gives both bounds (Sink::up), so the 16
 // rows are 16 channels of a position, or, with 8 channels or fewer, those of two neighbouring
 // positions (nwin = 2: rows 0-7 and 8-15, each in its own window's coordinates; the windows'
 // relaxations stand one behind the other).
@@ -266,7 +266,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
   __syncthreads();
 
   // the rows of W_k, relaxed onto g^(k-1): thread = (row, quad of channels of a position)
-  float beta = 0.f, gap = 0.f;
+  RowBias<SYM> rb;
   {
     const int m = k - 1;
     const int w = d.K, Cq = d.L[m].Cq, C = d.L[m].C, plane = d.L[m].plane;
@@ -297,11 +297,9 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
         const int c = 4 * cq + r;
         at[r] = c < C ? sgn * wk[c * ww + pos] : 0.f;
         const float4v p = prm[pos * 4 * Cq + c];
-        v[r] = at[r] * (at[r] >= 0.f ? p[0] : p[1]);
+        v[r] = at[r] * rb.slope(at[r], p[0], p[1]);
         if constexpr (!GRAD) {
-          beta = fmaf(fminf(at[r], 0.f), p[2], beta);
-          beta = fmaf(v[r], p[3], beta);
-          if constexpr (SYM) gap = fmaf(fabsf(at[r]), p[2], gap);
+          rb.add(at[r], fminf(at[r], 0.f), v[r], p[2], p[3]);
         }
       }
       put_split(pl, plane, ((pos * 16 + row) * Cq + cq) * 8, v);
@@ -345,12 +343,9 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
 #pragma unroll
                          for (int r = 0; r < 4; ++r) {
                            const float4v p = prm[(pos * Cqd + cq) * 4 + r];
-                           v[r] = dv[r] * (dv[r] >= 0.f ? p[0] : p[1]);
-                           if constexpr (!GRAD) {
-                             beta = fmaf(fminf(dv[r], 0.f), p[2], beta);
-                             beta = fmaf(v[r], p[3], beta);
-                             if constexpr (SYM) gap = fmaf(fabsf(dv[r]), p[2], gap);
-                           }
+                           v[r] = dv[r] * rb.slope(dv[r], p[0], p[1]);
+                           if constexpr (!GRAD)
+                             rb.add(dv[r], fminf(dv[r], 0.f), v[r], p[2], p[3]);
                          }
                          put_split(pl, pld, ((pos * 16 + n) * Cqd + cq) * 8, v);
                          if constexpr (GRAD)
@@ -384,10 +379,10 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
   }
 
   if constexpr (!GRAD) {
-    // a thread's beta: row tid % 16 in the fill and n in the stages are the same row
-    float v3[3] = {beta, l1, gap};
+    // a thread's bias terms: row tid % 16 in the fill and n in the stages are the same row
+    float v3[3] = {rb.lo(), l1, rb.up()};
 #pragma unroll
-    for (int e = 0; e < 3; ++e) {
+    for (int e = 0; e < (SYM ? 3 : 2); ++e) {
       v3[e] += __shfl_xor(v3[e], 16, 64);
       v3[e] += __shfl_xor(v3[e], 32, 64);
       if (lane < 16) red[(wave * 3 + e) * 16 + lane] = v3[e];
@@ -397,17 +392,17 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
     const bool neg = !SYM && tid >= 8;
     const int ch = SYM ? (nwin == 2 ? tid & 7 : 16 * g + tid) : 8 * g + (tid & 7);
     if (ch >= d.C || px + win >= d.W) return;
-    float tb = (neg ? -1.f : 1.f) * d.bk[ch], ta = 0.f, tg = 0.f;
+    float tb = (neg ? -1.f : 1.f) * d.bk[ch], ta = 0.f, tu = tb;
     for (int w = 0; w < nw; ++w) {
       tb += red[(w * 3 + 0) * 16 + tid];
       ta += red[(w * 3 + 1) * 16 + tid];
-      tg += red[(w * 3 + 2) * 16 + tid];
+      if constexpr (SYM) tu += red[(w * 3 + 2) * 16 + tid];
     }
     const float v = tb - a.eps * ta;
     const long j = b * a.n_relu + a.noff_k + ((long)ch * d.H + py) * d.W + px + win;
     if constexpr (SYM) {
       a.lo[j] = v;
-      a.hi[j] = (tb + tg) + a.eps * ta;
+      a.hi[j] = tu + a.eps * ta;
     } else if (neg) {
       a.hi[j] = -v;
     } else {

@@ -105,6 +105,40 @@ def test_many_convolutions(convs):
                lambda b, j: one_sided(rnet, x0, eps, C, None, alpha, b, j))
 
 
+# net, the layer whose weights are scaled, their largest value: bounds of that layer beyond fp32's
+# range, and in the last case all of them and every partial sum inside it (sum |a| b_up is beyond)
+OVERFLOWS = [("fc-four-tiles", 1, 3e37), ("base", 2, 3e37), ("deep", 3, 3e37), ("deep", 4, 3e37),
+             ("deep", 4, 1e36)]
+
+
+@pytest.mark.parametrize("name,layer,scale", OVERFLOWS)
+def test_overflowing_bounds_are_infinite(name, layer, scale):
+    # a pass with one row per neuron gives -inf and +inf where the bounds leave fp32's range, as
+    # one with two rows does, and never a NaN.  (Partial sums may leave it where the bound itself
+    # does not: then the bound is infinite on its sound side.)
+    layers = wl.random_net(NETS.get(name) or wl.ARCHS[name], 4)
+    W = layers[layer]["W"].astype(np.float64)
+    layers[layer]["W"] = (W * (scale / np.abs(W).max())).astype(np.float32)
+    x0 = np.random.default_rng(1).uniform(0, 1, wl.n_in(layers[0])).astype(np.float32)
+    C = np.eye(wl.n_out(layers[-1]), dtype=np.float32)
+    net = lirpa.Network(layers)
+    _, l, u = net.bound(dev(x0), 0.05, dev(C), None, None, B=1, want_lu=True)
+    want = ref.bound(ref.RefNet(layers), x0, 0.05, C, None, None)
+    o = sum(wl.relu_sizes(layers)[:layer])
+    top = float(np.finfo(np.float32).max)
+    for what, side, got, ref_ in (("l", -1, l, want[1]), ("u", 1, u, want[2])):
+        g = got.cpu().double().numpy()[0, o:o + wl.n_out(layers[layer])]
+        r = ref_[0, o:o + len(g)]
+        beyond = side * r > 1.01 * top
+        print(f"{name} {what}: {beyond.sum()} of {len(g)} beyond, {np.isinf(g).sum()} infinite, "
+              f"{np.isnan(g).sum()} NaN", flush=True)
+        assert not np.isnan(g).any(), f"{name} {what}"
+        assert np.all(g[beyond] == side * np.inf), f"{name} {what}"
+        assert np.all(side * (g - r) >= -1e-5 * np.abs(r)), f"{name} {what}: inside the bound"
+        if scale < 3e37:
+            assert np.isfinite(g).all(), f"{name} {what}"
+
+
 @pytest.mark.parametrize("mode", ["bound", "grad"])
 def test_workspace_without_room_for_fragments(mode):
     # a workspace that holds one sub-domain but not the split weight fragments beside it: the
