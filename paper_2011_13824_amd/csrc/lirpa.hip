@@ -5675,10 +5675,12 @@ long pass2_blocks(const lirpa_net* net, long nb);
 int p2_xw(const lirpa_net* net) { return net->T[1].out_w % 8 == 0 ? 8 : 4; }
 // ... and of its bound of nb sub-domains: one where blocks of 8 or 4 windows would leave CUs
 // idle while each block runs its windows in turn (8-16-channel net, by eights and by ones: one
-// sub-domain 20.7 and 8.0 us, four 21.5 and 9.9).  The sums are the same either way, so results
-// do not depend on the chunk.
-int p2_xw_bound(const lirpa_net* net, long nb) {
-  return pass2_blocks(net, nb) / p2_xw(net) < 256 ? 1 : p2_xw(net);
+// sub-domain 20.7 and 8.0 us, four 21.5 and 9.9; one row per neuron, with half the blocks, sixteen
+// 23.9 and 11.8, thirty-one 24 and 16.3).  The sums are the same either way, so results do not
+// depend on the chunk.
+int p2_xw_bound(const lirpa_net* net, long nb, bool sym) {
+  const long blocks = pass2_blocks(net, nb) / (sym && net->T[1].out_c % 16 == 0 ? 2 : 1);
+  return blocks / p2_xw(net) < 256 ? 1 : p2_xw(net);
 }
 
 template <int XW, bool SYM>
@@ -6637,7 +6639,7 @@ int run_stages(const Chunk& c, int pass, int mtop, long R, long Q, long ldq, flo
 int pass2_window(const Chunk& c) {
   const lirpa_net* net = c.net;
   int nw = 0;
-  const int xw = p2_xw_bound(net, c.nb);
+  const int xw = p2_xw_bound(net, c.nb, !c.alpha);
   Pass2Kernel kern = pass2_kernel_for(net, &nw, !c.alpha, xw);
   if (!kern) return 1;
   const lirpa_layer &t1 = net->T[0], &t2 = net->T[1];

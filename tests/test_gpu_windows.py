@@ -139,6 +139,23 @@ def test_overflowing_bounds_are_infinite(name, layer, scale):
             assert np.isfinite(g).all(), f"{name} {what}"
 
 
+@pytest.mark.parametrize("few", [1, 15, 16, 31, 32])
+@pytest.mark.parametrize("slopes", [False, True])
+def test_pass2_by_ones_and_by_eights(few, slopes):
+    # up to 31 sub-domains without slopes, 15 with them, the pass takes one window a block, beyond
+    # that eight: the same sums, bit for bit
+    w = wl.base()
+    net = lirpa.Network(w.layers)
+    rng = np.random.default_rng(0)
+    split = dev(wl.make_splits(40, net.n_relu, 9, 1))
+    a = dev(rng.uniform(0, 1, (40, net.n_relu)).astype(np.float32)) if slopes else None
+    cut = lambda t: None if t is None else t[:few].contiguous()  # noqa: E731
+    want = net.bound(dev(w.x0), w.eps, dev(w.C), split, a, want_lu=True)
+    got = net.bound(dev(w.x0), w.eps, dev(w.C), cut(split), cut(a), want_lu=True)
+    for x, y in zip(got, want):
+        assert torch.equal(x, y[:few])
+
+
 @pytest.mark.parametrize("mode", ["bound", "grad"])
 def test_workspace_without_room_for_fragments(mode):
     # a workspace that holds one sub-domain but not the split weight fragments beside it: the
