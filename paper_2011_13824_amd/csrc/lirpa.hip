@@ -7660,21 +7660,49 @@ int validate_enqueue(const lirpa_net* net, const float* x0, const float* C, int 
 }
 
 
+// Whether one block of k_fc_net takes a sub-domain through its passes, 32 rows at a turn, sooner
+// than the stages' launches follow each other.  Measured at one sub-domain: a turn through layer m
+// takes 0.9 us and 18 ns for each product of a lane (16 lanes a row), a launch 5.7 us.  Where the
+// line falls, and the speed against the stages there: 4-32-32-2 at 256 spec rows (1.14 at 200, 0.72
+// at 400), 20-16-3 at 480 (1.0 at 400), 48-48-48-48-10 at 128 (1.05; 0.74 at 200), 64-64-40-10 at 96
+// (1.0; 0.87 at 128), 60-60-60-10 at 64 (0.96; 0.78 at 96), eight layers of 30 at 320 (1.4 at 200,
+// 0.96 at 400).
+bool fc_net_latency_ok(const lirpa_net* net, long S) {
+  const int L = net->L;
+  double turn = 0.0, one = 5.0;  // us: a turn from layer k - 1 down; the one launch
+  int launches = 2;              // set-up, relaxation of layer 1
+  for (int k = 2; k <= L; ++k) {
+    turn += 0.9 + 0.018 * net->n[k - 1] * ((net->n[k - 2] + 15) / 16);
+    const long rows = k < L ? 2 * net->n[k] : S;
+    one += (double)((rows + 31) / 32) * turn;
+    launches += k < L ? k + 1 : (final_fc_covers(net) ? L - 1 : L + 1);
+  }
+  return one <= 5.7 * launches;
+}
+
 // The whole bound of a small fully connected net in one launch (k_fc_net): every width up to 64
 // and the weights within 32 KB, where the stages' launches cost more than their work.  Measured
 // against the stages, one spec row: 4-32-32-2 33.1 -> 12.5 us at 64 sub-domains, 152 -> 80 at
 // 4,096; eight layers of 30 261 -> 94 and 3,559 -> 938; 60-60-60-10 52.7 -> 41.3 at 64, 139 -> 116
-// at 1,024 but 396 -> 422 at 4,096, so widths over 48 stop at 1,024; two layers, where no pass
-// needs the weights more than once, 22.7 -> 14.6 at 256 but 23.3 -> 32.2 at 1,024, so they stop
-// at 256.  Returns 1 for other calls.
+// at 1,024 but 396 -> 422 at 4,096, so widths over 48 stop at 1,024 (without given slopes, where the
+// stages carry half the rows, and fewer than 32 spec rows at 512: 1.15 times the stages' speed there,
+// 0.83 at 640); two layers, where no pass needs the weights more than once, 22.7 -> 14.6 at 256 but
+// 23.3 -> 32.2 at 1,024, so they stop at 256.  With fewer blocks than CUs the call is as long as
+// one block's passes, and up to 127 sub-domains many spec rows are the stages' (fc_net_latency_ok;
+// 400 spec rows, speed against the stages: 48-48-48-48-10 0.94 at 64 sub-domains, 1.37 at 128;
+// 64-64-40-10 0.70 and 1.06; 60-60-60-10 0.57 and 0.85).  Returns 1 for other calls.
 int fc_net_run(const lirpa_net* net, const float* x0, float eps, const float* C, int S, int B,
                const int8_t* split, const float* alpha, float* lb, float* l_out, float* u_out,
                int8_t* code_out, const float* l_par, const float* u_par, hipStream_t stream) {
   if (net->L < 2 || net->L > kNetLayers || (net->L == 2 && B > 256)) return 1;
+  const long widest = *std::max_element(net->n, net->n + net->L + 1);
+  if (widest > kNetWidth) return 1;
+  const bool wide = widest > 48;
+  if (wide && B > (!alpha && S < 32 ? 512 : 1024)) return 1;
+  if (B < 128 && !fc_net_latency_ok(net, S)) return 1;
   FcNet d{};
   int o = 0;
   for (int m = 0; m <= net->L; ++m) {
-    if (net->n[m] > kNetWidth || (net->n[m] > 48 && B > 1024)) return 1;
     d.n[m] = (int)net->n[m];
     if (m == 0) continue;
     const lirpa_layer& t = net->T[m - 1];

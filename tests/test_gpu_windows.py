@@ -156,6 +156,34 @@ def test_pass2_by_ones_and_by_eights(few, slopes):
         assert torch.equal(x, y[:few])
 
 
+# widths, sub-domains, spec rows on each side of every line of the one-launch rule: sub-domains of
+# a two-layer net, of a net wider than 48 with and without slopes, few and many spec rows
+NET_LINES = [([20, 16, 3], 256, 2), ([20, 16, 3], 257, 2), ([48, 49, 3], 512, 31), ([48, 49, 3], 513, 31),
+             ([48, 49, 3], 513, 32), ([48, 49, 3], 1024, 2), ([48, 49, 3], 1025, 2),
+             ([48, 48, 5, 3], 1025, 2), ([64, 7, 5, 3], 2, 32), ([64, 7, 5, 3], 2, 33),
+             ([64, 9, 3], 127, 999), ([64, 9, 3], 128, 999), ([48, 9, 3], 127, 999),
+             ([48, 9, 3], 128, 999), ([20, 16, 3], 2, 480), ([20, 16, 3], 2, 481),
+             ([60, 60, 60, 3], 2, 64), ([60, 60, 60, 3], 2, 65), ([65, 7, 5, 3], 2, 1)]
+
+
+@pytest.mark.parametrize("slopes", [False, True])
+@pytest.mark.parametrize("widths,B,S", NET_LINES)
+def test_one_launch_rule(widths, B, S, slopes):
+    layers = wl.random_net([wl.fc(a, b) for a, b in zip(widths, widths[1:])], 2)
+    rng = np.random.default_rng(B + S)
+    x0 = rng.uniform(0, 1, widths[0]).astype(np.float32)
+    C = rng.normal(size=(S, 3)).astype(np.float32)
+    rnet = ref.RefNet(layers)
+    split = wl.make_splits(B, rnet.n_relu, 3, B)
+    alpha = rng.uniform(0, 1, (B, rnet.n_relu)).astype(np.float32) if slopes else None
+    net = lirpa.Network(layers)
+    lb, l, u = net.bound(dev(x0), 0.1, dev(C), dev(split), dev(alpha), want_lu=True)
+    lr, llr, ulr, _ = ref.bound(rnet, x0, 0.1, C, split, alpha)
+    close("lb", lb.cpu().double().numpy(), lr)
+    close("l", l.cpu().double().numpy(), llr)
+    close("u", u.cpu().double().numpy(), ulr)
+
+
 @pytest.mark.parametrize("mode", ["bound", "grad"])
 def test_workspace_without_room_for_fragments(mode):
     # a workspace that holds one sub-domain but not the split weight fragments beside it: the
