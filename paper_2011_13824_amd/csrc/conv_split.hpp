@@ -190,9 +190,9 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
     park(ay + 1);
     __syncthreads();
   }
-  float beta = rb.lo(), up = 0.f;
+  float beta = rb.lo, up = 0.f;
   if constexpr (SYM) {
-    up = rb.up();
+    up = rb.up;
     up += __shfl_xor(up, 16, 64);
     up += __shfl_xor(up, 32, 64);
   }

@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(kFcThreads)
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    float v[4] = {rb[t].lo(), lin[t], l1[t], rb[t].up()};
+    float v[4] = {rb[t].lo, lin[t], l1[t], rb[t].up};
 #pragma unroll
     for (int e = 0; e < (SYM ? 4 : 3); ++e) {
       v[e] += __shfl_xor(v[e], 16, 64);

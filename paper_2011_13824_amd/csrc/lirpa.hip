@@ -269,29 +269,27 @@ struct Acc {
 
 // A row's bias terms over the entries it relaxes: intercepts of the negative coefficients and the
 // constants.  SYM (one row per neuron): the upper bound's as well, which has the intercepts of the
-// positive coefficients.  Each sign has a sum of its own: an upper bias taken as the lower one and
-// sum |a| b_up would cancel the negative intercepts, to rounding (boxes five times the usual
-// radius, 2-norm error of u against 64 bits: 784-256-256-10 net 1.35e-7, here 0.64e-7; the
-// four-convolution net 1.28e-7 and 0.63e-7) and to NaN where they overflow.  The slope of an entry
-// needs no sign there: without given slopes the two are the same.
+// positive coefficients.  The two are summed apart, term for term as two rows +-e_j would: an upper
+// bias taken as the lower one and sum |a| b_up would cancel the negative intercepts, to rounding
+// (boxes five times the usual radius, 2-norm error of u against 64 bits: 784-256-256-10 net
+// 1.35e-7, here 0.77e-7) and to NaN where they overflow; so would a sum of the intercepts apart from
+// the constants.  The slope of an entry needs no sign there: without given slopes the two are the
+// same.
 template <bool SYM>
 struct RowBias {
-  float beta = 0.f, neg = 0.f, pos = 0.f;  // (not SYM: beta with the intercepts)
+  float lo = 0.f, up = 0.f;
   // a before relaxation, an its negative part, ah after; intercept and constant of the entry
   __device__ __forceinline__ void add(float a, float an, float ah, float bu, float bz) {
+    lo = fmaf(an, bu, lo);
+    lo = fmaf(ah, bz, lo);
     if constexpr (SYM) {
-      neg = fmaf(an, bu, neg);
-      pos = fmaf(fmaxf(a, 0.f), bu, pos);
-    } else {
-      beta = fmaf(an, bu, beta);
+      up = fmaf(fmaxf(a, 0.f), bu, up);
+      up = fmaf(ah, bz, up);
     }
-    beta = fmaf(ah, bz, beta);
   }
   static __device__ __forceinline__ float slope(float a, float a_lo, float a_up) {
     return !SYM && a >= 0.f ? a_lo : a_up;
   }
-  __device__ __forceinline__ float lo() const { return SYM ? beta + neg : beta; }
-  __device__ __forceinline__ float up() const { return beta + pos; }
 };
 
 template <int MODE>
@@ -487,8 +485,8 @@ __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float*
       s.out[idx] = ah;
     }
   }
-  red[0][w][lane] = rb.lo();
-  if constexpr (SYM) red[1][w][lane] = rb.up();
+  red[0][w][lane] = rb.lo;
+  if constexpr (SYM) red[1][w][lane] = rb.up;
   __syncthreads();
   if (w == 0 && ok) {
     float tb = red[0][0][lane];
@@ -1060,9 +1058,9 @@ k_convT_mfma(DLayer t, const float* __restrict__ in, unsigned ldq, unsigned Q, S
   }
 
   // sum over lane groups and waves, then finish rows q0..q0+15
-  float beta = rb.lo(), up = 0.f;
+  float beta = rb.lo, up = 0.f;
   if constexpr (SYM) {
-    up = rb.up();
+    up = rb.up;
     up += __shfl_xor(up, 16, 64);
     up += __shfl_xor(up, 32, 64);
   }
@@ -1404,10 +1402,10 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
     lds_barrier();
     if constexpr (FC) {
       // rows 2 qp, 2 qp + 1 of every task of this wave: lanes qp, qp + 8, ..., qp + 56
-      float fbeta_a = fa.lo(), fbeta_b = fb.lo(), fup_a = 0.f, fup_b = 0.f;
+      float fbeta_a = fa.lo, fbeta_b = fb.lo, fup_a = 0.f, fup_b = 0.f;
       if constexpr (SYM) {
-        fup_a = fa.up();
-        fup_b = fb.up();
+        fup_a = fa.up;
+        fup_b = fb.up;
       }
 #pragma unroll
       for (int o = 8; o < 64; o <<= 1) {
@@ -1477,11 +1475,11 @@ __global__ void __launch_bounds__(64 * (CI / CPW + NS), CI / CPW + NS <= 8 ? 4 :
   stage(H1 - 1);
   lds_barrier();
   stage(H1);
-  float beta = rb.lo();
+  float beta = rb.lo;
   beta += __shfl_xor(beta, 16, 64);
   beta += __shfl_xor(beta, 32, 64);
   if constexpr (SYM) {
-    float up = rb.up();
+    float up = rb.up;
     up += __shfl_xor(up, 16, 64);
     up += __shfl_xor(up, 32, 64);
     if (lane < 16) gred[ws * 16 + lane] = up;
@@ -1727,12 +1725,12 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
       if (st >= 1 && st <= H1 + 1) stage(st - 1);
       lds_barrier();
     }
-    float beta = rb.lo();
+    float beta = rb.lo;
     beta += __shfl_xor(beta, 16, 64);
     beta += __shfl_xor(beta, 32, 64);
     if (lane < 16) red[ws * 16 + lane] = beta;
     if constexpr (SYM) {
-      float up = rb.up();
+      float up = rb.up;
       up += __shfl_xor(up, 16, 64);
       up += __shfl_xor(up, 32, 64);
       if (lane < 16) red[(NS + C0 + ws) * 16 + lane] = up;
@@ -2242,10 +2240,10 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     lds_barrier();  // step H1 + 1
     if constexpr (FC) {
       // rows 2 qp, 2 qp + 1 of every task of this wave: lanes qp, qp + 8, ..., qp + 56
-      float fbeta_a = fa.lo(), fbeta_b = fb.lo(), fup_a = 0.f, fup_b = 0.f;
+      float fbeta_a = fa.lo, fbeta_b = fb.lo, fup_a = 0.f, fup_b = 0.f;
       if constexpr (SYM) {
-        fup_a = fa.up();
-        fup_b = fb.up();
+        fup_a = fa.up;
+        fup_b = fb.up;
       }
 #pragma unroll
       for (int o = 8; o < 64; o <<= 1) {
@@ -2493,7 +2491,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
   resolve(NSTEP & 1);
   l1 += __shfl_xor(l1, 16, 64);
   l1 += __shfl_xor(l1, 32, 64);
-  float beta = rb.lo();
+  float beta = rb.lo;
   beta += __shfl_xor(beta, 16, 64);
   beta += __shfl_xor(beta, 32, 64);
   if (lane < 16) {
@@ -2501,7 +2499,7 @@ __attribute__((amdgpu_waves_per_eu(SPEC > 0 ? 2 : (CI / CPW + NXW <= 8 ? 4 : 3),
     red[NM * 16 + (NXW + XB) * 16 + lane] = l1;
   }
   if constexpr (SYM) {
-    float up = rb.up();
+    float up = rb.up;
     up += __shfl_xor(up, 16, 64);
     up += __shfl_xor(up, 32, 64);
     if (lane < 16) gred[(NM + XB) * 16 + lane] = up;
@@ -2722,7 +2720,7 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) - (SYM ? 1 : 0) 
     __syncthreads();
     if (xi + 1 < XW) pfetch(X1 + t2.stride);
     {
-      float bpart = 0.f, npart = 0.f, upart = 0.f;  // (SYM: intercepts apart, see RowBias)
+      float bpart = 0.f, upart = 0.f;  // (see RowBias)
 #pragma unroll
       for (int k = 0; k < NEP; ++k) {
         // (no early exit: the loop unrolls, so the arrays are indexed statically)
@@ -2730,19 +2728,18 @@ __attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) - (SYM ? 1 : 0) 
         if (k + 1 < NEP || e < NE) {  // (only the last k can fall past NE)
           const float4v pr = prm[e];
           const float v = fmaf(wp[k], pr[0], wn[k] * pr[1]);
-          if constexpr (SYM) {
-            npart = fmaf(wn[k], pr[2], npart);
-            upart = fmaf(wp[k], pr[2], upart);
-          } else {
-            bpart = fmaf(wn[k], pr[2], bpart);
-          }
+          bpart = fmaf(wn[k], pr[2], bpart);
           // layer-1 bias and the linear term of the concretisation together: v (W1 x0 + b1)
           bpart = fmaf(v, pr[3], bpart);
+          if constexpr (SYM) {
+            upart = fmaf(wp[k], pr[2], upart);
+            upart = fmaf(v, pr[3], upart);
+          }
           tile[toff[k % TP] + (k / TP) * TS * CS] = v;
         }
       }
-      bred[part * 16 + row] = SYM ? bpart + npart : bpart;
-      if constexpr (SYM) bred[(RPT + part) * 16 + row] = bpart + upart;
+      bred[part * 16 + row] = bpart;
+      if constexpr (SYM) bred[(RPT + part) * 16 + row] = upart;
     }
     __syncthreads();
 
@@ -3765,8 +3762,8 @@ __global__ void __launch_bounds__(64 * NWAVE) k_fcT_mfma(DLayer t, const float* 
         }
     }
   }
-  sum.beta = rb.lo();
-  if constexpr (SYM) sum.up = rb.up();
+  sum.beta = rb.lo;
+  if constexpr (SYM) sum.up = rb.up;
   block_finish<MODE, SYM>(s, sum, red, q0, Q, false);
 }
 

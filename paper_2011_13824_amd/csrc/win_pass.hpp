@@ -380,7 +380,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
 
   if constexpr (!GRAD) {
     // a thread's bias terms: row tid % 16 in the fill and n in the stages are the same row
-    float v3[3] = {rb.lo(), l1, rb.up()};
+    float v3[3] = {rb.lo, l1, rb.up};
 #pragma unroll
     for (int e = 0; e < (SYM ? 3 : 2); ++e) {
       v3[e] += __shfl_xor(v3[e], 16, 64);
