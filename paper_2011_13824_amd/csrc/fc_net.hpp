@@ -39,7 +39,10 @@ __global__ void __launch_bounds__(kNetThreads) k_fc_net(FcNet d_) {
       *(const __attribute__((address_space(4))) FcNet*)__builtin_amdgcn_kernarg_segment_ptr();
   __shared__ float wt[kNetWeights];
   __shared__ float x0s[kNetWidth];
-  __shared__ float4v rel[kNetLayers][kNetWidth];  // (a_lo, a_up, b_up, bias) of ReLU layer m
+  // (a_lo, a_up, b_up, constant) of ReLU layer m: the bias, and of layer 1 z1 = W_1 x0 + b_1, which
+  // holds the rows' terms in x0 (summed over x they would overflow where the bound does not)
+  __shared__ float4v rel[kNetLayers][kNetWidth];
+  __shared__ float z1[kNetWidth];
   __shared__ float lu[2][kNetWidth];
   __shared__ float4v buf[kNetThreads / 16][2][kNetWidth / 4];
   const int tid = threadIdx.x, grp = tid >> 4, ln = tid & 15;
@@ -61,7 +64,7 @@ __global__ void __launch_bounds__(kNetThreads) k_fc_net(FcNet d_) {
       parent_clip(lj, uj, d.lpar, d.upar, p);
       const Relax1 r = relax_neuron(lj, uj, d.split ? d.split[p] : 0,
                                     d.alpha ? d.alpha + p : nullptr);
-      rel[m][j] = float4v{r.lo, r.up, r.bu, wt[d.bo[m] + j]};
+      rel[m][j] = float4v{r.lo, r.up, r.bu, m == 1 ? z1[j] : wt[d.bo[m] + j]};
       if (d.l) {
         d.l[p] = lj;
         d.u[p] = uj;
@@ -86,6 +89,7 @@ __global__ void __launch_bounds__(kNetThreads) k_fc_net(FcNet d_) {
     z = lane_sum(z) + wt[d.bo[1] + j];
     r = lane_sum(r);
     if (ln == 0) {
+      z1[j] = z;
       lu[0][j] = z - d.eps * r;
       lu[1][j] = z + d.eps * r;
     }
@@ -103,7 +107,7 @@ __global__ void __launch_bounds__(kNetThreads) k_fc_net(FcNet d_) {
       const int r = min(r0 + grp, rows - 1);
       const int j = r >> 1;
       const float sg = (r & 1) ? -1.f : 1.f;
-      float beta = 0.f;
+      float beta = 0.f, l1 = 0.f;
       if (last) {
         if (ln == 0)
           for (int o = 0; o < nk; ++o) beta = fmaf(d.C[r * nk + o], wt[d.bo[k] + o], beta);
@@ -154,15 +158,14 @@ __global__ void __launch_bounds__(kNetThreads) k_fc_net(FcNet d_) {
           if (m > 1) {
             put(m - 1, nxt, i, a);
           } else {
-            beta = fmaf(a, x0s[i], beta);
-            beta = fmaf(-d.eps, fabsf(a), beta);
+            l1 += fabsf(a);
           }
         }
         float* t = cur;
         cur = nxt;
         nxt = t;
       }
-      beta = lane_sum(beta);
+      beta = fmaf(-d.eps, lane_sum(l1), lane_sum(beta));
       if (ln == 0 && r0 + grp < rows) {
         if (last)
           d.lb[b * d.S + r] = beta;

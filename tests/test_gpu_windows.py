@@ -156,6 +156,26 @@ def test_pass2_by_ones_and_by_eights(few, slopes):
         assert torch.equal(x, y[:few])
 
 
+@pytest.mark.parametrize("layer,scale", [(1, 2e38), (2, 1e38)])
+def test_overflow_in_one_launch(layer, scale):
+    # the 4-32-32-2 net, bounded in one launch: the terms in x0 are part of layer 1's constants, so
+    # coefficients over x beyond fp32's range give -inf, not inf - inf, and no bound on the wrong side
+    layers = wl.random_net(wl.ARCHS["tiny"], 4)
+    W = layers[layer]["W"].astype(np.float64)
+    layers[layer]["W"] = (W * (scale / np.abs(W).max())).astype(np.float32)
+    x0 = np.random.default_rng(1).uniform(0, 1, 4).astype(np.float32)
+    C = np.eye(2, dtype=np.float32)
+    net = lirpa.Network(layers)
+    lb, l, u = (t.cpu().double().numpy() for t in net.bound(dev(x0), 0.05, dev(C), None, None, B=1,
+                                                            want_lu=True))
+    lr, llr, ulr, _ = ref.bound(ref.RefNet(layers), x0, 0.05, C, None, None)
+    print(f"{np.isinf(lb).sum()} lb, {np.isinf(l).sum()} l, {np.isinf(u).sum()} u infinite", flush=True)
+    if layer == 2:
+        assert not np.isnan(lb).any()
+        assert np.all(lb - lr <= 1e-5 * np.abs(lr))
+    assert not np.any(l == np.inf) and not np.any(u == -np.inf)
+
+
 # widths, sub-domains, spec rows on each side of every line of the one-launch rule: sub-domains of
 # a two-layer net, of a net wider than 48 with and without slopes, few and many spec rows
 NET_LINES = [([20, 16, 3], 256, 2), ([20, 16, 3], 257, 2), ([48, 49, 3], 512, 31), ([48, 49, 3], 513, 31),
