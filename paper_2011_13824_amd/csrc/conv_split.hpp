@@ -177,7 +177,7 @@ __global__ void __launch_bounds__(512) k_convT_split(ConvSplit c, const float* _
           if constexpr (MODE == MODE_SLAB) {
             if (s.tape) s.tape[idx] = a;
             const float ah = a * rb.slope(a, lo[r], up[r]);
-            rb.add(a, fminf(a, 0.f), ah, bu[r], bz[r]);
+            rb.add_any(a, ah, bu[r], bz[r]);
             s.out[idx] = ah;
           } else {
             if (s.tsign) s.tsign[idx] = sign8(a);

@@ -287,6 +287,17 @@ struct RowBias {
       up = fmaf(ah, bz, up);
     }
   }
+  // The same where the intercept may be infinite (bounds past 1.8e19, whose product overflows): an
+  // entry of the other sign has no part in it, where 0 times it would be NaN.
+  __device__ __forceinline__ void add_any(float a, float ah, float bu, float bz) {
+    const bool neg = a < 0.f;
+    const float t = fmaf(a, bu, lo);
+    lo = fmaf(ah, bz, neg ? t : lo);
+    if constexpr (SYM) {
+      const float v = fmaf(a, bu, up);
+      up = fmaf(ah, bz, neg ? up : v);
+    }
+  }
   static __device__ __forceinline__ float slope(float a, float a_lo, float a_up) {
     return !SYM && a >= 0.f ? a_lo : a_up;
   }

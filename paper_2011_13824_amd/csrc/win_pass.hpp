@@ -299,7 +299,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
         const float4v p = prm[pos * 4 * Cq + c];
         v[r] = at[r] * rb.slope(at[r], p[0], p[1]);
         if constexpr (!GRAD) {
-          rb.add(at[r], fminf(at[r], 0.f), v[r], p[2], p[3]);
+          rb.add_any(at[r], v[r], p[2], p[3]);
         }
       }
       put_split(pl, plane, ((pos * 16 + row) * Cq + cq) * 8, v);
@@ -345,7 +345,7 @@ __global__ void __launch_bounds__(512) k_win_pass(WinDesc d_, WinArgs a) {
                            const float4v p = prm[(pos * Cqd + cq) * 4 + r];
                            v[r] = dv[r] * rb.slope(dv[r], p[0], p[1]);
                            if constexpr (!GRAD)
-                             rb.add(dv[r], fminf(dv[r], 0.f), v[r], p[2], p[3]);
+                             rb.add_any(dv[r], v[r], p[2], p[3]);
                          }
                          put_split(pl, pld, ((pos * 16 + n) * Cqd + cq) * 8, v);
                          if constexpr (GRAD)
