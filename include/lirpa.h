@@ -132,7 +132,9 @@ int lirpa_bound_child(lirpa_net* net, const float* x0, float eps, const float* C
  * no workspace argument.  Its workspace is the library's own scratch array of 128 MiB per
  * device (a static device array, held from the time the library is loaded on the device until
  * the process ends); the call allocates and frees nothing.  A batch whose workspace exceeds it
- * runs in chunks of as many sub-domains as fit (results are identical to any other chunking).
+ * runs in chunks of as many sub-domains as fit (results are identical to any other chunking; a
+ * network whose one sub-domain fits, but not beside the kernels' packed weights, runs kernels
+ * without them, whose sums have another order).
  * LIRPA_ENOMEM when one sub-domain alone needs more than 128 MiB.  Every call on a device
  * shares that device's array and leaves its contents behind: calls that overlap on one device
  * (from several streams or threads) race and give undefined results. */

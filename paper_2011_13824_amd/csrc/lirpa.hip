@@ -7602,6 +7602,11 @@ long fit_chunk(const lirpa_net* net, long S, long B, size_t ws_bytes, Plan* out,
   return 0;
 }
 
+// The least workspace that fit_chunk takes.
+size_t least_bytes(const lirpa_net* net, long S, int mode) {
+  return std::min(plan_for(net, S, 1, mode).total, plan_for(net, S, 1, mode, false).total);
+}
+
 Chunk make_chunk(lirpa_net* net, const Plan& p, void* ws, const float* x0, float eps, long S,
                  long B, long b0, const int8_t* split, const float* alpha, float* l_out,
                  float* u_out, hipStream_t stream) {
@@ -8191,7 +8196,7 @@ int lirpa_bound(lirpa_net* net, const float* x0, float eps, const float* C, int 
   long Bc = fit_chunk(net, S, B, ws_bytes, &p);
   if (Bc < 1)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes holds no sub-domain (need %zu)", ws_bytes,
-                make_plan(net, S, 1).total);
+                least_bytes(net, S, 0));
   return bound_run(net, p, Bc, x0, eps, C, S, B, split, alpha, lb, l_out, u_out, code_out, ws,
                    stream);
 }
@@ -8209,7 +8214,7 @@ int lirpa_bound_child(lirpa_net* net, const float* x0, float eps, const float* C
   long Bc = fit_chunk(net, S, B, ws_bytes, &p);
   if (Bc < 1)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes holds no sub-domain (need %zu)", ws_bytes,
-                make_plan(net, S, 1).total);
+                least_bytes(net, S, 0));
   return bound_run(net, p, Bc, x0, eps, C, S, B, split, alpha, lb, l_out, u_out, code_out, ws,
                    stream, l_parent, u_parent);
 }
@@ -8228,7 +8233,7 @@ int lirpa_bound_noalloc(lirpa_net* net, const float* x0, float eps, const float*
     return fail(LIRPA_ENOMEM,
                 "one sub-domain needs %zu bytes of workspace, beyond the library's scratch array "
                 "of %zu MiB; call lirpa_bound with a workspace",
-                make_plan(net, S, 1).total, kScratchBytes >> 20);
+                least_bytes(net, S, 0), kScratchBytes >> 20);
   void* ws = nullptr;
   if (int e = scratch_address(&ws)) return e;
   return bound_run(net, p, Bc, x0, eps, C, S, B, split, alpha, lb, l_out, u_out, code_out, ws,
@@ -8245,7 +8250,7 @@ int lirpa_bound_grad(lirpa_net* net, const float* x0, float eps, const float* C,
   long Bc = fit_chunk(net, S, B, ws_bytes, &p, 1);
   if (Bc < 1)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes holds no sub-domain (need %zu)", ws_bytes,
-                make_plan(net, S, 1, 1).total);
+                least_bytes(net, S, 1));
   if (int e = validate_report(stream)) return e;
   if (int e = validate_enqueue(net, x0, C, S, B, split, alpha, stream)) return e;
   if (int e = layer1_bounds(net, p, ws, x0, eps, C, S, true, stream)) return e;
@@ -8272,7 +8277,7 @@ int lirpa_optimize(lirpa_net* net, const float* x0, float eps, const float* C, i
   long Bc = fit_chunk(net, S, B, ws_bytes, &p, 1);
   if (Bc < 1)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes holds no sub-domain (need %zu)", ws_bytes,
-                make_plan(net, S, 1, 1).total);
+                least_bytes(net, S, 1));
   if (int e = validate_report(stream)) return e;
   // alpha is an input only when the call continues from the caller's state
   if (int e = validate_enqueue(net, x0, C, S, B, split, params->fresh ? nullptr : alpha, stream))
@@ -8293,7 +8298,7 @@ int lirpa_bound_ul(lirpa_net* net, const float* x0, float eps, const float* C, i
   long Bc = fit_chunk(net, S, B, ws_bytes, &p, 2);
   if (Bc < 1)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes holds no sub-domain (need %zu)", ws_bytes,
-                plan_for(net, S, 1, 2).total);
+                least_bytes(net, S, 2));
   if (int e = validate_report(stream)) return e;
   if (int e = validate_enqueue(net, x0, C, S, B, split, alpha, stream)) return e;
   return bound_ul_run(net, p, Bc, x0, eps, C, S, B, split, alpha, lb, ub, l_out, u_out, code_out,
@@ -8314,7 +8319,7 @@ int lirpa_optimize_ul(lirpa_net* net, const float* x0, float eps, const float* C
   long Bc = fit_chunk(net, S, B, ws_bytes, &p, 3);
   if (Bc < 1)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes holds no sub-domain (need %zu)", ws_bytes,
-                plan_for(net, S, 1, 3).total);
+                least_bytes(net, S, 3));
   if (int e = validate_report(stream)) return e;
   if (int e = validate_enqueue(net, x0, C, S, B, split, params->fresh ? nullptr : alpha_lo,
                                stream))
@@ -8355,10 +8360,11 @@ int lirpa_bab(lirpa_net* net, const float* x0, float eps, const float* c,
   if (!params || !result) return fail(LIRPA_EINVAL, "params and result must be given");
   if (int e = check_bab_params(*params)) return e;
   BabPlan q = bab_plan(net, *params);
-  if (q.total > ws_bytes) q = bab_plan(net, *params, false);
+  const size_t full = q.total;
+  if (full > ws_bytes) q = bab_plan(net, *params, false);
   if (q.total > ws_bytes)
     return fail(LIRPA_ENOMEM, "workspace of %zu bytes, branch and bound needs %zu", ws_bytes,
-                q.total);
+                std::min(full, q.total));
   if (int e = validate_report(stream)) return e;
   if (int e = validate_enqueue(net, x0, c, 1, 1, nullptr, nullptr, stream)) return e;
   *result = lirpa_bab_result{};

@@ -10,6 +10,8 @@ Tolerance: a bound is at most four chained fp32 sums of up to 2,000 terms, each 
 2-norm (the fp32 matrix instruction's measured error at that length); with a factor 3 for
 cancellation 1e-5 (1 + |ref|).  Gradients: the same, normwise, with the kink rule of the gradient
 tests."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -237,6 +239,27 @@ def test_workspace_without_room_for_fragments(mode):
                               None, None, ws, room)
             lr = ref.bound(rnet, x0, 0.1, C, None, alpha)[0]
         close(f"{mode} lb", lb.cpu().double().numpy(), lr)
+
+
+def test_least_workspace_is_the_one_named():
+    # the refusal of a workspace that is too small names what one sub-domain needs at least
+    layers = wl.random_net(NETS["off-chip"], 3)
+    net = lirpa.Network(layers)
+    x0, C = dev(np.full(16, 0.5, np.float32)), dev(wl.margin_spec(3, 0))
+    lb = torch.empty((2, 2), device="cuda")
+
+    def call(room):
+        lirpa.lirpa_bound(net.handle, x0, 0.1, C, 2, 2, None, None, lb, None, None, None,
+                          torch.empty(room, dtype=torch.uint8, device="cuda"), room)
+
+    with pytest.raises(lirpa.LirpaError) as ei:
+        call(256)
+    assert ei.value.code == lirpa.LIRPA_ENOMEM
+    need = int(re.search(r"need (\d+)", str(ei.value)).group(1))
+    call(need)
+    with pytest.raises(lirpa.LirpaError) as ei:
+        call(need - 1)
+    assert ei.value.code == lirpa.LIRPA_ENOMEM
 
 
 @pytest.mark.parametrize("B,S", [(1, 1), (5, 7), (129, 2), (1024, 1), (1025, 3)])
