@@ -3,8 +3,10 @@ intermediate bounds and gradients of nets whose windows have every edge the kern
 (strides 1 to 4, kernels 1 to 7 larger than the map, taps that do not divide by the stride,
 channel counts off the 4, 8 and 16 of its tiles, up to four convolutions), and of one whose
 windows do not fit on chip (the dense stages).  The fc nets do the same for the fully connected
-stages: four, two and one tiles of rows a block, widths off every tile, and a layer too narrow
-for the split kernels.  The net nets run the one-launch bound of small fully connected nets.
+stages, on one tile of rows a block: widths off every tile, and a layer too narrow for the split
+kernels (test_fc_row_tiles runs two and four tiles).  The net nets run the one-launch bound of
+small fully connected nets.  The slab nets end their intermediate pass 4, whose rows come from a
+fully connected layer of even width off the 16 rows of a block, in the two convolutions' kernel.
 
 Tolerance: a bound is at most four chained fp32 sums of up to 2,000 terms, each within 8e-7 of its
 2-norm (the fp32 matrix instruction's measured error at that length); with a factor 3 for
@@ -16,10 +18,11 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import ref
+from oracle import bab, ref
 from paper_2011_13824_amd import lirpa
 from paper_2011_13824_amd import workloads as wl
-from tests.test_gpu_grad import check_grad, dev, one_sided
+from tests import helpers as H
+from tests.test_gpu_grad import check_grad, dev, heuristic_alpha, one_sided
 
 pytestmark = pytest.mark.gpu
 
@@ -33,14 +36,18 @@ NETS = {
     "k-over-map": [wl.conv(3, 6, 8, 5, 3, 2), wl.conv(8, 2, 33, 1, 1, 0), wl.fc(132, 3)],
     "wide-channels": [wl.conv(3, 6, 40, 3, 1, 1), wl.conv(40, 6, 12, 3, 2, 1), wl.fc(108, 3)],
     "conv-last": [wl.conv(1, 6, 4, 4, 2, 1), wl.conv(4, 3, 16, 3, 1, 1), wl.conv(16, 3, 1, 3, 1, 0)],
-    "fc-four-tiles": [wl.fc(70, 250), wl.fc(250, 67), wl.fc(67, 3)],
-    "fc-two-tiles": [wl.fc(50, 330), wl.fc(330, 54), wl.fc(54, 3)],
-    "fc-one-tile": [wl.fc(20, 850), wl.fc(850, 20), wl.fc(20, 31), wl.fc(31, 3)],
+    "fc-odd": [wl.fc(70, 250), wl.fc(250, 67), wl.fc(67, 3)],
+    "fc-even": [wl.fc(50, 330), wl.fc(330, 54), wl.fc(54, 3)],
+    "fc-narrow": [wl.fc(20, 850), wl.fc(850, 20), wl.fc(20, 31), wl.fc(31, 3)],
     "net-edges": [wl.fc(1, 64), wl.fc(64, 1), wl.fc(1, 33), wl.fc(33, 3)],
     "net-eight-layers": [wl.fc(7, 5), wl.fc(5, 6), wl.fc(6, 7), wl.fc(7, 8), wl.fc(8, 9),
                          wl.fc(9, 10), wl.fc(10, 11), wl.fc(11, 3)],
     "net-two-layers": [wl.fc(20, 16), wl.fc(16, 3)],
     "off-chip": [wl.conv(1, 4, 64, 7, 1, 3), wl.conv(64, 4, 2, 7, 1, 3), wl.fc(32, 3)],
+    "slab-8-16": [wl.conv(3, 32, 8, 4, 2, 1), wl.conv(8, 16, 16, 4, 2, 1), wl.fc(1024, 30),
+                  wl.fc(30, 34), wl.fc(34, 3)],
+    "slab-16-32": [wl.conv(3, 32, 16, 4, 2, 1), wl.conv(16, 16, 32, 4, 2, 1), wl.fc(2048, 30),
+                   wl.fc(30, 18), wl.fc(18, 3)],
     "gray": [wl.conv(1, 28, 16, 4, 2, 1), wl.conv(16, 14, 32, 4, 2, 1), wl.fc(1568, 100),
              wl.fc(100, 3)],
 }
@@ -85,6 +92,116 @@ def test_windows(name, B):
                lambda b, j: one_sided(rnet, x0, eps, C, split, alpha, b, j))
 
 
+# Fully connected stages take two tiles of 16 rows a block from 16,384 rows on and four from 32,768:
+# the first pass's rows here, two per neuron with slopes (134 and 108), 54 without
+@pytest.mark.parametrize("name,B", [("fc-odd", 125), ("fc-odd", 251), ("fc-even", 309),
+                                    ("fc-even", 617)])
+def test_fc_row_tiles(name, B):
+    arch = NETS[name]
+    layers = wl.random_net(arch, B)
+    rng = np.random.default_rng(B)
+    x0 = rng.uniform(0, 1, wl.n_in(arch[0])).astype(np.float32)
+    eps, C, some = 0.1, wl.margin_spec(3, 1), [0, 1, B // 2, B - 2, B - 1]
+    rnet = ref.RefNet(layers)
+    split = wl.make_splits(B, rnet.n_relu, 6, B)
+    alpha = rng.uniform(0.05, 0.95, (B, rnet.n_relu)).astype(np.float32)
+    net = lirpa.Network(layers)
+    for a in (None, alpha):
+        got = net.bound(dev(x0), eps, dev(C), dev(split), dev(a), want_lu=True)
+        want = ref.bound(rnet, x0, eps, C, split[some], None if a is None else a[some])
+        for what, g, w in zip(("lb", "l", "u"), got, want):
+            close(f"{name} {B} {what}", g.cpu().double().numpy()[some], w)
+    lb, g = net.bound_grad(dev(x0), eps, dev(C), dev(split), dev(alpha))
+    lr, gr = ref.bound_grad(rnet, x0, eps, C, split[some], alpha[some])
+    close(f"{name} {B} grad lb", lb.cpu().double().numpy()[some], lr)
+    check_grad(f"{name} {B} grad", g.cpu().double().numpy()[some], gr, split[some],
+               lambda b, j: one_sided(rnet, x0, eps, C, split[some], alpha[some], b, j))
+
+
+@pytest.mark.parametrize("slopes", [False, True])
+@pytest.mark.parametrize("name", ["four-convs", "k7-stride4", "conv-last", "off-chip", "fc-even"])
+def test_other_entry_points(name, slopes):
+    # bounds from a parent's and bounds of both sides
+    arch, B = NETS[name], 5
+    layers = wl.random_net(arch, 3)
+    rng = np.random.default_rng(3)
+    x0 = rng.uniform(0, 1, wl.n_in(arch[0])).astype(np.float32)
+    eps, C = 0.1, np.eye(wl.n_out(arch[-1]), dtype=np.float32)
+    rnet = ref.RefNet(layers)
+    split = wl.make_splits(B, rnet.n_relu, 6, B)
+    alpha = rng.uniform(0.05, 0.95, (B, rnet.n_relu)).astype(np.float32) if slopes else None
+    net = lirpa.Network(layers)
+    # (the parent: the same sub-domain without its splits)
+    _, lp, up, _ = ref.bound(rnet, x0, eps, C, np.zeros_like(split), alpha)
+    lp, up = lp.astype(np.float32), up.astype(np.float32)
+    got = net.bound_child(dev(x0), eps, dev(C), dev(split), dev(alpha), dev(lp), dev(up))
+    want = ref.bound_child(rnet, x0, eps, C, split, alpha, lp, up)
+    for what, g, w in zip(("lb", "l", "u"), got, want):
+        close(f"{name} child {what}", g.cpu().double().numpy(), w)
+    lo, hi = net.bound_ul(dev(x0), eps, dev(C), dev(split), dev(alpha))
+    close(f"{name} ul lb", lo.cpu().double().numpy(), ref.bound(rnet, x0, eps, C, split, alpha)[0])
+    close(f"{name} ul ub", hi.cpu().double().numpy(),
+          -ref.bound(rnet, x0, eps, -C, split, alpha)[0])
+
+
+@pytest.mark.parametrize("name", ["four-convs", "k7-stride4", "conv-last", "off-chip", "fc-even"])
+def test_optimize_step(name):
+    # a fresh start: the heuristic bound, the gradient there (ten times the first moment), and the
+    # bound at the slopes after the step
+    arch, B = NETS[name], 3
+    layers = wl.random_net(arch, 4)
+    rng = np.random.default_rng(4)
+    x0 = rng.uniform(0, 1, wl.n_in(arch[0])).astype(np.float32)
+    eps, C = 0.1, np.eye(wl.n_out(arch[-1]), dtype=np.float32)
+    rnet = ref.RefNet(layers)
+    split = wl.make_splits(B, rnet.n_relu, 6, B)
+    net = lirpa.Network(layers)
+    a = torch.empty((B, rnet.n_relu), device="cuda")
+    m, v = torch.empty_like(a), torch.empty_like(a)
+    best, trace = net.optimize(dev(x0), eps, dev(C), dev(split), a, m, v, steps=1, fresh=True,
+                               trace=True)
+    lr, l, u, _ = ref.bound(rnet, x0, eps, C, split)
+    a0 = heuristic_alpha(l, u).astype(np.float32)
+    gr = ref.bound_grad(rnet, x0, eps, C, split, a0)[1]
+    close(f"{name} start", trace[0].cpu().double().numpy(), lr)
+    check_grad(f"{name} gradient", 10 * m.cpu().double().numpy(), gr, split,
+               lambda b, j: one_sided(rnet, x0, eps, C, split, a0, b, j))
+    end = ref.bound(rnet, x0, eps, C, split, a.cpu().numpy())[0]
+    close(f"{name} end", trace[1].cpu().double().numpy(), end)
+    assert torch.equal(best, trace.max(0).values)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(root_steps=2, steps=2)])
+def test_search_without_room_for_fragments(kw):
+    # the search's least workspace, where its calls run without their packed weights or in chunks:
+    # its course on the heuristic slopes is the oracle's, with optimised ones the full workspace's
+    layers = wl.random_net(H.small_conv_arch(), 21)
+    x0 = np.random.default_rng(21).uniform(0, 1, wl.n_in(layers[0])).astype(np.float32)
+    c = wl.margin_spec(3, 2)[1]
+    net = lirpa.Network(layers)
+    p = lirpa.lirpa_bab_params(8, 100, 3, kw.get("root_steps", 0), kw.get("steps", 0), 0.1, 0.9,
+                               0.999, 1e-8)
+    full = lirpa.lirpa_bab_workspace_bytes(net.handle, p)
+
+    def search(room):
+        r = lirpa.lirpa_bab(net.handle, dev(x0), 0.05, dev(c), p,
+                            torch.empty(room, dtype=torch.uint8, device="cuda"), room)
+        return {k: getattr(r, k) for k, _ in r._fields_}
+
+    with pytest.raises(lirpa.LirpaError) as ei:
+        search(256)
+    need = int(re.search(r"needs (\d+)", str(ei.value)).group(1))
+    assert need <= full
+    got, want = search(need), search(full)
+    if not kw:
+        want = bab.bab(ref.RefNet(layers), x0, 0.05, c, 8, 100, 3)
+    print(f"{need} of {full} bytes: {got}", flush=True)
+    for k in ("status", "iterations", "domains_bounded", "domains_left"):
+        assert got[k] == want[k], k
+    for k in ("f_lo", "f_hi"):
+        assert abs(got[k] - want[k]) <= 1e-4 * (1 + abs(want[k])), k
+
+
 @pytest.mark.parametrize("convs", [8, 10, 16])
 def test_many_convolutions(convs):
     # every convolution has weight fragments of its own in each direction, and a set-up launch
@@ -113,7 +230,7 @@ def test_many_convolutions(convs):
 # range, and in the fifth case all of them and every partial sum inside it (sum |a| b_up is beyond).
 # "gray" with layer 0 scaled: layer 1's bounds are inside the range and their intercepts beyond it;
 # the bounds after the next layer's
-OVERFLOWS = [("fc-four-tiles", 1, 3e37), ("base", 2, 3e37), ("deep", 3, 3e37), ("deep", 4, 3e37),
+OVERFLOWS = [("fc-odd", 1, 3e37), ("base", 2, 3e37), ("deep", 3, 3e37), ("deep", 4, 3e37),
              ("deep", 4, 1e36), ("gray", 0, 1e36)]
 
 
