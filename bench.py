@@ -152,6 +152,12 @@ def stage_work(layers, S, B, fr=None):
             add(f"convT_slab_bound[layer2,pass{k}]",
                 2.0 * Q * (macs(layers[1]) + macs(layers[0])),
                 4.0 * n[2] * Q + 4.0 * Q + 4.0 * (3 * B * n[1] + n[1]))
+    if all(t["kind"] == wl.FC for t in layers):
+        # a whole bound in one launch (launched instead of the stages for small nets): every stage's
+        # flops; the weights and split masks read, the bounds written
+        add("fc_net", sum(f for c, (f, _) in work.items() if c.startswith("fcT")),
+            4.0 * sum(macs(t) + n[m + 1] for m, t in enumerate(layers))
+            + B * (sum(n[1:L]) + 4.0 * S))
     return work
 
 
@@ -277,21 +283,36 @@ def unstable_fractions(net, x0, w, C, split, alpha):
 
 def split_classes(work, layers, one_row):
     """The same work under the names of the split-operand kernels, which run where their shapes
-    apply.  one_row: bounds without given slopes carry one row per neuron instead of two in every
-    intermediate pass, so those passes' counts halve."""
+    apply.  one_row: bounds without given slopes need one row per neuron instead of two in every
+    intermediate pass, so those passes' counts halve.  That is what the bound needs, not always
+    what runs: pass 2 keeps both rows where its channels are no multiple of 16, the fp32 window
+    kernels always, the other stages for layers of odd width or under 16 neurons; "executed" has the
+    flops of those classes.  (An optimiser's counts are those of given slopes, also in the one
+    heuristic bound it starts from.)"""
+    from paper_2011_13824_amd import workloads as wl
     L = len(layers)
-    out = {}
+    out, executed = {}, {}
     for cls, (f, b) in work.items():
         k = int(cls.split("pass")[-1].rstrip("]")) if "[" in cls else L
+        full = f
         if one_row and 2 <= k < L and not cls.startswith("relax_params"):
             f, b = f / 2, b / 2
-        out[cls] = (f, b)
+        names = [cls]
         for old, new in (("pass3_window", "win_bound"), ("pass4_window", "win_bound"),
                          ("fcT_relax", "fcT_split_relax"), ("fcT_bound", "fcT_split_bound"),
                          ("convT_relax", "convT_split_relax"),
                          ("convT_bound", "convT_split_bound")):
             if cls.startswith(old + "["):
-                out[new + cls[len(old):]] = (f, b)
+                names.append(new + cls[len(old):])
+        for c in names:
+            out[c] = (f, b)
+            n = wl.n_out(layers[k - 1])
+            both = (layers[k - 1]["out_c"] % 16 != 0 if c.startswith("pass2_window") else
+                    c.startswith(("pass3_window", "pass4_window")) or
+                    not c.startswith("win_bound") and (n % 2 != 0 or n < 16))
+            if f < full and both:
+                executed[c] = full
+    out["executed"] = executed
     return out
 
 
@@ -449,10 +470,10 @@ def main():
     torch.cuda.synchronize()
     fr = unstable_fractions(net, x0, w, C, split, alpha) if optimise else None
     work = split_classes(stage_work(w.layers, S, B, fr), w.layers, not optimise)
-    executed = {}
+    executed = work.pop("executed")
     if optimise:
         work.update(grad_work(w.layers, S, B, layer2_stats(net, x0, w, C, split, alpha), fr))
-        executed = work.pop("executed", {})
+        executed.update(work.pop("executed", {}))
     stages = {}
     for cls, (tot_ms, launches) in sorted(times.items(), key=lambda kv: -kv[1][0]):
         f, b = work.get(cls, (0.0, 0.0))
@@ -479,7 +500,8 @@ def main():
     roof["kernel"] = dom
     roof["avg_launch_ms"] = round(tot_ms / launches, 4)
     if dom in executed:
-        # the MFMA work the kernel actually issues (it skips T_2 where nothing uses it)
+        # the MFMA work the kernel actually issues (it skips T_2 where nothing uses it, or carries
+        # both rows of a neuron where one is counted)
         roof["executed_tflops"] = round(executed[dom] / (tot_ms / launches / 1e3) / 1e12, 3)
     roof["traffic"] = None if args.batch else traffic_record(w.name, dom)
 

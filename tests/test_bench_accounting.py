@@ -81,3 +81,46 @@ def test_relax_params_reads_alpha_of_unstable_neurons_only(layers):
     assert plain["relax_params[layer1,pass1]"][1] == pytest.approx(22.0 * B * N1)
     assert opt["relax_params[layer1,pass1]"][1] == pytest.approx((22.0 + 0.4) * B * N1)
     assert opt["relax_params[layer2,pass2]"][1] == pytest.approx((22.0 + 1.0) * B * N2)
+
+
+def test_one_row_per_neuron_halves_intermediate_passes_only():
+    w = wl.get("deep")
+    plain = bench.stage_work(w.layers, w.S, w.B)
+    two = bench.split_classes(plain, w.layers, False)
+    one = bench.split_classes(plain, w.layers, True)
+    assert two.pop("executed") == {}
+    executed = one.pop("executed")
+    assert set(one) == set(two) and set(plain) <= set(two)
+    for cls, (f, b) in two.items():
+        k = int(cls.split("pass")[-1].rstrip("]"))
+        half = 2 <= k < 6 and not cls.startswith("relax_params")
+        assert one[cls] == ((f / 2, b / 2) if half else (f, b)), cls
+    # the split kernels' names carry the work of the classes they replace
+    assert two["win_bound[layer1,pass3]"] == plain["pass3_window[layer1,pass3]"]
+    assert two["win_bound[layer1,pass4]"] == plain["pass4_window[layer1,pass4]"]
+    assert two["convT_split_relax[layer3,pass4]"] == plain["convT_relax[layer3,pass4]"]
+    assert two["fcT_split_relax[layer5,pass6]"] == plain["fcT_relax[layer5,pass6]"]
+    # 8 channels on T_2: pass 2 runs both rows of a neuron, the window kernel of pass 3 one
+    assert executed["pass2_window[layer1,pass2]"] == plain["pass2_window[layer1,pass2]"][0]
+    assert "win_bound[layer1,pass3]" not in executed
+    assert "convT_relax[layer3,pass5]" not in executed
+
+
+def test_both_rows_where_the_width_is_odd_or_small():
+    conv, fc = wl.conv, wl.fc
+    arch = [conv(3, 32, 8, 4, 2, 1), conv(8, 16, 16, 4, 2, 1), fc(1024, 33), fc(33, 14), fc(14, 3)]
+    ex = bench.split_classes(bench.stage_work(arch, 2, 10), arch, True)["executed"]
+    assert "pass2_window[layer1,pass2]" not in ex  # 16 channels
+    for cls in ("convT_fc_bound[layer2,pass3]", "fcT_relax[layer3,pass4]",
+                "convT_slab_bound[layer2,pass4]"):
+        assert cls in ex, cls
+    assert not [c for c in ex if c.endswith("pass5]")]  # the final pass
+
+
+def test_one_launch_bound_counts_every_stage():
+    # 4-32-32-2, 64 sub-domains, one spec row: 64 rows through T_1 and one through T_2 and T_1
+    # and the last layer, per sub-domain
+    w = wl.get("tiny")
+    f, b = bench.stage_work(w.layers, 1, 64)["fc_net"]
+    assert f == 2.0 * 64 * (64 * 128 + 64 + 1024 + 128)
+    assert b == 4.0 * (128 + 32 + 1024 + 32 + 64 + 2) + 64 * (64 + 4)
