@@ -8,8 +8,8 @@
 // keeps the fragments of its M tile in registers as long as the tile does not change.
 // What bounds them: the epilogue's loads and stores, four bytes a lane (rows of 16 are half a
 // line), more than the matrix work.  Measured, 255 sub-domains of a 28x28 1-16-32-channel net
-// with two rows per neuron: T_2^T of pass 3 70 ms per lane, 0.62 here (41 GFLOP), T_1^T 7.4 and
-// 0.44.  Witness forward of the four-convolution net's pass 5 (12,800 rows, 8 channels): 0.275 ms
+// with two rows per neuron: T_2^T of pass 3 70 ms per lane, 0.31 here (41 GFLOP), T_1^T 7.4 and
+// 0.22.  Witness forward of the four-convolution net's pass 5 (12,800 rows, 8 channels): 0.275 ms
 // a layer with the fp32 kernel of those shapes, 0.18 here with two columns a tile.
 
 // Input row loader: task = (column x, quad of channels, quad of rows q): four 16-byte loads,

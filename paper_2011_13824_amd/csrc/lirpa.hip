@@ -453,7 +453,7 @@ __global__ void __launch_bounds__(kBlock) k_init_rows(DLayer t, const float* __r
 // k-1 (slab sink).  Block: 64 rows x NW waves; each wave covers its share of the coefficients
 // (float4 parameter loads), and the rows' bias terms are summed through LDS in a fixed order.
 // 16 waves from 512 coefficients on: a wave's loop over them is a chain of cache latencies (1,568
-// coefficients, 25,500 rows: 0.306 ms with 4 waves, 0.119 with 16).
+// coefficients, 25,500 rows: 0.152 ms with 4 waves, 0.057 with 16).
 template <int NW, bool SYM>
 __global__ void __launch_bounds__(64 * NW) k_init_fc_rows(DLayer t, const float* __restrict__ WT,
                                                           long Q, Sink s) {
@@ -1875,8 +1875,8 @@ __global__ void __launch_bounds__(64 * (CI + NS + C0))
 // (R = n_k rows per sub-domain, even) and gives both bounds: l = beta - eps ||A_x||_1 and
 // u = up + eps ||A_x||_1, up with the intercepts of the positive entries (those of the negated
 // row) instead of the negative ones' (RowBias).  Half the rows of a bound: the
-// pass of 400 sub-domains of the 8-16-channel net 0.440 -> 0.231 ms, of 1,024 of the
-// 16-32-channel net 2.84 -> 1.53.
+// pass of 400 sub-domains of the 8-16-channel net 0.395 -> 0.208 ms, of 1,024 of the
+// 16-32-channel net 2.80 -> 1.46.
 template <int K, int S, int P, int H1, int W1, int H0, int W0, int CO, int CI, int CPW, int K1,
           int S1, int P1, int HX, int WX, int C0, int NXW, bool FC, int NBS, int SPEC = 0,
           bool TAPE = false, bool SYM = false>
@@ -2604,13 +2604,13 @@ __host__ __device__ inline int p2_groups(int C2) { return C2 / 8; }
 //      writes l_j (sign +) or u_j (sign -) of the sub-domain.
 // The result equals the dense pass exactly in arithmetic terms: the skipped products are zeros.
 // SYM (no given slopes, C2 a multiple of 16): the row -e_j is the negative of +e_j, so the 16
-// rows are 16 channels and each gives both bounds (see k_convT_fc_bound): 0.151 -> 0.095 ms for
-// 400 sub-domains of the 8-16-channel net, 1.24 -> 0.71 for 1,024 of the 16-32-channel net.
+// rows are 16 channels and each gives both bounds (see k_convT_fc_bound): 0.136 -> 0.082 ms for
+// 400 sub-domains of the 8-16-channel net, 1.21 -> 0.65 for 1,024 of the 16-32-channel net.
 template <int K1, int S1, int P1, int K2, int C1, int NW, int XW, bool SYM>
 // (with 8 windows per block the kernel fits 80 VGPRs with 8 channels on T_1, 128 with 16, one
 // more wave per SIMD than it would take unhinted; with 4 it would spill, so it is left alone)
 __global__ void __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) - (SYM ? 1 : 0) : 1, 8)))
+__attribute__((amdgpu_waves_per_eu(XW == 8 ? (C1 >= 16 ? 4 : 6) : 1, 8)))
     k_pass2_window(DLayer t1, DLayer t2, long nb, const float* __restrict__ a_lo,
                const float* __restrict__ a_up, const float* __restrict__ b_up, long pstride,
                const float* __restrict__ z1, float eps, float* __restrict__ L,
@@ -7009,8 +7009,8 @@ int bound_chunk(const Chunk& c, const float* C, float* lb) {
       }
     }
     // (with one row per neuron k_win_pass is the faster kernel: 1,024 sub-domains of the
-    // four-convolution net, pass 3 3.28 -> 2.31 ms, pass 4 2.58 -> 2.40; with two it is not,
-    // 4.30 and 4.49)
+    // four-convolution net, pass 3 3.28 -> 1.70 ms, pass 4 2.57 -> 1.92; with two it is about even
+    // in pass 3, 3.20, and not in pass 4, 3.67)
     const bool symwin = !c.alpha && win_bound_pass(net, k, c.p->split, true);
     if (k == 4 && !symwin && (!c.tape || win_grad_pass(net, k, c.p->split))) {
       int e = pass4_window(c);
@@ -7818,8 +7818,10 @@ int optimize_run(lirpa_net* net, const Plan& p, long Bc, const float* x0, float 
     float* lbt = at<float>(ws, p.off_lbt);
     // A fresh start bounds with the heuristic lower slopes u/(u-l) and sets alpha to them; the
     // bound at t = 0 (alpha at those values, every layer's l and u recomputed from layer 1 up)
-    // then repeats that bound operation for operation.  So with steps to take, the heuristic
-    // bound records the tape and serves as the t = 0 iterate.
+    // then has the same value.  So with steps to take, the heuristic bound records the tape and
+    // serves as the t = 0 iterate.  (Where a pass without given slopes runs one row per neuron in
+    // another kernel than with them, as the four-convolution net's passes 3 and 4 do, the two sum
+    // in other orders, so a run continued from these slopes differs from a fresh one by rounding.)
     const bool t0_done = op.fresh && op.steps > 0;
     if (op.fresh) {
       Chunk h = c;

@@ -22,10 +22,12 @@
 //
 // What bounds it: instructions, the relaxation and split of every window entry and the operand
 // addresses before the matrix work (a block of the four-convolution net's pass 3 issues about
-// 1,700 per wave beside 120 matrix instructions; more positions in flight change nothing).
+// 1,700 per wave beside 120 matrix instructions; more positions in flight change nothing); in
+// that net's pass 4 also its LDS, 108 KB for a bound and 153 KB for the reverse sweep: one block of
+// eight waves a CU, where the registers would hold two.
 // Measured (ms, before and after): 64 sub-domains of the four-convolution net, ten reverse sweeps
 // of passes 3 and 4 with their bounds, dense slabs 209, here 12.2; 255 sub-domains of a 28x28
-// 1-16-32-channel net, pass 2, per-lane gathers 57, here 0.26.
+// 1-16-32-channel net, pass 2, per-lane gathers 57, here 0.215 (0.127 with one row per neuron).
 
 constexpr int kWinMax = 6;   // most layers below the pass's own
 constexpr int kWinLds = 160 * 1024;
