@@ -6,11 +6,14 @@
 // [slot][part][x][row][channel], channels padded to eight; the next step's are loaded into
 // registers before the step's matrix work and parked after it, one barrier a step.  Each wave
 // keeps the fragments of its M tile in registers as long as the tile does not change.
-// What bounds them: the epilogue's loads and stores, four bytes a lane (rows of 16 are half a
-// line), more than the matrix work.  Measured, 255 sub-domains of a 28x28 1-16-32-channel net
-// with two rows per neuron: T_2^T of pass 3 70 ms per lane, 0.31 here (41 GFLOP), T_1^T 7.4 and
-// 0.22.  Witness forward of the four-convolution net's pass 5 (12,800 rows, 8 channels): 0.275 ms
-// a layer with the fp32 kernel of those shapes, 0.18 here with two columns a tile.
+// What bounds them: latency at two waves a SIMD (213 VGPRs with four K steps of fragments): the
+// epilogue's loads and stores, four bytes a lane (rows of 16 are half a line), and the LDS reads,
+// with 3.7 conflict cycles each.  On the net below the relaxing stage keeps the matrix cores 21 %
+// and the VALU 44 % busy at 1.6 TB/s, the concretising one 12 % and 40 % at 1.4.  Measured, 255
+// sub-domains of a 28x28 1-16-32-channel net with two rows per neuron: T_2^T of pass 3 70 ms per
+// lane, 0.31 here (41 GFLOP), T_1^T 7.4 and 0.22.  Witness forward of the four-convolution net's
+// pass 5 (12,800 rows, 8 channels): 0.275 ms a layer with the fp32 kernel of those shapes, 0.18
+// here with two columns a tile.
 
 // Input row loader: task = (column x, quad of channels, quad of rows q): four 16-byte loads,
 // transposed into four 8-byte stores per part.

@@ -6,8 +6,9 @@
 // time, streaming the weight fragments from the cache one K step ahead.  Two output tiles per
 // operand read keep the LDS at half its rate; NT = 4 row tiles per fragment read keep the cache
 // at a quarter of its own.  Measured on a 784-256 layer and 102,400 rows (41 GFLOP): T^T with its
-// sign tape 1.03 ms with the fp32 kernel, 0.31 here (the byte stores of the tape bound it);
-// witness forward 2.61 and 0.26.
+// sign tape 1.03 ms with the fp32 kernel, 0.31 here (0.25 without the tape; matrix cores 35 % and
+// VALU 23 % busy, 1.9 conflict cycles an LDS read, 0.7 TB/s: latency at three waves a SIMD);
+// witness forward 2.61 and 0.26 (21 %, 26 %, 3.8, 1.1 TB/s).
 
 constexpr int kFcThreads = 512;
 

@@ -272,9 +272,9 @@ struct Acc {
 // positive coefficients.  The two are summed apart, term for term as two rows +-e_j would: an upper
 // bias taken as the lower one and sum |a| b_up would cancel the negative intercepts, to rounding
 // (boxes five times the usual radius, 2-norm error of u against 64 bits: 784-256-256-10 net
-// 1.35e-7, here 0.77e-7) and to NaN where they overflow; so would a sum of the intercepts apart from
-// the constants.  The slope of an entry needs no sign there: without given slopes the two are the
-// same.
+// 1.35e-7, here 0.77e-7) and to NaN where they overflow; so would a sum of the intercepts apart
+// from the constants.  The slope of an entry needs no sign there: without given slopes the two are
+// the same.
 template <bool SYM>
 struct RowBias {
   float lo = 0.f, up = 0.f;
@@ -586,7 +586,7 @@ __device__ __forceinline__ void layer1_neuron(const Job& job, long j, int g) {
   }
 }
 
-// (Job: SetupJob, or SetupFrags where there are fragments, whose 1.3 KB of arguments and twice the
+// (Job: SetupJob, or SetupFrags where there are fragments, whose 1 KB of arguments and twice the
 // registers a call without them does not pay for)
 template <class Job>
 __global__ void __launch_bounds__(kBlock) k_setup(Job job_) {

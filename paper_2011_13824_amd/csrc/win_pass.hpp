@@ -21,10 +21,12 @@
 // K = (tap pair j, output channel), N = the 16 rows.
 //
 // What bounds it: instructions, the relaxation and split of every window entry and the operand
-// addresses before the matrix work (a block of the four-convolution net's pass 3 issues about
-// 1,700 per wave beside 120 matrix instructions; more positions in flight change nothing); in
-// that net's pass 4 also its LDS, 108 KB for a bound and 153 KB for the reverse sweep: one block of
-// eight waves a CU, where the registers would hold two.
+// addresses before the matrix work (VALU 78 % and matrix cores 20 % of the SIMD cycles in the bound
+// of a 28x28 net's pass 2, 65 and 16 in the reverse sweep of the four-convolution net's pass 3, 49
+// and 13 in its pass 4; LDS reads with 1 to 2.6 conflict cycles each; a block of that net's pass 3
+// issues about 1,700 per wave beside 120 matrix instructions; more positions in flight change
+// nothing).  In its pass 4 also the LDS, 108 KB for a bound and 153 KB for the reverse sweep: one
+// block of eight waves a CU, where the registers would hold two.
 // Measured (ms, before and after): 64 sub-domains of the four-convolution net, ten reverse sweeps
 // of passes 3 and 4 with their bounds, dense slabs 209, here 12.2; 255 sub-domains of a 28x28
 // 1-16-32-channel net, pass 2, per-lane gathers 57, here 0.215 (0.127 with one row per neuron).
