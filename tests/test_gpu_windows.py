@@ -3,10 +3,11 @@ intermediate bounds and gradients of nets whose windows have every edge the kern
 (strides 1 to 4, kernels 1 to 7 larger than the map, taps that do not divide by the stride,
 channel counts off the 4, 8 and 16 of its tiles, up to four convolutions), and of one whose
 windows do not fit on chip (the dense stages).  The fc nets do the same for the fully connected
-stages, on one tile of rows a block: widths off every tile, and a layer too narrow for the split
-kernels (test_fc_row_tiles runs two and four tiles).  The net nets run the one-launch bound of
-small fully connected nets.  The slab nets end their intermediate pass 4, whose rows come from a
-fully connected layer of even width off the 16 rows of a block, in the two convolutions' kernel.
+stages: widths off every tile, and a layer too narrow for the split kernels.  Their few rows here
+run on one tile of rows a block, whatever their LDS panels would hold; test_fc_row_tiles runs the
+first two on two and four tiles.  The net nets run the one-launch bound of small fully connected
+nets.  The slab nets end their intermediate pass 4, whose rows come from a fully connected layer of
+even width off the 16 rows of a block, in the two convolutions' kernel.
 
 Tolerance: a bound is at most four chained fp32 sums of up to 2,000 terms, each within 8e-7 of its
 2-norm (the fp32 matrix instruction's measured error at that length); with a factor 3 for
@@ -36,9 +37,9 @@ NETS = {
     "k-over-map": [wl.conv(3, 6, 8, 5, 3, 2), wl.conv(8, 2, 33, 1, 1, 0), wl.fc(132, 3)],
     "wide-channels": [wl.conv(3, 6, 40, 3, 1, 1), wl.conv(40, 6, 12, 3, 2, 1), wl.fc(108, 3)],
     "conv-last": [wl.conv(1, 6, 4, 4, 2, 1), wl.conv(4, 3, 16, 3, 1, 1), wl.conv(16, 3, 1, 3, 1, 0)],
-    "fc-odd": [wl.fc(70, 250), wl.fc(250, 67), wl.fc(67, 3)],
-    "fc-even": [wl.fc(50, 330), wl.fc(330, 54), wl.fc(54, 3)],
-    "fc-narrow": [wl.fc(20, 850), wl.fc(850, 20), wl.fc(20, 31), wl.fc(31, 3)],
+    "fc-four-tiles": [wl.fc(70, 250), wl.fc(250, 67), wl.fc(67, 3)],
+    "fc-two-tiles": [wl.fc(50, 330), wl.fc(330, 54), wl.fc(54, 3)],
+    "fc-one-tile": [wl.fc(20, 850), wl.fc(850, 20), wl.fc(20, 31), wl.fc(31, 3)],
     "net-edges": [wl.fc(1, 64), wl.fc(64, 1), wl.fc(1, 33), wl.fc(33, 3)],
     "net-eight-layers": [wl.fc(7, 5), wl.fc(5, 6), wl.fc(6, 7), wl.fc(7, 8), wl.fc(8, 9),
                          wl.fc(9, 10), wl.fc(10, 11), wl.fc(11, 3)],
@@ -94,8 +95,8 @@ def test_windows(name, B):
 
 # Fully connected stages take two tiles of 16 rows a block from 16,384 rows on and four from 32,768:
 # the first pass's rows here, two per neuron with slopes (134 and 108), 54 without
-@pytest.mark.parametrize("name,B", [("fc-odd", 125), ("fc-odd", 251), ("fc-even", 309),
-                                    ("fc-even", 617)])
+@pytest.mark.parametrize("name,B", [("fc-four-tiles", 125), ("fc-four-tiles", 251),
+                                    ("fc-two-tiles", 309), ("fc-two-tiles", 617)])
 def test_fc_row_tiles(name, B):
     arch = NETS[name]
     layers = wl.random_net(arch, B)
@@ -118,8 +119,11 @@ def test_fc_row_tiles(name, B):
                lambda b, j: one_sided(rnet, x0, eps, C, split[some], alpha[some], b, j))
 
 
+SOME = ["four-convs", "k7-stride4", "conv-last", "off-chip", "fc-two-tiles"]
+
+
 @pytest.mark.parametrize("slopes", [False, True])
-@pytest.mark.parametrize("name", ["four-convs", "k7-stride4", "conv-last", "off-chip", "fc-even"])
+@pytest.mark.parametrize("name", SOME)
 def test_other_entry_points(name, slopes):
     # bounds from a parent's and bounds of both sides
     arch, B = NETS[name], 5
@@ -144,7 +148,7 @@ def test_other_entry_points(name, slopes):
           -ref.bound(rnet, x0, eps, -C, split, alpha)[0])
 
 
-@pytest.mark.parametrize("name", ["four-convs", "k7-stride4", "conv-last", "off-chip", "fc-even"])
+@pytest.mark.parametrize("name", SOME)
 def test_optimize_step(name):
     # a fresh start: the heuristic bound, the gradient there (ten times the first moment), and the
     # bound at the slopes after the step
@@ -230,7 +234,7 @@ def test_many_convolutions(convs):
 # range, and in the fifth case all of them and every partial sum inside it (sum |a| b_up is beyond).
 # "gray" with layer 0 scaled: layer 1's bounds are inside the range and their intercepts beyond it;
 # the bounds after the next layer's
-OVERFLOWS = [("fc-odd", 1, 3e37), ("base", 2, 3e37), ("deep", 3, 3e37), ("deep", 4, 3e37),
+OVERFLOWS = [("fc-four-tiles", 1, 3e37), ("base", 2, 3e37), ("deep", 3, 3e37), ("deep", 4, 3e37),
              ("deep", 4, 1e36), ("gray", 0, 1e36)]
 
 
@@ -283,7 +287,8 @@ def test_pass2_by_ones_and_by_eights(few, slopes):
 @pytest.mark.parametrize("layer,scale", [(1, 2e38), (2, 1e38)])
 def test_overflow_in_one_launch(layer, scale):
     # the 4-32-32-2 net, bounded in one launch: the terms in x0 are part of layer 1's constants, so
-    # coefficients over x beyond fp32's range give -inf, not inf - inf, and no bound on the wrong side
+    # coefficients over x beyond fp32's range give -inf, not inf - inf, and no bound on the wrong
+    # side
     layers = wl.random_net(wl.ARCHS["tiny"], 4)
     W = layers[layer]["W"].astype(np.float64)
     layers[layer]["W"] = (W * (scale / np.abs(W).max())).astype(np.float32)
@@ -293,7 +298,7 @@ def test_overflow_in_one_launch(layer, scale):
     lb, l, u = (t.cpu().double().numpy() for t in net.bound(dev(x0), 0.05, dev(C), None, None, B=1,
                                                             want_lu=True))
     lr, llr, ulr, _ = ref.bound(ref.RefNet(layers), x0, 0.05, C, None, None)
-    print(f"{np.isinf(lb).sum()} lb, {np.isinf(l).sum()} l, {np.isinf(u).sum()} u infinite", flush=True)
+    print([int(np.isinf(a).sum()) for a in (lb, l, u)], "infinite", flush=True)
     if layer == 2:
         assert not np.isnan(lb).any()
         assert np.all(lb - lr <= 1e-5 * np.abs(lr))
@@ -302,12 +307,13 @@ def test_overflow_in_one_launch(layer, scale):
 
 # widths, sub-domains, spec rows on each side of every line of the one-launch rule: sub-domains of
 # a two-layer net, of a net wider than 48 with and without slopes, few and many spec rows
-NET_LINES = [([20, 16, 3], 256, 2), ([20, 16, 3], 257, 2), ([48, 49, 3], 512, 31), ([48, 49, 3], 513, 31),
-             ([48, 49, 3], 513, 32), ([48, 49, 3], 1024, 2), ([48, 49, 3], 1025, 2),
-             ([48, 48, 5, 3], 1025, 2), ([64, 7, 5, 3], 2, 32), ([64, 7, 5, 3], 2, 33),
-             ([64, 9, 3], 127, 999), ([64, 9, 3], 128, 999), ([48, 9, 3], 127, 999),
-             ([48, 9, 3], 128, 999), ([20, 16, 3], 2, 480), ([20, 16, 3], 2, 481),
-             ([60, 60, 60, 3], 2, 64), ([60, 60, 60, 3], 2, 65), ([65, 7, 5, 3], 2, 1)]
+NET_LINES = [([20, 16, 3], 256, 2), ([20, 16, 3], 257, 2), ([48, 49, 3], 512, 31),
+             ([48, 49, 3], 513, 31), ([48, 49, 3], 513, 32), ([48, 49, 3], 1024, 2),
+             ([48, 49, 3], 1025, 2), ([48, 48, 5, 3], 1025, 2), ([64, 7, 5, 3], 2, 32),
+             ([64, 7, 5, 3], 2, 33), ([64, 9, 3], 127, 999), ([64, 9, 3], 128, 999),
+             ([48, 9, 3], 127, 999), ([48, 9, 3], 128, 999), ([20, 16, 3], 2, 480),
+             ([20, 16, 3], 2, 481), ([60, 60, 60, 3], 2, 64), ([60, 60, 60, 3], 2, 65),
+             ([65, 7, 5, 3], 2, 1)]
 
 
 @pytest.mark.parametrize("slopes", [False, True])
